@@ -281,49 +281,6 @@ __global__ void k_scale(double* v, long n, const double* num, double target) {
     if (i < n) v[i] *= target / *num;
 }
 
-// eyez, dy, dz of every sweep pair: the line (slab row, plane) of pair q
-// against its candidate's image-shifted centre.  The pair's (slab, plane)
-// list is found by binary search in pair_off.
-__global__ void k_pair_geometry(SweepPair* pairs, long n, const int* pair_off, int nlists, const CandInfo* cand,
-                                int kmax, int nz, int ty, const double* pos, double hy, double hz, double Ly,
-                                double Lz, double inv_rc2) {
-    long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    int lo = 0, hi = nlists;   // pair_off[lo] <= q < pair_off[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) / 2;
-        if (pair_off[mid] <= q) lo = mid;
-        else hi = mid;
-    }
-    const int sl = lo / nz, z = lo - sl * nz;
-    SweepPair& P = pairs[q];
-    if (P.n == 0) {
-        P.eyez = P.dy = P.dz = 0.0;
-        return;
-    }
-    const CandInfo ci = cand[(long)sl * kmax + P.k];
-    const double cy = pos[3 * ci.atom + 1] - (double)ci.sy * Ly;
-    const double cz = pos[3 * ci.atom + 2] - (double)ci.sz * Lz;
-    const double dy = (double)(sl * ty + P.row) * hy - cy;
-    const double dz = (double)z * hz - cz;
-    P.dy = dy;
-    P.dz = dz;
-    P.eyez = exp(-(dy * dy + dz * dz) * inv_rc2);
-}
-
-__global__ void k_pack_proj_pairs(const SweepPair* pairs, long n, ProjPair* out) {
-    long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const SweepPair P = pairs[q];
-    ProjPair R;
-    R.kw = (uint32_t)P.k | ((uint32_t)P.xo << 10) | ((uint32_t)P.run << 18);
-    R.rw = (uint32_t)P.row | ((uint32_t)P.xlo << 8) | ((uint32_t)P.n << 16);
-    R.eyez = P.eyez;
-    R.dy = P.dy;
-    R.dz = P.dz;
-    out[q] = R;
-}
-
 // ------------------------------------------------------------------ host set-up
 
 static long factorial(int n) {
@@ -422,201 +379,6 @@ static double symbol(const double* w, int n_o, double th) {
     return s;
 }
 
-// Per-slab tables of the nonlocal sweep.  The grid is cut into y-slabs of
-// ty rows.  A candidate of a slab is an (atom, periodic image) pair whose
-// support meets the slab; the image shift of a support point is the floor of
-// its unwrapped index over the grid size, so every candidate's points lie
-// inside the periodic cell.  The support of a candidate on one grid line
-// (slab row, plane) is a segment of consecutive x (a ball meets a line in a
-// segment); each (plane, candidate, row) segment is a "pair".  Per (slab,
-// plane) the pairs are listed by (candidate, row), and point p stores the
-// byte indices of its pairs in its plane's list in pe8[p] (0xFF pads).
-void free_slab_tables(NonlocalTables& T) {
-    for (void* p : {(void*)T.pe8, (void*)T.slab_cand, (void*)T.slab_k, (void*)T.pairs, (void*)T.pair_off,
-                    (void*)T.red_off, (void*)T.red_idx, (void*)T.ppairs})
-        if (p) hipFree(p);
-    T.ppairs = nullptr;
-    T.pe8 = nullptr;
-    T.slab_cand = nullptr;
-    T.slab_k = nullptr;
-    T.pairs = nullptr;
-    T.pair_off = nullptr;
-    T.red_off = nullptr;
-    T.red_idx = nullptr;
-    T.slab_ty = 0;
-}
-
-sparc_status build_pair_tables(sparc_gpu_ctx c, const std::vector<uint32_t>& ent, int ty, NonlocalTables& T) {
-    const int nx = c->nx, ny = c->ny, nz = c->nz;
-    const int nslab = (ny + ty - 1) / ty;
-    // slab-local candidate index of every image entry
-    std::vector<std::vector<uint32_t>> cand_key(nslab);
-    std::vector<std::vector<CandInfo>> cands(nslab);
-    struct Tup {
-        uint64_t key;   // (slab, z, k, row) for sorting
-        int x;
-        long e;         // entry index
-    };
-    std::vector<Tup> tup;
-    tup.reserve(ent.size());
-    std::vector<std::unordered_map<uint32_t, int>> kmap(nslab);
-    for (long p = 0; p < c->nd; ++p) {
-        const int x = (int)(p % nx), y = (int)((p / nx) % ny), z = (int)(p / ((long)nx * ny));
-        const int sl = y / ty, row = y - sl * ty;
-        for (int e = c->pe_off_host[p]; e < c->pe_off_host[p + 1]; ++e) {
-            const uint32_t w = ent[e];
-            auto& km = kmap[sl];
-            const auto it = km.find(w);
-            int k = it == km.end() ? -1 : it->second;
-            const int sx = (int)((w >> 20) & 15u) - 8, sz = (int)(w >> 28) - 8;
-            const int ix = x + sx * nx, iz = z + sz * nz;
-            if (k < 0) {
-                k = (int)cands[sl].size();
-                km.emplace(w, k);
-                CandInfo ci;
-                ci.atom = (int)(w & 0xFFFFFu);
-                ci.sx = sx;
-                ci.sy = (int)((w >> 24) & 15u) - 8;
-                ci.sz = sz;
-                ci.ixlo = ci.ixhi = ix;
-                ci.izlo = ci.izhi = iz;
-                cands[sl].push_back(ci);
-            }
-            CandInfo& ci = cands[sl][k];
-            ci.ixlo = std::min(ci.ixlo, ix);
-            ci.ixhi = std::max(ci.ixhi, ix);
-            ci.izlo = std::min(ci.izlo, iz);
-            ci.izhi = std::max(ci.izhi, iz);
-            if (k >= 1023 || row >= 63)
-                return set_err(c, SPARC_ERR_ARG, "projector overlap too dense for the sweep tables");
-            tup.push_back({(((uint64_t)sl * nz + z) << 20) | ((uint64_t)k << 6) | (uint64_t)row, x, e});
-        }
-    }
-    std::sort(tup.begin(), tup.end(), [](const Tup& A, const Tup& B) {
-        return A.key < B.key || (A.key == B.key && A.x < B.x);
-    });
-    // group into pairs; per (slab, plane) the lists are consecutive
-    std::vector<SweepPair> pairs;
-    std::vector<int> pair_off((size_t)nslab * nz + 1, 0);
-    std::vector<int> ent_pair(ent.size(), -1);   // pair index (within its plane list) of every entry
-    int pmax = 0;
-    size_t i = 0;
-    while (i < tup.size()) {
-        const uint64_t sz_key = tup[i].key >> 20;
-        size_t j = i;
-        int npl = 0;
-        while (j < tup.size() && (tup[j].key >> 20) == sz_key) {
-            size_t q = j;
-            while (q < tup.size() && tup[q].key == tup[j].key) ++q;
-            const int xlo = tup[j].x, n = (int)(q - j);
-            if (tup[q - 1].x != xlo + n - 1)
-                return set_err(c, SPARC_ERR_ARG, "projector support is not a segment on a grid line");
-            if (n > 255 || xlo > 255) return set_err(c, SPARC_ERR_ARG, "projector segment too long for the sweep tables");
-            const int sl = (int)(sz_key / nz);
-            SweepPair sp;
-            sp.k = (int)((tup[j].key >> 6) & 1023u);
-            sp.row = (int)(tup[j].key & 63u);
-            sp.xlo = xlo;
-            sp.n = n;
-            sp.run = 0;
-            sp.xo = xlo - (cands[sl][sp.k].ixlo - cands[sl][sp.k].sx * nx);
-            sp.eyez = sp.dy = sp.dz = 0.0;
-            // run length of the candidate's pairs, held by its first pair; a
-            // run never crosses a multiple of 64 in the plane list (empty
-            // pairs pad it), so that one wave holds every run it starts
-            if (npl == 0 || pairs.back().k != sp.k) {
-                int r = 0;
-                for (size_t q2 = j; q2 < tup.size() && (tup[q2].key >> 6) == (tup[j].key >> 6); ++q2)
-                    if (q2 == j || (tup[q2].key & 63u) != (tup[q2 - 1].key & 63u)) ++r;
-                sp.run = r;
-                if (npl % 64 + r > 64) {
-                    SweepPair pad{};
-                    while (npl % 64 != 0) {
-                        pairs.push_back(pad);
-                        ++npl;
-                    }
-                }
-            }
-            if (npl >= 255) return set_err(c, SPARC_ERR_ARG, "more than 255 projector segments in one slab plane");
-            if (sp.xo < 0 || sp.xo > 255) return set_err(c, SPARC_ERR_ARG, "projector support wider than 256 points");
-            for (size_t r = j; r < q; ++r) ent_pair[tup[r].e] = npl;
-            pairs.push_back(sp);
-            ++npl;
-            j = q;
-        }
-        pair_off[sz_key + 1] = npl;
-        pmax = std::max(pmax, npl);
-        i = j;
-    }
-    for (size_t q = 0; q < (size_t)nslab * nz; ++q) pair_off[q + 1] += pair_off[q];
-    // per point: its pairs (at most 7)
-    std::vector<uint64_t> pe8(c->nd, ~0ull);
-    int max_entries = 0;
-    for (long p = 0; p < c->nd; ++p) {
-        uint64_t word = ~0ull;
-        int cnt = 0;
-        for (int e = c->pe_off_host[p]; e < c->pe_off_host[p + 1]; ++e) {
-            if (cnt >= 7) return set_err(c, SPARC_ERR_ARG, "more than 7 projector supports meet at one point");
-            word &= ~(0xFFull << (8 * cnt));
-            word |= (uint64_t)ent_pair[e] << (8 * cnt);
-            ++cnt;
-        }
-        pe8[p] = word;
-        max_entries = std::max(max_entries, cnt);
-    }
-    T.max_entries = max_entries;
-    int kmax = 0, xw = 0;
-    for (int sl = 0; sl < nslab; ++sl) {
-        kmax = std::max(kmax, (int)cands[sl].size());
-        for (auto& ci : cands[sl]) xw = std::max(xw, ci.ixhi - ci.ixlo + 1);
-    }
-    T.slab_kmax = std::max(kmax, 1);
-    T.slab_xw = std::max(xw, 1);
-    T.pair_max = std::max(pmax, 1);
-    std::vector<CandInfo> flat((size_t)nslab * T.slab_kmax);
-    std::vector<int> kcount(nslab);
-    for (int sl = 0; sl < nslab; ++sl) {
-        kcount[sl] = (int)cands[sl].size();
-        for (size_t k = 0; k < cands[sl].size(); ++k) flat[(size_t)sl * T.slab_kmax + k] = cands[sl][k];
-    }
-    // the (slab, candidate) partials of each atom, in (slab, candidate) order
-    std::vector<int> red_off(c->n_atoms + 1, 0), red_idx;
-    {
-        std::vector<std::vector<int>> per_atom(c->n_atoms);
-        for (int sl = 0; sl < nslab; ++sl)
-            for (size_t k = 0; k < cands[sl].size(); ++k)
-                per_atom[cands[sl][k].atom].push_back(sl * T.slab_kmax + (int)k);
-        for (int a = 0; a < c->n_atoms; ++a) {
-            red_off[a + 1] = red_off[a] + (int)per_atom[a].size();
-            red_idx.insert(red_idx.end(), per_atom[a].begin(), per_atom[a].end());
-        }
-    }
-    sparc_status st;
-    if ((st = upload(c, &T.pe8, pe8)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.slab_cand, flat)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.slab_k, kcount)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.pairs, pairs)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.pair_off, pair_off)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.red_off, red_off)) != SPARC_OK) return st;
-    if ((st = upload(c, &T.red_idx, red_idx)) != SPARC_OK) return st;
-    // geometry of every pair on the device
-    if (!pairs.empty()) {
-        k_pair_geometry<<<div_up((long)pairs.size(), 256), 256, 0, c->stream>>>(
-            T.pairs, (long)pairs.size(), T.pair_off, nslab * nz, T.slab_cand, T.slab_kmax, nz, ty, c->atom_pos,
-            c->hy, c->hz, (double)ny * c->hy, (double)nz * c->hz, 1.0 / (c->rc_nl * c->rc_nl));
-        SG_CHECK_LAUNCH(c);
-        SG_HIP(c, hipMalloc((void**)&T.ppairs, pairs.size() * sizeof(ProjPair)));
-        k_pack_proj_pairs<<<div_up((long)pairs.size(), 256), 256, 0, c->stream>>>(T.pairs, (long)pairs.size(),
-                                                                                  T.ppairs);
-        SG_CHECK_LAUNCH(c);
-    }
-    T.slab_ty = ty;
-    if (c->debug)
-        fprintf(stderr, "[sparc_gpu] pair tables: ty %d, %zu pairs, at most %d per plane, %d candidates, ex width %d\n",
-                ty, pairs.size(), T.pair_max, T.slab_kmax, T.slab_xw);
-    return SPARC_OK;
-}
-
 sparc_status build_tables(sparc_gpu_ctx c) {
 #pragma clang fp contract(off)
     const double pi = 3.14159265358979323846;
@@ -701,7 +463,8 @@ sparc_status build_tables(sparc_gpu_ctx c) {
         if (c->n_atoms >= (1 << 20)) return set_err(c, SPARC_ERR_ARG, "too many atoms for the projector tables");
         std::vector<long> sup_off(c->n_atoms + 1, 0);
         std::vector<int> sup_idx, sup_atom, img_off(1, 0), img_ijk;
-        std::vector<std::pair<long, uint32_t>> img_pts;  // (flat point, packed atom/image)
+        std::vector<NlCand> cands;   // (atom, image) pairs
+        std::vector<NlSeg> segs;
         std::vector<long> ip_off(c->n_atoms + 1, 0);
         std::vector<int> ip_idx, box_lo(3 * (size_t)c->n_atoms);
         std::vector<uint32_t> ip_box;
@@ -718,6 +481,8 @@ sparc_status build_tables(sparc_gpu_ctx c) {
             }
             // (flat index, unwrapped i, j, k) of every image point in the ball
             std::vector<std::pair<long, std::array<int, 3>>> pts;
+            const int cand0 = (int)cands.size();
+            int seg_k = lo[2] - 1, seg_j = 0, seg_sx = 0;
             auto fdiv = [](int v, int m) { return (v >= 0) ? v / m : -((-v + m - 1) / m); };
             for (int k = lo[2]; k <= hi[2]; ++k) {
                 double dz = k * h[2] - P[2];
@@ -733,12 +498,22 @@ sparc_status build_tables(sparc_gpu_ctx c) {
                         int wk = ((k % n[2]) + n[2]) % n[2];
                         long flat = wi + (long)n[0] * (wj + (long)n[1] * wk);
                         pts.push_back({flat, {i, j, k}});
-                        // image-level entry of the point: atom and image shifts
-                        int sx = fdiv(i, n[0]), sy = fdiv(j, n[1]), sz = fdiv(k, n[2]);
+                        const int sx = fdiv(i, n[0]), sy = fdiv(j, n[1]), sz = fdiv(k, n[2]);
                         if (sx < -8 || sx > 7 || sy < -8 || sy > 7 || sz < -8 || sz > 7) image_overflow = true;
-                        img_pts.push_back({flat, (uint32_t)a | ((uint32_t)((sx + 8) & 15) << 20) |
-                                                     ((uint32_t)((sy + 8) & 15) << 24) |
-                                                     ((uint32_t)((sz + 8) & 15) << 28)});
+                        if (seg_k != k || seg_j != j || seg_sx != sx) {
+                            // a new line, or the line enters the next image
+                            const int bx = sx * n[0], by = sy * n[1], bz = sz * n[2];
+                            int q = cand0;
+                            while (q < (int)cands.size() &&
+                                   (cands[q].bx != bx || cands[q].by != by || cands[q].bz != bz))
+                                ++q;
+                            if (q == (int)cands.size()) cands.push_back({P[0], P[1], P[2], bx, by, bz, a, a});
+                            segs.push_back({q, wi, wj, wk, 0});
+                            seg_k = k;
+                            seg_j = j;
+                            seg_sx = sx;
+                        }
+                        ++segs.back().n;
                     }
                 }
             }
@@ -771,48 +546,18 @@ sparc_status build_tables(sparc_gpu_ctx c) {
             T.max_per_atom = std::max<int>(T.max_per_atom, (int)(sup_off[a + 1] - sup_off[a]));
         }
         T.n_sup = (long)sup_idx.size();
-        // image-level point-major entries, atom order within a point
+        // the support as line segments of the wrapped grid, per (atom, image) pair
         {
             if (image_overflow)
                 return set_err(c, SPARC_ERR_ARG, "projector support spans too many periodic images");
-            c->pe_off_host.assign(c->nd + 1, 0);
-            for (auto& q : img_pts) c->pe_off_host[q.first + 1]++;
-            for (long p = 0; p < c->nd; ++p) c->pe_off_host[p + 1] += c->pe_off_host[p];
-            std::vector<uint32_t> ent(img_pts.size());
-            std::vector<int> fill(c->pe_off_host.begin(), c->pe_off_host.end() - 1);
-            for (auto& q : img_pts) ent[fill[q.first]++] = q.second;
-            T.n_pe = (long)ent.size();
-            // slab height: from the nonlocal sweep's largest choice down, the
-            // first whose tables fit (at most 255 segments per slab plane, the
-            // FP64 sweep and the two-wave FP64 projection within 160 KB of LDS)
-            for (int ty = choose_sweep_ty(c->nx, c->ny, nl_sweep_max_threads());; --ty) {
-                st = build_pair_tables(c, ent, ty, c->nl);
-                const NonlocalTables& N = c->nl;
-                const size_t lds = st == SPARC_OK
-                                       ? std::max(nl_sweep_lds_bytes(ty, c->nx, c->nz, N.slab_kmax, N.slab_xw, 8),
-                                                  nl_proj_lds_bytes(ty, c->nx, c->nz, N.slab_kmax, N.slab_xw, 2, 8))
-                                       : 0;
-                if (st == SPARC_OK && lds <= 160 * 1024) break;
-                if (ty <= 1) return st != SPARC_OK ? st : set_err(c, SPARC_ERR_ARG, "projector tables exceed LDS");
-                free_slab_tables(c->nl);
-                c->err.clear();
+            std::vector<uint8_t> met(c->nd, 0);
+            for (const NlSeg& s : segs) {
+                uint8_t* m = met.data() + s.x0 + (long)c->nx * (s.y + (long)c->ny * s.z);
+                for (int i = 0; i < s.n; ++i)
+                    if (++m[i] > 7)
+                        return set_err(c, SPARC_ERR_ARG, "more than 7 projector supports meet at one point");
             }
-            c->nl_ty = c->nl.slab_ty;
-            // The FP32 sweep takes slabs of at most 512 threads, like the
-            // local FP32 sweep (measured faster than the FP64 slabs: 13.8
-            // against 15.8 ms at 120^3, 0.80 against 0.92 ms at 72^3); the
-            // projection pass keeps the FP64 tables in both precisions.  If no
-            // such slab fits, the FP32 sweep uses the FP64 tables.
-            for (int ty = choose_sweep_ty(c->nx, c->ny, 512); ty >= 1 && ty != c->nl_ty; --ty) {
-                st = build_pair_tables(c, ent, ty, c->nl32);
-                const NonlocalTables& N = c->nl32;
-                if (st == SPARC_OK &&
-                    nl_sweep_lds_bytes(ty, c->nx, c->nz, N.slab_kmax, N.slab_xw, 4) <= 160 * 1024)
-                    break;
-                free_slab_tables(c->nl32);
-                c->err.clear();
-                st = SPARC_OK;
-            }
+            if ((st = build_nl_pass(c, cands, segs)) != SPARC_OK) return st;
         }
         // Morton order of the atoms (10 bits per axis of the fractional position)
         {
@@ -986,8 +731,6 @@ sparc_status sparc_gpu_create(const sparc_gpu_system* s, void* hip_stream, sparc
     if (const char* e = std::getenv("SPARC_GPU_TRD_TAIL")) c->trd_tail = std::max(0, std::atoi(e));
     if (const char* e = std::getenv("SPARC_GPU_CHOL_MULTI_MIN")) c->chol_multi_min = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_STEIN_LDS_MIN_TPW")) c->stein_lds_min_tpw = std::atoi(e);
-    if (const char* e = std::getenv("SPARC_GPU_PROJ_NB")) c->proj_nb = std::atoi(e);
-    if (const char* e = std::getenv("SPARC_GPU_NL_SLOTS")) c->nl_slots = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_GEMM_TILE")) c->gemm_tile = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_GEMM_NN_COLS")) c->gemm_nn_cols = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_GEMM_NN_ROWS")) c->gemm_nn_rows = std::atoi(e);
@@ -1025,13 +768,11 @@ sparc_status sparc_gpu_destroy(sparc_gpu_ctx c) {
                     c->kp_tile_off, c->kp_tile_atoms, c->kp_proj, c->chol_dorig,
                     c->kp_bounds, c->kp_wts, c->b, c->pois_ux, c->pois_uy, c->pois_uz, c->pois_inv, c->work, c->D,
                     c->D32, c->gemm_part, c->small, c->red, c->scal, c->flags, c->field, c->nl.sup_off,
-                    c->nl.sup_chi, c->nl.gamma4, c->nl.atom_order, c->atom_pos, c->nl.pe8, c->nl.slab_cand,
-                    c->nl.slab_k, c->nl.pairs, c->nl.ppairs, c->nl.pair_off, c->nl.red_off, c->nl.red_idx, c->nl_part,
-                    c->nl32.pe8, c->nl32.slab_cand, c->nl32.slab_k, c->nl32.pairs, c->nl32.ppairs, c->nl32.pair_off,
-                    c->nl32.red_off, c->nl32.red_idx,
+                    c->nl.sup_chi, c->nl.gamma4, c->nl.atom_order, c->atom_pos, c->nl_part,
                     c->nl.ip_off, c->nl.ip_idx, c->nl.ip_box, c->nl.box_lo};
     for (void* p : ptrs)
         if (p) hipFree(p);
+    free_nl_pass(c->nlp);
     for (int i = 0; i < 8; ++i)
         if (c->ev[i]) hipEventDestroy(c->ev[i]);
     for (hipEvent_t e : c->prof_pool) hipEventDestroy(e);

@@ -613,11 +613,8 @@ static sparc_status rr_core(sparc_gpu_ctx c, T* X, int N, long ldx, double* d_ei
 
 template <typename T>
 sparc_status rayleigh_ritz_impl(sparc_gpu_ctx c, T* X, int N, long ldx, double* d_eig, bool check) {
-    return rr_core<T>(c, X, N, ldx, d_eig, check, c->nd, [&](T* Y, T* W) -> sparc_status {
-        sparc_status st = launch_projection<T>(c, Y, N, ldx);
-        if (st != SPARC_OK) return st;
-        return launch_hsweep<T>(c, Y, W, nullptr, N, ldx, 0, 0);
-    });
+    return rr_core<T>(c, X, N, ldx, d_eig, check, c->nd,
+                      [&](T* Y, T* W) -> sparc_status { return apply_impl<T>(c, Y, W, N, ldx); });
 }
 
 // Bloch columns at the context's k: the real embedding of the Hermitian H_k.

@@ -8,33 +8,10 @@
 //   sums the partials in a fixed order in double.
 // gemm_nn: Out = A Bm with A tall (K x M), Bm small (M x N, double, rounded
 //   to the block precision).
-//
-// MFMA 16x16x4 operand layout (one wave): lane l supplies A[i = l%16][k = l/16]
-// and B[k = l/16][j = l%16].  Accumulator register r of lane l holds
-// C[i][j = l%16] with i = 4*(l/16) + r for the f32 instruction and
-// i = l/16 + 4*r for the f64 one (both measured on gfx950).
 #include "internal.hpp"
+#include "mfma.hpp"
 
 namespace sg {
-
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<double> {
-    typedef double acc_t __attribute__((ext_vector_type(4)));
-    static __device__ inline acc_t run(double a, double b, acc_t c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ inline int row(int lane, int r) { return (lane >> 4) + 4 * r; }
-};
-template <>
-struct Mfma<float> {
-    typedef float acc_t __attribute__((ext_vector_type(4)));
-    static __device__ inline acc_t run(float a, float b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ inline int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-};
 
 // Workgroup = 2 x 2 waves; a wave owns (16 MT) x (16 NT) outputs as MT x NT
 // MFMA 16x16 tiles, so a workgroup tile is (32 MT) x (32 NT).  Operands pass

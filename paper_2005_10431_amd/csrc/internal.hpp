@@ -24,38 +24,46 @@ struct StencilCoef {
     T c0;
 };
 
-// An (atom, periodic image) pair whose projector support meets a slab, with
-// the unwrapped x and z index ranges it covers there.
-struct CandInfo {
-    int atom, sx, sy, sz;
-    int ixlo, ixhi, izlo, izhi;
+// An (atom, periodic image) pair of the projector supports: grid point
+// (x, y, z) of the home cell lies at ((x + bx) hx - px, ...) from the image's
+// centre; dcol: the pair's column of D in units of 4 values.
+struct NlCand {
+    double px, py, pz;
+    int bx, by, bz;
+    int atom, dcol;
 };
 
-// One line segment of a candidate's support in the nonlocal sweep: the
-// points x in [xlo, xlo + n) of slab row `row` at one plane z lie in the
-// support of slab candidate k; eyez = exp(-(dy^2 + dz^2)/rc^2) with dy, dz the
-// line's offsets from the candidate's (image-shifted) centre.  The host
-// fills k, row, xlo, n, run, xo; the device the geometry (k_pair_geometry).
-// A plane list may hold empty pairs (n = 0), which contribute nothing.
-struct SweepPair {
-    int k, row, xlo, n;
-    int run;   // first pair of a candidate in its plane list: the candidate's pair count; else 0
-    int xo;    // index of the segment's first point in the candidate's ex table
-    double eyez, dy, dz;
+// One line of a pair's support: n points from (x0, y, z) along x.
+struct NlSeg {
+    int cand, x0, y, z, n;
 };
 
-// The same pair packed for the projection pass (32 bytes):
-// kw = k | xo << 10 | run << 18, rw = row | xlo << 8 | n << 16.
-struct ProjPair {
-    uint32_t kw, rw;
-    double eyez, dy, dz;
+constexpr int kNlBlocks = 6;   // 16-point blocks of a pencil of the nonlocal pass
+
+// A pencil of nb blocks over planes [zb, ze); its pairs are entries ebase .. ebase + ncl - 1
+struct NlUnit {
+    int zb, ze, pencil, nb, ebase, ncl;
+};
+
+// Tables of the nonlocal pass (nonlocal.hip)
+struct NlPass {
+    NlUnit* units = nullptr;
+    int* blk = nullptr;          // first points of the kNlBlocks blocks of each pencil, -1 pads
+    void* dummy = nullptr;       // 256 doubles: target of the stores of pads
+    uint8_t* occ = nullptr;      // per unit zlen x slots: the unit's pair in each slot (255: none)
+    uint64_t* gm = nullptr;      // per unit zlen: slot groups that meet each block
+    int* ent_cand = nullptr;     // pair of every entry
+    NlCand* cand = nullptr;
+    int* red_off = nullptr;      // entries of each atom
+    int* red_ent = nullptr;
+    int slots = 8, zlen = 1, ncl = 1;
+    long n_entries = 0;
+    std::vector<int> layer_off;  // unit ranges of the layers
 };
 
 // Nonlocal projector tables on the device.
-//  - projection: the image points of each atom's ball (ip_*), with the
+//  - Bloch projection: the image points of each atom's ball (ip_*), with the
 //    projector values evaluated from per-axis Gaussian tables;
-//  - apply (inside the sweep): per-slab candidate (atom, image) lists and a
-//    per-point word of candidate indices (pe8, slab_*);
 //  - spectral bound: projector values per unique support point (sup_*).
 struct NonlocalTables {
     int n_atoms = 0;
@@ -64,27 +72,6 @@ struct NonlocalTables {
     double* sup_chi = nullptr; // 4 n_sup projector values (summed over images; for the spectral bound)
     double* gamma4 = nullptr;  // 4 n_atoms: (g_s, g_p, g_p, g_p)
     int* atom_order = nullptr; // atoms in space-filling (Morton) order
-    // number of image-level (point, atom, image) entries; the sweep's
-    // per-slab tables are built from them on the host
-    long n_pe = 0;
-    // per-slab tables of the nonlocal sweep (see build_pair_tables): the
-    // slab's candidate (atom, image) pairs, the line segments (pairs) of each
-    // plane sorted by (candidate, row), and per point the byte indices of its
-    // pairs in its plane's list (0xFF pads)
-    uint64_t* pe8 = nullptr;
-    CandInfo* slab_cand = nullptr;          // [n_slabs][slab_kmax]
-    int* slab_k = nullptr;                  // candidates per slab
-    int slab_kmax = 0, slab_xw = 0;
-    SweepPair* pairs = nullptr;             // all segments, plane lists back to back
-    ProjPair* ppairs = nullptr;             // the same, packed for the projection pass
-    int* pair_off = nullptr;                // n_slabs * nz + 1: list of (slab, plane)
-    int pair_max = 0;                       // longest plane list
-    // the (slab, candidate) partial projections of one atom, in fixed order:
-    // entries slab * slab_kmax + k of red_idx[red_off[a] .. red_off[a + 1])
-    int* red_off = nullptr;
-    int* red_idx = nullptr;
-    int slab_ty = 0;                        // rows per slab of these tables (0: none built)
-    int max_entries = 0;                    // most pairs meeting at one point (at most 7)
     double nl_hi = 0.0, nl_lo = 0.0;  // signed spectral bound contributions
     int max_per_atom = 0;
     // image points of each atom's ball for the projection, in grid order:
@@ -130,7 +117,6 @@ struct sparc_gpu_ctx_s {
     double* force_tab = nullptr;  // per-atom force table: pos (3n), Z (n), rc (n), gamma (4n); on use
     // Bloch k-points (allocated on use)
     double kvec[3] = {0, 0, 0};   // current k (1/Bohr)
-    int sweep_local_only = 0;     // sweeps skip the nonlocal term (Bloch path adds its own)
     int* kp_off = nullptr;        // N_d + 1: point-major projector entries
     uint32_t* kp_ent = nullptr;   // (atom, image) entries
     uint16_t* kp_slot = nullptr;  // per entry: the atom's slot in its point's tile list
@@ -151,9 +137,7 @@ struct sparc_gpu_ctx_s {
     double* b = nullptr;        // pseudocharge, N_d
     double e_self = 0, e_c = 0;
     sg::NonlocalTables nl;
-    // per-slab tables of the FP32 sweep when its slab height differs (only
-    // the per-slab fields are filled; slab_ty 0: it uses nl's)
-    sg::NonlocalTables nl32;
+    sg::NlPass nlp;
 
     // Poisson: real orthonormal Fourier bases per axis and the operator's
     // eigenvalues on the product basis
@@ -166,7 +150,7 @@ struct sparc_gpu_ctx_s {
     void* work = nullptr;       // one block of n_states columns (bytes below)
     size_t work_bytes = 0;
     double* D = nullptr;        // projector coefficients: 4 n_atoms x n_states
-    double* nl_part = nullptr;  // projection partials per (z range, slab, candidate)
+    double* nl_part = nullptr;  // projection partials per (entry, column)
     double* scratch = nullptr;  // this device's fixed scratch array (allocation-free filter)
     size_t scratch_elems = 0;
     size_t nl_part_elems = 0;
@@ -190,8 +174,6 @@ struct sparc_gpu_ctx_s {
 
     // captured Jacobi sweep (see dense.hip)
     hipStream_t cap_stream = nullptr;
-    int proj_nb = 8;            // SPARC_GPU_PROJ_NB: at most this many orbitals per projection workgroup (2, 4, 8)
-    int nl_slots = 0;           // SPARC_GPU_NL_SLOTS=7: FP64 sweep takes 7 nonlocal slots per point (0: by the tables)
     int gemm_tile = 0;          // SPARC_GPU_GEMM_TILE: Gram/projected-H tile edge (128, 160; 0: by size)
     int gemm_nn_cols = 160;     // SPARC_GPU_GEMM_NN_COLS: rotation tile width (160, 288)
     int gemm_nn_rows = 0;       // SPARC_GPU_GEMM_NN_ROWS: rotation tile height (64, 128; 0: 128 FP64, 64 FP32)
@@ -208,8 +190,6 @@ struct sparc_gpu_ctx_s {
     int stein_lds_min_tpw = 3;  // SPARC_GPU_STEIN_LDS_MIN_TPW: fewest solves per workgroup for the LDS inverse iteration
     int chol_multi_min = 384;   // SPARC_GPU_CHOL_MULTI_MIN: N from which Cholesky updates over many workgroups
     double* chol_dorig = nullptr;  // original diagonal for the many-workgroup Cholesky (kEighMaxN)
-    std::vector<int> pe_off_host;  // point offsets of the image-level entries (host)
-    int nl_ty = 6;                 // slab height of the nonlocal sweep
     double* atom_pos = nullptr;    // 3 n_atoms
 
     // kernel timing (sparc_gpu_profile)
@@ -261,30 +241,55 @@ enum Flag {
 };
 
 // ---- kernels (launchers) -------------------------------------------------
-// H application / Chebyshev sweeps. mode: 0 out = H x; 1 first filter step;
-// 2 filter step `step` (>= 2) with xprev = X_{k-1} (may alias out).  With
-// projectors the sweep applies the projections held in the context's D,
-// which launch_projection must have formed from x.
+// Local part of H / Chebyshev sweeps. mode: 0 out = H_loc x; 1 first filter
+// step; 2 filter step `step` (>= 2) with xprev = X_{k-1} (may alias out).
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx,
                            int mode, int step);
-// D = gamma dV chi^T x, streaming x once over the sweep's slabs.  The
-// partial sums go to `part` (part_elems doubles, as many columns at a time
-// as fit) when given, else to context memory sized for the whole block.
+// The nonlocal term of a block in one pass: apply (y += alpha chi D, alpha
+// that of the recurrence for (mode, step), 1 for mode 0) and / or project (D =
+// gamma dV chi^T y of the completed y).  The partial sums go to `part`
+// (part_elems doubles, as many columns at a time as fit) when given, else to
+// context memory sized for the whole block.  Does nothing without projectors.
 template <typename T>
-sparc_status launch_projection(sparc_gpu_ctx c, const T* x, int ncol, long ldx, double* part = nullptr,
-                               size_t part_elems = 0);
+sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool apply, bool project, int mode, int step,
+                     double* part = nullptr, size_t part_elems = 0);
+// Y = H X
+template <typename T>
+sparc_status apply_impl(sparc_gpu_ctx c, const T* X, T* Y, int ncol, long ldx);
 // Chebyshev filter of degree m on X (Wk: scratch block); projection partials
-// as in launch_projection.
+// as in nl_pass.
 template <typename T>
 sparc_status filter_impl(sparc_gpu_ctx c, T* X, T* Wk, int ncol, long ldx, int m, double* part = nullptr,
                          size_t part_elems = 0);
-// LDS bytes of a nonlocal sweep workgroup (slab height ty, nz planes, K
-// candidates, ex tables xw wide) of element size tsize
-size_t nl_sweep_lds_bytes(int ty, int nx, int nz, int K, int xw, size_t tsize);
-// LDS bytes of a projection workgroup of NW waves (one orbital each)
-size_t nl_proj_lds_bytes(int ty, int nx, int nz, int K, int xw, int NW, size_t tsize);
-int nl_sweep_max_threads();   // workgroup size limit of the nonlocal sweep
+// Filter coefficients of step k of the scaled recurrence:
+//   e = (b-a)/2, c = (b+a)/2, sigma_1 = e/(a0-c), tau = 2/sigma_1,
+//   sigma_k = 1/(tau - sigma_{k-1});
+//   step 1: out = (sigma_1/e)(Hx - c x)
+//   step k: out = (2 sigma_k/e)(Hx - c x) - sigma_{k-1} sigma_k xprev
+__device__ inline void filter_coefs(const double* params, int mode, int step, double& alpha, double& cshift,
+                                    double& beta) {
+    alpha = 1.0;
+    cshift = 0.0;
+    beta = 0.0;
+    if (mode == 0) return;
+    double A = params[0], B = params[1], A0 = params[2];
+    double e = 0.5 * (B - A), c = 0.5 * (B + A);
+    double s1 = e / (A0 - c);
+    cshift = c;
+    if (mode == 1) {
+        alpha = s1 / e;
+        return;
+    }
+    double tau = 2.0 / s1;
+    double sp = s1, s = s1;
+    for (int k = 2; k <= step; ++k) {
+        sp = s;
+        s = 1.0 / (tau - s);
+    }
+    alpha = 2.0 * s / e;
+    beta = -sp * s;
+}
 
 // C(MxN, col-major, ldc) = alpha * A^T B, A: K x M (lda), B: K x N (ldb),
 // T inputs, double output, deterministic split-K.
@@ -372,8 +377,8 @@ void prof_end(sparc_gpu_ctx c, int slot, hipStream_t s = nullptr);
 
 // Build geometry tables (ctx.hip)
 sparc_status build_tables(sparc_gpu_ctx c);
-sparc_status build_pair_tables(sparc_gpu_ctx c, const std::vector<uint32_t>& ent, int ty, NonlocalTables& T);
-void free_slab_tables(NonlocalTables& T);
+sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, const std::vector<NlSeg>& segs);
+void free_nl_pass(NlPass& T);
 // Device address of the fixed scratch array on device `dev` (current),
 // looked up once per device and kept in the context.
 sparc_status scratch_init(sparc_gpu_ctx c, int dev);

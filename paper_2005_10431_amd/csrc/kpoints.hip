@@ -632,9 +632,7 @@ static sparc_status bloch_step(sparc_gpu_ctx c, const T* Y, T* out, const T* pre
     if (ldx == 2 * c->nd && lds <= 64 * 1024) {
         // unpadded blocks: the halves u, v are real columns of N_d rows, swept
         // by the Gamma local kernel (recurrence fused); then the Bloch terms
-        c->sweep_local_only = 1;
         st = launch_hsweep<T>(c, Y, out, prev, 2 * ncol, c->nd, mode, step);
-        c->sweep_local_only = 0;
         if (st != SPARC_OK) return st;
         if (nl && !(c->kp_etab_valid && c->kp_etab_k[0] == c->kvec[0] && c->kp_etab_k[1] == c->kvec[1] &&
                     c->kp_etab_k[2] == c->kvec[2])) {

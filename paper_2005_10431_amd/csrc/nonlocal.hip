@@ -1,0 +1,794 @@
+// Nonlocal term of H at the Gamma point (Sec. 2.1: applied through its outer
+// products), V_nl x = sum_I sum_lm chi_Ilm D_Ilm with D = gamma dV chi^T x.
+//
+// The projections D of a block and their application are products with a
+// tall matrix that every orbital shares: chi on a tile of the grid, against
+// 16 orbitals at a time, on MFMA.  One pass over the block does
+//   apply    y += alpha chi D     and / or     project    D' = gamma dV chi^T y,
+// so a filter step is one local sweep followed by one pass that completes
+// its output and forms the projections the next step needs.
+//
+// Layout of the pass (one workgroup = one unit x up to 64 orbitals, 16 per
+// wave):
+//  - the points of a z-plane are cut into blocks of 16 consecutive points
+//    (one 128-byte line in FP64, aligned whenever n_x n_y is a multiple of
+//    16), so that a wave reads and writes whole lines of every orbital: on
+//    24-point pieces of rows instead, a plain read and write of the block
+//    ran at 2.9 instead of 4.3 TB/s at 120^3 x 1200;
+//  - a pencil is up to kNlBlocks blocks that lie close together in x and y; a unit is a
+//    pencil over a range of z;
+//  - along the unit's planes every (atom, image) pair that reaches it holds
+//    one of S slots for its z extent.  A slot's 4 projections stay in
+//    accumulators and its 4 coefficients in registers until it leaves, when
+//    the sums are written as one partial entry (entry, orbital, lm); the
+//    entries of an atom are added in a fixed order by k_nl_reduce, so results
+//    are bitwise reproducible and independent of how columns are grouped;
+//  - per plane the workgroup tabulates chi of the plane's points x slots in
+//    LDS, shared by its orbitals; slots go in groups of four (16 projectors,
+//    one MFMA row tile) and a block skips the groups that do not touch it (a
+//    block of a 4.5-Bohr lattice meets 5.3 pairs in 2.6 groups on average).
+// The accumulator layout of the apply product is the operand layout of the
+// projection product, so a value goes from its load through both without
+// leaving its lane.
+#include <algorithm>
+#include <array>
+#include <cmath>
+#include <map>
+#include <mutex>
+
+#include "internal.hpp"
+#include "mfma.hpp"
+
+namespace sg {
+
+namespace {
+
+constexpr int kIdle = 255;          // slot without a pair
+constexpr int kMaxLocal = 112;      // pairs of a unit (with 24 slots and 128 planes 160 KB of LDS are full)
+constexpr int kMaxPlanes = 128;     // planes of a unit
+constexpr int kMaxSlots = 24;
+constexpr int kNlWaves = 4;         // waves of a workgroup, 16 orbitals each
+
+typedef double nl_d2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float nl_f4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// The four points (of a block's 16) that lane group g holds, and the point of MFMA row i.
+template <typename T>
+struct Pts;
+template <>
+struct Pts<double> {
+    static __device__ inline int of(int g, int r) { return 2 * g + (r & 1) + 8 * (r >> 1); }
+    static __device__ inline int row(int i) { return 2 * (i & 3) + ((i >> 2) & 1) + 8 * (i >> 3); }
+    // position of MFMA row i (slot i % 4, lm i / 4) among a group's 16 (slot, lm) values
+    static __device__ inline int perm(int i) { return 4 * (i & 3) + (i >> 2); }
+    static __device__ inline void load(const double* x, int p0, int g, double* q) {
+        const nl_d2 a = *reinterpret_cast<const nl_d2*>(x + p0 + 2 * g);
+        const nl_d2 b = *reinterpret_cast<const nl_d2*>(x + p0 + 2 * g + 8);
+        q[0] = a.x;
+        q[1] = a.y;
+        q[2] = b.x;
+        q[3] = b.y;
+    }
+    static __device__ inline void store(double* x, int p0, int g, const double* q) {
+        *reinterpret_cast<nl_d2*>(x + p0 + 2 * g) = nl_d2{q[0], q[1]};
+        *reinterpret_cast<nl_d2*>(x + p0 + 2 * g + 8) = nl_d2{q[2], q[3]};
+    }
+};
+template <>
+struct Pts<float> {
+    static __device__ inline int of(int g, int r) { return 4 * g + r; }
+    static __device__ inline int row(int i) { return i; }
+    static __device__ inline int perm(int i) { return i; }
+    static __device__ inline void load(const float* x, int p0, int g, float* q) {
+        const nl_f4 a = *reinterpret_cast<const nl_f4*>(x + p0 + 4 * g);
+        q[0] = a.x;
+        q[1] = a.y;
+        q[2] = a.z;
+        q[3] = a.w;
+    }
+    static __device__ inline void store(float* x, int p0, int g, const float* q) {
+        *reinterpret_cast<nl_f4*>(x + p0 + 4 * g) = nl_f4{q[0], q[1], q[2], q[3]};
+    }
+};
+
+template <typename T>
+struct NlArgs {
+    T* y;
+    long ldx;
+    int nx, ny, nz, nxy, ncol;
+    int nwc, nchunk, nunit;      // MFMA waves per workgroup, column chunks, units
+    int zlen, ncl;               // most planes and pairs of a unit
+    const NlUnit* units;
+    const int* blk;              // first points of the kNlBlocks blocks of each pencil, -1 pads
+    int tail;                    // n_x n_y % 16
+    T* dummy;                    // 256 values: where the places past a pencil's list store
+    const uint8_t* occ;          // per unit zlen x S: pair (local index) in each slot
+    const uint64_t* gm;          // per unit zlen: bit b S/4 + G: block b meets group G
+    const int* ent_cand;         // pair of every entry
+    const NlCand* cand;
+    double hx, hy, hz, inv_rc2, N0, N1, rcut2;
+    const T* D;                  // column j at D + j ldD, 4 per (pair's) atom
+    long ldD;
+    double* part;                // [(entry ncol + col) 4 + lm]
+    const double* params;
+    int mode, step;              // filter step whose output is completed: alpha of the recurrence
+};
+
+// Planes of the sums of one group: FP64 in the accumulators; in FP32 the MFMA
+// sums of one plane (at most 96 points) are added to FP64 sums.
+template <typename T>
+struct GroupSum;
+template <>
+struct GroupSum<double> {
+    typename Mfma<double>::acc_t p{0, 0, 0, 0};
+    __device__ inline void plane() {}
+    __device__ inline double get(int r) const { return p[r]; }
+    __device__ inline void zero() { p = Mfma<double>::acc_t{0, 0, 0, 0}; }
+};
+template <>
+struct GroupSum<float> {
+    typename Mfma<float>::acc_t p{0, 0, 0, 0};
+    double s[4] = {0, 0, 0, 0};
+    __device__ inline void plane() {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] += (double)p[r];
+        p = Mfma<float>::acc_t{0, 0, 0, 0};
+    }
+    __device__ inline double get(int r) const { return s[r]; }
+    __device__ inline void zero() {
+        p = Mfma<float>::acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = 0;
+    }
+};
+
+struct NlLds {
+    size_t gxy, ez, gm, cand, xy, occ, total;
+};
+
+__host__ __device__ inline NlLds nl_lds_layout(size_t ts, int S, int zlen, int ncl) {
+    auto up = [](size_t v) { return (v + 15) & ~(size_t)15; };
+    NlLds L{};
+    const size_t np = 16 * kNlBlocks;
+    size_t o = up(np * (4 * S + 4) * ts);   // chi of the current plane
+    L.gxy = o;                              // per (slot, point): the Gaussian's x-y factor
+    o += up(np * S * ts);
+    L.ez = o;                               // per plane parity and slot: z factor, dz
+    o += 2 * (size_t)S * 16;
+    L.gm = o;
+    o += up((size_t)zlen * 8);
+    L.cand = o;
+    o += up((size_t)ncl * sizeof(NlCand));
+    L.xy = o;
+    o += up(np * sizeof(int));
+    L.occ = o;
+    o += up((size_t)(zlen + 1) * S);
+    L.total = o;
+    return L;
+}
+
+// Offsets and squared distances of grid points from an image's centre in the
+// host tables' own operations (dx^2 + dy^2, then + dz^2), so that a point is
+// inside rcut exactly when the tables say so.
+__device__ inline double off_x(const NlCand& c, int x, double hx) {
+#pragma clang fp contract(off)
+    return (x + c.bx) * hx - c.px;
+}
+__device__ inline double off_y(const NlCand& c, int y, double hy) {
+#pragma clang fp contract(off)
+    return (y + c.by) * hy - c.py;
+}
+__device__ inline double off_z(const NlCand& c, int z, double hz) {
+#pragma clang fp contract(off)
+    return (z + c.bz) * hz - c.pz;
+}
+__device__ inline double sum_sq(double u, double v) {
+#pragma clang fp contract(off)
+    return u * u + v * v;
+}
+__device__ inline double add_sq(double r2, double d) {
+#pragma clang fp contract(off)
+    return r2 + d * d;
+}
+
+__device__ inline double gauss(double v) { return exp(v); }
+__device__ inline float gauss(float v) { return expf(v); }
+
+// AP: y += alpha chi D.  PR: partial projections of (the completed) y.
+// Per plane: barrier; chi of the plane into LDS; barrier; the products.  Two
+// workgroups of four waves fit a compute unit (71 KB of LDS each), so one's
+// table overlaps the other's products.  A wave has the loads of a whole plane
+// (12 KB in FP64) in flight: with half of that and six waves per workgroup
+// the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.
+template <typename T, int S, bool AP, bool PR, bool TAIL>
+__global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
+    using P = Pts<T>;
+    using acc_t = typename Mfma<T>::acc_t;
+    constexpr int NB = kNlBlocks, NG = S / 4, RS = 4 * S + 4, NP = 16 * NB;
+    constexpr int RING = NB;   // blocks in flight per wave: a plane
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const NlLds L = nl_lds_layout(sizeof(T), S, a.zlen, a.ncl);
+    T* chi = reinterpret_cast<T*>(smem_raw);
+    T* gxy = reinterpret_cast<T*>(smem_raw + L.gxy);
+    double* ezdz = reinterpret_cast<double*>(smem_raw + L.ez);
+    uint64_t* gml = reinterpret_cast<uint64_t*>(smem_raw + L.gm);
+    NlCand* cand = reinterpret_cast<NlCand*>(smem_raw + L.cand);
+    int* xy = reinterpret_cast<int*>(smem_raw + L.xy);
+    uint8_t* occ = reinterpret_cast<uint8_t*>(smem_raw + L.occ);
+
+    // block b runs on XCD b % 8: each XCD takes a contiguous range of units
+    const int nblk = gridDim.x, bid = blockIdx.x;
+    const int qn = nblk / 8, rn = nblk % 8;
+    const int xcd = bid % 8;
+    const int logical = xcd * qn + min(xcd, rn) + bid / 8;
+    const int chunk = logical % a.nchunk, u = logical / a.nchunk;
+    const NlUnit U = a.units[u];
+    const int nzl = U.ze - U.zb;
+    const int t = threadIdx.x, nt = blockDim.x;
+    const int* blk = a.blk + (long)U.pencil * NB;
+    // the last block of a plane whose points are no multiple of 16 starts
+    // early; it sits in the last place and leaves the points that the block
+    // before it owns alone
+    const bool part5 = a.tail && blk[NB - 1] == a.nxy - 16;
+    const int nb = U.nb - (part5 ? 1 : 0);   // blocks in the first places
+    T* const dummy = a.dummy + 16 * (threadIdx.x & 15);
+
+    // the unit's tables
+    for (int j = t; j < nzl; j += nt) gml[j] = a.gm[(long)u * a.zlen + j];
+    for (int j = t; j < (nzl + 1) * S; j += nt) occ[j] = j < nzl * S ? a.occ[(long)u * a.zlen * S + j] : (uint8_t)kIdle;
+    for (int j = t; j < U.ncl; j += nt) cand[j] = a.cand[a.ent_cand[U.ebase + j]];
+    for (int j = t; j < NP; j += nt) {
+        const int p = blk[j / 16] + j % 16;
+        const bool own = blk[j / 16] >= 0 && !(part5 && j / 16 == NB - 1 && j % 16 < 16 - a.tail);
+        xy[j] = own ? (p % a.nx) | (p / a.nx) << 16 : -1;
+    }
+    __syncthreads();
+
+    // z factor and dz of the slots' pairs at plane zl
+    auto zfactor = [&](int zl) {
+        if (t < S) {
+            const int o = occ[zl * S + t];
+            if (o != kIdle) {
+                const double dz = off_z(cand[o], U.zb + zl, a.hz);
+                double* e = ezdz + ((zl & 1) * S + t) * 2;
+                e[0] = exp(-dz * dz * a.inv_rc2);
+                e[1] = dz;
+            }
+        }
+    };
+    // chi of plane zl: point-major rows of (slot, lm), zero where the pair
+    // does not reach.  A thread keeps the same (slot, point) places through
+    // the planes; it forms their x-y Gaussian when a pair enters the slot.
+    auto build = [&](int zl) {
+        const uint64_t gm = gml[zl];
+        for (int e = t; e < NP * S; e += nt) {
+            const int s = e / NP, q = e - s * NP;
+            const int o = occ[zl * S + s], w = xy[q];
+            const bool live = o != kIdle && w >= 0;
+            double dx = 0, dy = 0, r2 = 0;
+            if (live) {
+                dx = off_x(cand[o], w & 0xFFFF, a.hx);
+                dy = off_y(cand[o], w >> 16, a.hy);
+                r2 = sum_sq(dx, dy);
+                if (zl == 0 || occ[(zl - 1) * S + s] != o) gxy[e] = (T)exp(-r2 * a.inv_rc2);
+            }
+            if (!((gm >> ((q >> 4) * NG + (s >> 2))) & 1)) continue;
+            T v0 = 0, v1 = 0, v2 = 0, v3 = 0;
+            if (live) {
+                const double* z = ezdz + ((zl & 1) * S + s) * 2;
+                if (add_sq(r2, z[1]) <= a.rcut2) {
+                    const T ex = gxy[e] * (T)z[0];
+                    const T e1 = (T)a.N1 * ex;
+                    v0 = (T)a.N0 * ex;
+                    v1 = e1 * (T)dx;
+                    v2 = e1 * (T)dy;
+                    v3 = e1 * (T)z[1];
+                }
+            }
+            T* r = chi + q * RS + 4 * s;
+            r[0] = v0;
+            r[1] = v1;
+            r[2] = v2;
+            r[3] = v3;
+        }
+    };
+
+    const int wv = t >> 6, lane = t & 63, li = lane & 15, g = lane >> 4;
+    // waves without columns only help to build; lanes past the last column
+    // repeat it (the same loads, results and stores)
+    const bool mine = wv < a.nwc && 16 * (chunk * a.nwc + wv) < a.ncol;
+    const int cl = 16 * (chunk * a.nwc + wv) + li, col = min(cl, a.ncol - 1);
+    T* yc = a.y + (long)col * a.ldx;
+
+    double alpha = 1.0, csh, beta;
+    if (AP) filter_coefs(a.params, a.mode, a.step, alpha, csh, beta);
+    const T al = (T)alpha;
+
+    GroupSum<T> sum[NG];
+    T d[NG][4];
+    int oc[NG];
+#pragma unroll
+    for (int G = 0; G < NG; ++G) {
+        oc[G] = kIdle;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[G][j] = 0;
+    }
+    // the lane's slot of each group at plane zl: a pair that left leaves its
+    // sums behind, one that came brings its coefficients
+    auto slots = [&](int zl) {
+#pragma unroll
+        for (int G = 0; G < NG; ++G) {
+            const int on = occ[zl * S + 4 * G + g];
+            if (on == oc[G]) continue;
+            if (PR) {
+                if (oc[G] != kIdle && cl < a.ncol) {
+                    double* q = a.part + ((long)(U.ebase + oc[G]) * a.ncol + col) * 4;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) q[r] = sum[G].get(r);
+                }
+                sum[G].zero();
+            }
+            if (AP) {
+                const T* Dc = a.D + (long)col * a.ldD + 4 * (on == kIdle ? 0 : cand[on].dcol);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[G][j] = on == kIdle ? (T)0 : al * Dc[j];
+            }
+            oc[G] = on;
+        }
+    };
+
+    // first point of each block (in scalar registers); places past the
+    // pencil's list load the plane's first points and meet no group
+    int pb0[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) pb0[b] = __builtin_amdgcn_readfirstlane(max(0, blk[b]));
+    T q[RING][4];
+    auto load = [&](T* v, int b, int z) { P::load(yc + (long)z * a.nxy, pb0[b], g, v); };
+    if (mine) {
+#pragma unroll
+        for (int b = 0; b < RING; ++b) load(q[b], b, U.zb);
+        slots(0);
+    }
+    zfactor(0);
+
+    for (int z = U.zb; z < U.ze; ++z) {
+        const int zl = z - U.zb;
+        __syncthreads();
+        build(zl);
+        __syncthreads();
+        if (zl + 1 < nzl) zfactor(zl + 1);
+        if (!mine) continue;
+        const uint64_t gv = gml[zl];
+        const uint32_t glo = __builtin_amdgcn_readfirstlane((int)(uint32_t)gv);
+        const uint32_t ghi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(gv >> 32));
+        const uint64_t gm = (uint64_t)ghi << 32 | glo;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
+            T* v = q[b % RING];
+            acc_t acc = {v[0], v[1], v[2], v[3]};
+            // the next block of this ring place; loads and stores take no
+            // branch, so that those in flight can be counted
+            load(v, (b + RING) % NB, b + RING < NB ? z : min(z + 1, U.ze - 1));
+            const T* cb = chi + 16 * b * RS;
+            if (AP) {
+                const T* A = cb + P::row(li) * RS + 4 * g;
+#pragma unroll
+                for (int G = 0; G < NG; ++G)
+                    if ((gb >> G) & 1) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc = Mfma<T>::run(A[16 * G + j], d[G][j], acc);
+                    }
+                T* yp = yc + (long)z * a.nxy + pb0[b];
+                const T o[4] = {acc[0], acc[1], acc[2], acc[3]};
+                if (TAIL && b == NB - 1 && part5) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (P::of(g, r) >= 16 - a.tail) yp[P::of(g, r)] = o[r];
+                } else {
+                    P::store(b < nb ? yp : dummy, 0, g, o);
+                }
+            }
+            if (PR) {
+#pragma unroll
+                for (int G = 0; G < NG; ++G)
+                    if ((gb >> G) & 1) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            sum[G].p = Mfma<T>::run(cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r], sum[G].p);
+                    }
+            }
+        }
+        if (PR) {
+#pragma unroll
+            for (int G = 0; G < NG; ++G) sum[G].plane();
+        }
+        slots(zl + 1);
+    }
+}
+
+// D(4a+lm, col) = gamma_lm dV sum of atom a's entries, in entry order.
+template <typename T>
+__global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ part, int ncol,
+                                                   const int* __restrict__ off, const int* __restrict__ ent,
+                                                   const double* __restrict__ g4, double dV, T* __restrict__ D,
+                                                   long ldD) {
+    const int a = blockIdx.x;
+    const long q = (long)blockIdx.y * blockDim.x + threadIdx.x;
+    if (q >= 4L * ncol) return;
+    const int col = (int)(q / 4), lm = (int)(q % 4);
+    // eight loads in flight, added in order
+    double s = 0.0;
+    const int e1 = off[a + 1];
+    for (int e = off[a]; e < e1; e += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = part[(long)ent[min(e + k, e1 - 1)] * ncol * 4 + q];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (e + k < e1) s += v[k];
+    }
+    D[(long)col * ldD + 4 * a + lm] = (T)(g4[4 * a + lm] * dV * s);
+}
+
+template <typename V>
+sparc_status put(sparc_gpu_ctx c, V** dst, const std::vector<V>& src) {
+    SG_HIP(c, hipMalloc((void**)dst, std::max<size_t>(1, src.size()) * sizeof(V)));
+    if (!src.empty()) SG_HIP(c, hipMemcpy(*dst, src.data(), src.size() * sizeof(V), hipMemcpyHostToDevice));
+    return SPARC_OK;
+}
+
+template <typename T>
+T* D_of(sparc_gpu_ctx c);
+template <>
+double* D_of<double>(sparc_gpu_ctx c) {
+    return c->D;
+}
+template <>
+float* D_of<float>(sparc_gpu_ctx c) {
+    return c->D32;
+}
+
+}  // namespace
+
+void free_nl_pass(NlPass& T) {
+    for (void* p : {(void*)T.units, (void*)T.blk, (void*)T.occ, (void*)T.gm, (void*)T.ent_cand, (void*)T.cand,
+                    (void*)T.red_off, (void*)T.red_ent, T.dummy})
+        if (p) hipFree(p);
+    T = NlPass{};
+}
+
+// The units, slots and block masks of the pass.  segs: every (atom, image)
+// pair's support as line segments of the wrapped grid.
+sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, const std::vector<NlSeg>& segs) {
+    const int nx = c->nx, ny = c->ny, nz = c->nz, nxy = nx * ny;
+    const int nb = (nxy + 15) / 16;
+    NlPass& T = c->nlp;
+    // pencils: cells of rows x x-range, a block belonging to the cell of its
+    // first point, cut into lists of kNlBlocks.  Among the cell shapes take the
+    // one with the fewest block places times the area whose atoms reach it.
+    auto cells = [&](int npx, int by, std::vector<int>& cell) {
+        cell.resize(nb);
+        for (int b = 0; b < nb; ++b) {
+            const int x = (16 * b) % nx, y = (16 * b) / nx;
+            cell[b] = (y / by) * npx + std::min(npx - 1, (int)((long)x * npx / nx));
+        }
+    };
+    int bnpx = 1, bby = 1;
+    double best = 1e300;
+    std::vector<int> cell;
+    for (int by = 1; by <= std::min(6, ny); ++by)
+        for (int npx = 1; npx <= (nx + 15) / 16; ++npx) {
+            cells(npx, by, cell);
+            std::vector<int> cnt((size_t)npx * ((ny + by - 1) / by), 0);
+            for (int b = 0; b < nb; ++b) cnt[cell[b]]++;
+            long np = 0;
+            for (int v : cnt) np += (v + kNlBlocks - 1) / kNlBlocks;
+            const double wx = std::min(c->Lx, ((double)nx / npx + 8) * c->hx), wy = by * c->hy, r = c->rcut_nl;
+            const double cost = (double)np * (wx * wy + 2 * r * (wx + wy) + 3.14159265358979 * r * r);
+            if (cost < best) {
+                best = cost;
+                bnpx = npx;
+                bby = by;
+            }
+        }
+    cells(bnpx, bby, cell);
+    std::vector<std::vector<int>> lists((size_t)bnpx * ((ny + bby - 1) / bby));
+    for (int b = 0; b < nb; ++b) lists[cell[b]].push_back(b);
+    std::vector<int> blk, nblk, pen(nb), place(nb);
+    int npen = 0;
+    for (auto& l : lists) {
+        const int n = (int)l.size();
+        if (!n) continue;
+        const int parts = (n + kNlBlocks - 1) / kNlBlocks, per = (n + parts - 1) / parts;
+        for (int i = 0; i < n; i += per, ++npen) {
+            blk.insert(blk.end(), kNlBlocks, -1);
+            nblk.push_back(std::min(per, n - i));
+            for (int j = i; j < std::min(n, i + per); ++j) {
+                // an incomplete last block starts 16 points before the end of
+                // the plane and takes the last place
+                const bool tail = nxy % 16 != 0 && l[j] == nb - 1;
+                const int at = tail ? kNlBlocks - 1 : j - i;
+                blk[(size_t)npen * kNlBlocks + at] = tail ? nxy - 16 : 16 * l[j];
+                pen[l[j]] = npen;
+                place[l[j]] = at;
+            }
+        }
+    }
+    // z ranges: the count with the fewest planes one after another on a chip
+    // that holds 512 workgroups, a range costing about 3 planes more than its
+    // own (set-up, ends of pairs).  Fixed here, for the context's full block, so
+    // that a column's sums do not depend on the block it comes in.
+    const long per_range = (long)npen * div_up(div_up(c->n_states, 16), kNlWaves);
+    int zs = 0;
+    long least = 0;
+    for (int k = (nz + kMaxPlanes - 1) / kMaxPlanes; k <= std::max(1, nz / 4); ++k) {
+        const long cost = div_up(per_range * k, 512) * (div_up(nz, k) + 3L);
+        if (zs == 0 || cost < least) {
+            zs = k;
+            least = cost;
+        }
+    }
+    const int zlen = (nz + zs - 1) / zs;
+    zs = (nz + zlen - 1) / zlen;
+    // (pencil, pair, plane) -> blocks met
+    struct Hit {
+        int pencil, cand, z;
+        uint32_t mask;
+    };
+    std::vector<Hit> hits;
+    hits.reserve(2 * segs.size());
+    for (const NlSeg& s : segs) {
+        const int p0 = s.x0 + nx * s.y, p1 = p0 + s.n - 1;
+        for (int b = p0 / 16; b <= p1 / 16; ++b) {
+            if (!hits.empty() && hits.back().pencil == pen[b] && hits.back().cand == s.cand && hits.back().z == s.z)
+                hits.back().mask |= 1u << place[b];
+            else
+                hits.push_back({pen[b], s.cand, s.z, 1u << place[b]});
+        }
+    }
+    std::sort(hits.begin(), hits.end(), [](const Hit& A, const Hit& B) {
+        if (A.pencil != B.pencil) return A.pencil < B.pencil;
+        if (A.cand != B.cand) return A.cand < B.cand;
+        return A.z < B.z;
+    });
+    struct Span {
+        int z0, z1, cand;
+        size_t h0, h1;
+    };
+    // slots: each pair takes the lowest free one for its span of planes in the
+    // unit; pairs beyond the slots or the local indices go to a further layer
+    // (a further pass), which supports this dense do not reach in practice
+    struct Placed {
+        int slot, local;
+        Span s;
+    };
+    struct Unit {
+        NlUnit u;
+        std::vector<Placed> p;
+    };
+    std::vector<std::vector<Unit>> layers;
+    int most = 1, ncl = 1;
+    for (int pass = 0; pass < 2; ++pass) {
+        // the first pass only counts the slots an unlimited table would take
+        const int limit = pass == 0 ? 1 << 20 : T.slots;
+        layers.clear();
+        for (size_t i = 0; i < hits.size();) {
+            size_t e = i;
+            while (e < hits.size() && hits[e].pencil == hits[i].pencil) ++e;
+            for (int zr = 0; zr < zs; ++zr) {
+                const int zb = zr * zlen, ze = std::min(nz, zb + zlen);
+                std::vector<Span> sp;
+                for (size_t h = i; h < e;) {
+                    size_t k = h;
+                    Span s{1 << 30, -1, hits[h].cand, 0, 0};
+                    for (; k < e && hits[k].cand == hits[h].cand; ++k)
+                        if (hits[k].z >= zb && hits[k].z < ze) {
+                            if (s.z1 < 0) s.h0 = k;
+                            s.z0 = std::min(s.z0, hits[k].z);
+                            s.z1 = hits[k].z;
+                            s.h1 = k + 1;
+                        }
+                    if (s.z1 >= 0) sp.push_back(s);
+                    h = k;
+                }
+                std::sort(sp.begin(), sp.end(),
+                          [](const Span& A, const Span& B) { return A.z0 != B.z0 ? A.z0 < B.z0 : A.cand < B.cand; });
+                for (int layer = 0; !sp.empty(); ++layer) {
+                    std::vector<int> end;   // last plane of each slot's pair
+                    std::vector<Span> rest;
+                    Unit un;
+                    un.u = NlUnit{zb, ze, hits[i].pencil, nblk[hits[i].pencil], 0, 0};
+                    for (const Span& s : sp) {
+                        size_t q = 0;
+                        while (q < end.size() && end[q] >= s.z0) ++q;
+                        if ((int)q >= limit || (pass == 1 && un.p.size() >= (size_t)kMaxLocal)) {
+                            rest.push_back(s);
+                            continue;
+                        }
+                        if (q == end.size()) end.push_back(0);
+                        end[q] = s.z1;
+                        un.p.push_back({(int)q, (int)un.p.size(), s});
+                    }
+                    un.u.ncl = (int)un.p.size();
+                    if (pass == 0) most = std::max(most, (int)end.size());
+                    else {
+                        ncl = std::max(ncl, un.u.ncl);
+                        if ((int)layers.size() <= layer) layers.emplace_back();
+                        layers[layer].push_back(std::move(un));
+                    }
+                    sp.swap(rest);
+                }
+            }
+            i = e;
+        }
+        if (pass == 0) T.slots = most <= 8 ? 8 : (most <= 16 ? 16 : kMaxSlots);
+    }
+    const int S = T.slots, NG = S / 4;
+    std::vector<NlUnit> units;
+    std::vector<uint8_t> occ;
+    std::vector<uint64_t> gm;
+    std::vector<int> ent_cand;
+    std::vector<std::vector<int>> per_atom(c->n_atoms);
+    T.layer_off.assign(1, 0);
+    for (auto& ly : layers) {
+        // units of one z range and neighbouring pencils side by side
+        std::stable_sort(ly.begin(), ly.end(), [](const Unit& A, const Unit& B) { return A.u.zb < B.u.zb; });
+        for (Unit& un : ly) {
+            un.u.ebase = (int)ent_cand.size();
+            const size_t o0 = occ.size(), g0 = gm.size();
+            occ.insert(occ.end(), (size_t)zlen * S, (uint8_t)kIdle);
+            gm.insert(gm.end(), zlen, 0);
+            for (const Placed& p : un.p) {
+                per_atom[cands[p.s.cand].atom].push_back((int)ent_cand.size());
+                ent_cand.push_back(p.s.cand);
+                for (int z = p.s.z0; z <= p.s.z1; ++z) occ[o0 + (size_t)(z - un.u.zb) * S + p.slot] = (uint8_t)p.local;
+                for (size_t h = p.s.h0; h < p.s.h1; ++h) {
+                    if (hits[h].z < un.u.zb || hits[h].z >= un.u.ze) continue;
+                    uint64_t& w = gm[g0 + hits[h].z - un.u.zb];
+                    for (int b = 0; b < kNlBlocks; ++b)
+                        if ((hits[h].mask >> b) & 1) w |= 1ull << (b * NG + p.slot / 4);
+                }
+            }
+            units.push_back(un.u);
+        }
+        T.layer_off.push_back((int)units.size());
+    }
+    std::vector<int> roff(c->n_atoms + 1, 0), rent;
+    for (int a = 0; a < c->n_atoms; ++a) {
+        rent.insert(rent.end(), per_atom[a].begin(), per_atom[a].end());
+        roff[a + 1] = (int)rent.size();
+    }
+    T.zlen = zlen;
+    T.ncl = ncl;
+    SG_HIP(c, hipMalloc(&T.dummy, 256 * sizeof(double)));
+    T.n_entries = (long)ent_cand.size();
+    sparc_status st;
+    if ((st = put(c, &T.units, units)) != SPARC_OK) return st;
+    if ((st = put(c, &T.blk, blk)) != SPARC_OK) return st;
+    if ((st = put(c, &T.occ, occ)) != SPARC_OK) return st;
+    if ((st = put(c, &T.gm, gm)) != SPARC_OK) return st;
+    if ((st = put(c, &T.ent_cand, ent_cand)) != SPARC_OK) return st;
+    if ((st = put(c, &T.cand, cands)) != SPARC_OK) return st;
+    if ((st = put(c, &T.red_off, roff)) != SPARC_OK) return st;
+    if ((st = put(c, &T.red_ent, rent)) != SPARC_OK) return st;
+    if (c->debug)
+        fprintf(stderr,
+                "[sparc_gpu] nonlocal pass: %d pencils (%d x-ranges, %d rows), %zu units of %d planes, %d slots (%d "
+                "used), %zu layers, %ld entries, at most %d pairs per unit\n",
+                npen, bnpx, bby, units.size(), zlen, S, most, layers.size(), T.n_entries, ncl);
+    return SPARC_OK;
+}
+
+template <typename T, int S>
+static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T>& a, bool ap, bool pr, size_t shmem) {
+    const long nblocks = (long)a.nunit * a.nchunk;
+    if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "nonlocal pass: too many blocks");
+    const dim3 g((unsigned)nblocks), b(64 * std::max(4, a.nwc));
+    if (!ap) k_nl_pass<T, S, false, true, false><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail && pr) k_nl_pass<T, S, true, true, true><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail) k_nl_pass<T, S, true, false, true><<<g, b, shmem, c->stream>>>(a);
+    else if (pr) k_nl_pass<T, S, true, true, false><<<g, b, shmem, c->stream>>>(a);
+    else k_nl_pass<T, S, true, false, false><<<g, b, shmem, c->stream>>>(a);
+    SG_CHECK_LAUNCH(c);
+    return SPARC_OK;
+}
+
+// One pass over a block: apply (y += alpha chi D, alpha that of filter step
+// `step` of mode `mode`) and / or project (D = gamma dV chi^T y).
+template <typename T>
+sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step, double* part,
+                     size_t part_elems) {
+    const NlPass& N = c->nlp;
+    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
+    const size_t per_col = (size_t)N.n_entries * 4;
+    int group = ncol;
+    if (pr) {
+        if (part) {
+            // caller memory: as many columns at a time as it holds, whole
+            // 16-column tiles where it can
+            if (per_col > part_elems)
+                return set_err(c, SPARC_ERR_ARG, "projection partials of one column exceed the fixed scratch array");
+            group = (int)std::min<size_t>((size_t)ncol, part_elems / per_col);
+            if (group >= 16 && group < ncol) group -= group % 16;
+        } else {
+            const size_t need = per_col * ncol;
+            if (c->nl_part_elems < need) {
+                if (c->nl_part) {
+                    SG_HIP(c, hipStreamSynchronize(c->stream));
+                    SG_HIP(c, hipFree(c->nl_part));
+                    c->nl_part = nullptr;
+                    c->nl_part_elems = 0;
+                }
+                SG_HIP(c, hipMalloc((void**)&c->nl_part, need * sizeof(double)));
+                c->nl_part_elems = need;
+            }
+            part = c->nl_part;
+        }
+    }
+    NlArgs<T> a;
+    a.ldx = ldx;
+    a.nx = c->nx;
+    a.ny = c->ny;
+    a.nz = c->nz;
+    a.nxy = c->nx * c->ny;
+    a.zlen = N.zlen;
+    a.ncl = N.ncl;
+    a.blk = N.blk;
+    a.tail = a.nxy % 16;
+    a.dummy = reinterpret_cast<T*>(N.dummy);
+    a.ent_cand = N.ent_cand;
+    a.cand = N.cand;
+    a.hx = c->hx;
+    a.hy = c->hy;
+    a.hz = c->hz;
+    a.inv_rc2 = 1.0 / (c->rc_nl * c->rc_nl);
+    a.N0 = std::pow(2.0 / (3.14159265358979323846 * c->rc_nl * c->rc_nl), 0.75);
+    a.N1 = (2.0 / c->rc_nl) * a.N0;
+    a.rcut2 = c->rcut_nl * c->rcut_nl;
+    a.ldD = 4L * c->n_atoms;
+    a.part = part;
+    a.params = c->scal + S_A;
+    a.mode = mode;
+    a.step = step;
+    const size_t shmem = nl_lds_layout(sizeof(T), N.slots, N.zlen, N.ncl).total;
+    if (shmem > 160 * 1024) return set_err(c, SPARC_ERR_ARG, "nonlocal pass needs more than 160 KB of LDS");
+    const int slot = prof_begin(c, PK_PROJ);
+    const int nl = (int)N.layer_off.size() - 1;
+    for (int c0 = 0; c0 < ncol; c0 += group) {
+        a.ncol = std::min(group, ncol - c0);
+        a.y = y + (long)c0 * ldx;
+        a.D = D_of<T>(c) + (long)c0 * a.ldD;
+        const int tiles = div_up(a.ncol, 16);
+        a.nchunk = div_up(tiles, kNlWaves);
+        a.nwc = div_up(tiles, a.nchunk);
+        // with further layers every apply comes before the first projection
+        for (int half = 0; half < (nl > 1 ? 2 : 1); ++half) {
+            const bool ap1 = ap && half == 0, pr1 = pr && (nl == 1 || half == 1);
+            if (!ap1 && !pr1) continue;
+            for (int l = 0; l < nl; ++l) {
+                const long u0 = N.layer_off[l];
+                a.nunit = N.layer_off[l + 1] - (int)u0;
+                a.units = N.units + u0;
+                a.occ = N.occ + u0 * N.zlen * N.slots;
+                a.gm = N.gm + u0 * N.zlen;
+                sparc_status st = N.slots == 8    ? launch_pass<T, 8>(c, a, ap1, pr1, shmem)
+                                  : N.slots == 16 ? launch_pass<T, 16>(c, a, ap1, pr1, shmem)
+                                                  : launch_pass<T, kMaxSlots>(c, a, ap1, pr1, shmem);
+                if (st != SPARC_OK) return st;
+            }
+        }
+        if (pr) {
+            k_nl_reduce<T><<<dim3(c->n_atoms, div_up(4L * a.ncol, 256)), 256, 0, c->stream>>>(
+                part, a.ncol, N.red_off, N.red_ent, c->nl.gamma4, c->dV, D_of<T>(c) + (long)c0 * a.ldD, a.ldD);
+            SG_CHECK_LAUNCH(c);
+        }
+    }
+    prof_end(c, slot);
+    return SPARC_OK;
+}
+
+template sparc_status nl_pass<double>(sparc_gpu_ctx, double*, int, long, bool, bool, int, int, double*, size_t);
+template sparc_status nl_pass<float>(sparc_gpu_ctx, float*, int, long, bool, bool, int, int, double*, size_t);
+
+}  // namespace sg

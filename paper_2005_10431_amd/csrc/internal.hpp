@@ -61,6 +61,13 @@ struct NlPass {
     std::vector<int> layer_off;  // unit ranges of the layers
 };
 
+// Shape of a sweep over ncol columns (see sweep_plan)
+struct SweepPlan {
+    int ncol = 0, forced = 0;        // what it was made for
+    int ty = 0, threads = 0;         // rows of a slab, threads of its workgroup
+    int round = 1, split = 1;        // workgroups an XCD holds, z ranges past its last full round
+};
+
 // Nonlocal projector tables on the device.
 //  - Bloch projection: the image points of each atom's ball (ip_*), with the
 //    projector values evaluated from per-axis Gaussian tables;
@@ -138,6 +145,7 @@ struct sparc_gpu_ctx_s {
     double e_self = 0, e_c = 0;
     sg::NonlocalTables nl;
     sg::NlPass nlp;
+    sg::SweepPlan sweep_plans[2];   // FP32, FP64: of the last block width
 
     // Poisson: real orthonormal Fourier bases per axis and the operator's
     // eigenvalues on the product basis
@@ -382,7 +390,6 @@ void free_nl_pass(NlPass& T);
 // Device address of the fixed scratch array on device `dev` (current),
 // looked up once per device and kept in the context.
 sparc_status scratch_init(sparc_gpu_ctx c, int dev);
-int choose_sweep_ty(int nx, int ny, int max_threads);
 
 inline int div_up(long a, long b) { return (int)((a + b - 1) / b); }
 

@@ -9,17 +9,23 @@
 // nonlocal pass (nonlocal.hip) then completes X_{k+1} and forms its
 // projections for the next degree.
 //
-// Sweep kernel layout (one workgroup = one orbital x one y-slab x all z):
+// Sweep kernel layout (one workgroup = one orbital x one y-slab x a range of z):
+//  - a thread holds VX consecutive x points (16 bytes), so that loads, stores
+//    and the x and y reads from LDS move whole vectors and the address work is
+//    shared by VX points;
 //  - the slab is `ty` full x-rows; periodic x wraps inside LDS (padded rows),
 //    so only y needs halo rows, read from L2 where a neighbouring slab of the
 //    same orbital (mapped to the same XCD, see the block mapping below)
 //    loaded them recently enough, else from the last-level cache or HBM;
 //  - z is marched with a register ring of RING = 13 + PR planes per thread:
 //    planes z-6 .. z+6 in use and PR planes in flight, so every point of X_k
-//    is fetched once per sweep (plus the 12 periodic wrap planes);
+//    is fetched once per sweep (plus the 12 planes around the range);
 //  - the halo rows, X_{k-1} and V_eff of the coming planes sit in PQ-deep
 //    register queues, so each load has PQ plane steps to land;
-//  - two LDS plane buffers alternate so one barrier per plane suffices.
+//  - two LDS plane buffers alternate so one barrier per plane suffices;
+//  - a workgroup takes all of z, except those of a compute unit's last,
+//    incomplete round (or of a block too small to fill the chip), which are
+//    cut into equal z ranges (see sweep_split).
 #include <cmath>
 #include <map>
 #include <mutex>
@@ -38,29 +44,46 @@ struct SweepArgs {
     int nx, ny, nz;
     int ty, ntiles_y;
     int grp;          // orbitals whose copies of a slab are dispatched side by side
-    // -1/2 Delta_h with the y and z coefficients proportional to the x ones
-    // (same weights over h_y^2, h_z^2): ck[q] multiplies
-    // (x-pair + ry y-pair + rz z-pair) at distance q, c0 the point itself
+    // -1/2 Delta_h: c*[q] multiplies the pair at distance q, c0 the point itself
     double c0;
-    T ck[kMaxHalfOrder + 1], ry, rz;
+    T cx[kMaxHalfOrder + 1], cy[kMaxHalfOrder + 1], cz[kMaxHalfOrder + 1];
     const T* veff;
     const double* params;  // a, b, a0 on the device
     int step;
     int ncol;
+    int round, split;      // workgroups an XCD holds at once; z ranges of those past its last full round
 };
 
 constexpr int kRing = 16;            // z-ring slots: planes z-6 .. z+6 and 3 in flight
 constexpr int kRingAhead = kRing - 2 * kMaxHalfOrder - 1;
 constexpr int kQueue = 2;            // depth of the halo / X_{k-1} / V_eff queues
 static_assert(kRing % kQueue == 0, "the unrolled step count must cycle every queue");
+constexpr int kSweepPad = 8;         // columns left and right of a row in LDS
+
+// values of a row in LDS: 8 on both sides, a multiple of 4
+__host__ __device__ inline int sweep_row(int nx) { return (nx + 2 * kSweepPad + 3) / 4 * 4; }
+
+// Threads of a workgroup at most, and waves a compute unit holds: three per
+// SIMD at 168 VGPRs (FP32 with two points per thread and four waves per SIMD
+// took 275 instead of 254 us at 72^3 x 260).
+constexpr int kSweepThreads = 768;
+constexpr int kSweepWaves = 12;
+
+template <typename T, int N, int A>
+struct VecOf {
+    typedef T type __attribute__((ext_vector_type(N), aligned(A)));
+};
+
 // The sweep.  MODE: 0 out = H_loc x; 1 first filter step; 2 filter step `step`
-// (>= 2) with xprev = X_{k-1} (may alias out).  HM: halo values per thread and
-// plane.
+// (>= 2) with xprev = X_{k-1} (may alias out).  VX: points per thread; ALN: n_x
+// is a multiple of VX (else the last thread of a row starts VX points before
+// its end and stores only the points the thread before it does not hold).
+// HM: halo vectors per thread and plane.
 //
 // One z-plane step at ring phase U (z = z0 + U).  On entry the LDS buffer of
 // parity U holds plane z (own rows with x-wrap padding and halo rows), written
 // during the previous step.
-//  1. barrier, then the loads of the halo values of plane z + PQ and of ring
+//  1. barrier, then the loads of the halo rows of plane z + PQ and of ring
 //     plane z + 6 + PR (plane indices wrap, so the loads are unconditional);
 //  2. stencil + potential + recurrence for plane z, store;
 //  3. load X_{k-1} and V_eff of plane z + PQ into the queue slot plane z has
@@ -68,24 +91,36 @@ static_assert(kRing % kQueue == 0, "the unrolled step count must cycle every que
 //  4. plane z + 1 into the other LDS buffer.
 // Threads without a point of the slab (ragged slab, padding to 64) load valid
 // clamped addresses and compute on them, but never store.
-template <typename T, int MODE, int HM>
-__global__ __launch_bounds__(1024) void k_hsweep(SweepArgs<T> a) {
+template <typename T, int VX, bool ALN, int MODE, int HM>
+__global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
     constexpr int NO = kMaxHalfOrder;
     constexpr int RING = kRing, PR = kRingAhead, PQ = kQueue;
+    constexpr int PAD = kSweepPad;
+    using gv = typename VecOf<T, VX, sizeof(T)>::type;                     // in global memory
+    using lv = typename VecOf<T, VX, ALN ? VX * sizeof(T) : sizeof(T)>::type;   // in LDS
+    using rv = typename VecOf<T, VX, VX * sizeof(T)>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int W = nx + 2 * NO;
+    const int W = sweep_row(nx);
     const int R = a.ty + 2 * NO;
 
     // Hardware dispatches block b to XCD b % 8.  Give each XCD a contiguous
     // range of logical tiles so that the y-slabs of one orbital (which read
     // each other's rows as halos) share an L2.  Within a group of grp
     // orbitals the logical order is slab-major, so that the grp copies of a
-    // slab (which read the same V_eff rows and point words) run side by side.
-    const int nblk = gridDim.x, bid = blockIdx.x;
-    const int qn = nblk / 8, rn = nblk % 8;
-    const int xcd = bid % 8, bslot = bid / 8;
-    const int logical = xcd * qn + min(xcd, rn) + bslot;
+    // slab (which read the same V_eff rows) run side by side.
+    const int ntile = a.ncol * a.ntiles_y;
+    const int xcd = blockIdx.x % 8, bslot = blockIdx.x / 8;
+    const int mine = ntile / 8 + (xcd < ntile % 8 ? 1 : 0);      // tiles of this XCD
+    const int full = mine / a.round * a.round;                   // of them in full rounds
+    int item = bslot, zpart = 0, zparts = 1;
+    if (bslot >= full) {
+        zparts = a.split;
+        item = full + (bslot - full) / a.split;
+        zpart = (bslot - full) % a.split;
+    }
+    if (item >= mine) return;
+    const int logical = xcd * (ntile / 8) + min(xcd, ntile % 8) + item;
     const int gsz = a.grp * a.ntiles_y;
     const int gi = logical / gsz, gr = logical - gi * gsz;
     const int gcols = min(a.grp, a.ncol - gi * a.grp);   // the last group may be short
@@ -93,11 +128,18 @@ __global__ __launch_bounds__(1024) void k_hsweep(SweepArgs<T> a) {
     const int col = gi * a.grp + (gr - tile * gcols);
     const int y0 = tile * a.ty;
     const int tyn = min(a.ty, ny - y0);
+    const int zlen = (nz + zparts - 1) / zparts;
+    const int zb = zpart * zlen, ze = min(nz, zb + zlen);
+    if (zb >= ze) return;
 
     const int t = threadIdx.x;
     const int nt = blockDim.x;
-    const int lx = t % nx, ly = t / nx;
+    const int LW = (nx + VX - 1) / VX;
+    const int lx = t % LW, ly = t / LW;
+    const int x0 = ALN ? lx * VX : min(lx * VX, nx - VX);
+    const int e0 = lx * VX - x0;              // first point this thread stores
     const bool active = ly < tyn;
+    const bool wleft = x0 < NO, wright = x0 + VX > nx - NO;   // wraps into the padding
     const long plane = (long)nx * ny;
 
     T* const buf0 = reinterpret_cast<T*>(smem_raw);
@@ -106,34 +148,27 @@ __global__ __launch_bounds__(1024) void k_hsweep(SweepArgs<T> a) {
     const T* __restrict__ xc = a.x + (long)col * a.ldx;
     T* __restrict__ oc = a.out + (long)col * a.ldx;
     const T* __restrict__ pc = a.xprev ? a.xprev + (long)col * a.ldx : xc;
-    const long pxy = lx + (long)nx * (y0 + (active ? ly : 0));
-    const int lrow = ((active ? ly : 0) + NO) * W + NO + lx;
-    // halo rows: 2 NO rows of nx values per plane, spread over the threads
-    int goff[HM], loff[HM], poff[HM];
+    const long pxy = x0 + (long)nx * (y0 + (active ? ly : 0));
+    const int lrow = ((active ? ly : 0) + NO) * W + PAD + x0;
+    auto ld = [](const T* p) -> rv { return *reinterpret_cast<const gv*>(p); };
+    // halo rows: 2 NO rows of LW vectors per plane, spread over the threads
+    int goff[HM], loff[HM];
     int hn = 0;
-    const int nhalo = 2 * NO * nx;
+    const int nhalo = 2 * NO * LW;
 #pragma unroll
     for (int i = 0; i < HM; ++i) {
         const int e = t + i * nt;
         goff[i] = 0;
         loff[i] = 0;
-        poff[i] = -1;
         if (e < nhalo) {
             hn = i + 1;
-            int hr = e / nx, hx = e - hr * nx;
-            int lr, gy;
-            if (hr < NO) {
-                lr = hr;
-                gy = y0 - NO + hr;
-            } else {
-                lr = NO + tyn + (hr - NO);
-                gy = y0 + tyn + (hr - NO);
-            }
+            const int hr = e / LW, hl = e - hr * LW;
+            const int hx = ALN ? hl * VX : min(hl * VX, nx - VX);
+            const int lr = hr < NO ? hr : tyn + hr;
+            int gy = y0 - NO + lr;
             gy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
             goff[i] = hx + nx * gy;
-            loff[i] = lr * W + NO + hx;
-            if (hx < NO) poff[i] = loff[i] + nx;
-            if (hx >= nx - NO) poff[i] = loff[i] - nx;
+            loff[i] = lr * W + PAD + hx;
         }
     }
 
@@ -144,109 +179,162 @@ __global__ __launch_bounds__(1024) void k_hsweep(SweepArgs<T> a) {
     const T alpha = (T)alpha_d, beta = (T)beta_d, cc = (T)(a.c0 - c_d);
     auto wz = [nz](int z) { return z >= nz ? z - nz : (z < 0 ? z + nz : z); };
 
-    T q[RING];
-    T hq[PQ][HM];
-    T xp[PQ], ve[PQ];
-    // ring: planes -6 .. 5 + PR (slot = plane mod RING); queues: planes 0 .. PQ-1
+    rv q[RING];
+    rv hq[PQ][HM];
+    rv xp[PQ], ve[PQ];
+    // ring: planes zb - 6 .. zb + 5 + PR (slot = plane - zb mod RING); queues: planes zb .. zb + PQ - 1
 #pragma unroll
-    for (int j = -NO; j <= NO - 1 + PR; ++j) q[(j + 2 * RING) % RING] = xc[pxy + (long)wz(j) * plane];
+    for (int j = -NO; j <= NO - 1 + PR; ++j) q[(j + 2 * RING) % RING] = ld(xc + pxy + (long)wz(zb + j) * plane);
 #pragma unroll
     for (int j = 0; j < PQ; ++j) {
-        const long zo = (long)wz(j) * plane;
-        xp[j] = MODE == 2 ? __builtin_nontemporal_load(&pc[pxy + zo]) : (T)0;
-        ve[j] = a.veff[pxy + zo];
+        const long zo = (long)wz(zb + j) * plane;
+        if (MODE == 2) xp[j] = __builtin_nontemporal_load(reinterpret_cast<const gv*>(pc + pxy + zo));
+        ve[j] = ld(a.veff + pxy + zo);
     }
 #pragma unroll
     for (int j = 1; j < PQ; ++j)
 #pragma unroll
-        for (int i = 0; i < HM; ++i) hq[j][i] = (i < hn) ? xc[goff[i] + (long)wz(j) * plane] : (T)0;
-    // plane 0 into LDS buffer 0
-    if (active) {
-        buf0[lrow] = q[0];
-        if (lx < NO) buf0[lrow + nx] = q[0];
-        if (lx >= nx - NO) buf0[lrow - nx] = q[0];
-    }
+        for (int i = 0; i < HM; ++i) hq[j][i] = ld(xc + goff[i] + (long)wz(zb + j) * plane);
+    // own points of one plane into a buffer, with the x-wrap copies
+    auto put = [&](T* buf, rv v) {
+        if (active) {
+            *reinterpret_cast<lv*>(buf + lrow) = v;
+            if (wleft) *reinterpret_cast<lv*>(buf + lrow + nx) = v;
+            if (wright) *reinterpret_cast<lv*>(buf + lrow - nx) = v;
+        }
+    };
+    put(buf0, q[0]);
 #pragma unroll
     for (int i = 0; i < HM; ++i)
-        if (i < hn) {
-            const T v = xc[goff[i]];
-            buf0[loff[i]] = v;
-            if (poff[i] >= 0) buf0[poff[i]] = v;
-        }
+        if (i < hn) *reinterpret_cast<lv*>(buf0 + loff[i]) = ld(xc + goff[i] + (long)zb * plane);
 
-    for (int z0 = 0; z0 < nz; z0 += RING) {
+    for (int z0 = zb; z0 < ze; z0 += RING) {
 #pragma unroll
         for (int U = 0; U < RING; ++U) {
             const int z = z0 + U;
-            if (z >= nz) break;
+            if (z >= ze) break;
             const int P = U & 1, QS = U % PQ, QN = (U + 1) % PQ;
             __syncthreads();
             // 1. loads of later planes
             {
                 const long zo = (long)wz(z + PQ) * plane;
 #pragma unroll
-                for (int i = 0; i < HM; ++i) hq[QS][i] = (i < hn) ? xc[goff[i] + zo] : (T)0;
-                q[(U + NO + PR + RING) % RING] = xc[pxy + (long)wz(z + NO + PR) * plane];
+                for (int i = 0; i < HM; ++i) hq[QS][i] = ld(xc + goff[i] + zo);
+                q[(U + NO + PR + RING) % RING] = ld(xc + pxy + (long)wz(z + NO + PR) * plane);
             }
-            // 2. plane z
+            // 2. plane z: y and z neighbours, then x
             const T* rp = (P ? buf1 : buf0) + lrow;
             const int C = U % RING;
-            T lap = cc * q[C];
+            rv lap = cc * q[C];
 #pragma unroll
             for (int k = 1; k <= NO; ++k) {
-                T s = (rp[k] + rp[-k]) + a.ry * (rp[k * W] + rp[-k * W]);
-                s += a.rz * (q[(U + k) % RING] + q[(U + RING - k) % RING]);
-                lap += a.ck[k] * s;
+                const rv yy = *reinterpret_cast<const lv*>(rp + k * W) + *reinterpret_cast<const lv*>(rp - k * W);
+                const rv zz = q[(U + k) % RING] + q[(U + RING - k) % RING];
+                lap += a.cy[k] * yy;
+                lap += a.cz[k] * zz;
             }
-            T hv = lap + ve[QS] * q[C];
-            T o;
-            if (MODE == 0) {
-                o = hv;
-            } else {
-                o = alpha * hv;
-                if (MODE == 2) o += beta * xp[QS];
+            {
+                // x window of the thread's points: whole vectors on both sides
+                constexpr int NV = (NO + VX - 1) / VX;
+                T w[(2 * NV + 1) * VX];
+#pragma unroll
+                for (int v = -NV; v <= NV; ++v) {
+                    rv u;
+                    if (v == 0) u = q[C];
+                    else u = *reinterpret_cast<const lv*>(rp + v * VX);
+#pragma unroll
+                    for (int e = 0; e < VX; ++e) w[(v + NV) * VX + e] = u[e];
+                }
+#pragma unroll
+                for (int k = 1; k <= NO; ++k)
+#pragma unroll
+                    for (int e = 0; e < VX; ++e) lap[e] += a.cx[k] * (w[NV * VX + e + k] + w[NV * VX + e - k]);
             }
-            if (active) __builtin_nontemporal_store(o, &oc[pxy + (long)z * plane]);
+            rv o = lap + ve[QS] * q[C];
+            if (MODE != 0) o *= alpha;
+            if (MODE == 2) o += beta * xp[QS];
+            if (active) {
+                T* op = oc + pxy + (long)z * plane;
+                if (ALN || e0 == 0) {
+                    __builtin_nontemporal_store((gv)o, reinterpret_cast<gv*>(op));
+                } else {
+#pragma unroll
+                    for (int e = 1; e < VX; ++e)
+                        if (e >= e0) __builtin_nontemporal_store(o[e], op + e);
+                }
+            }
             // 3. queue loads of plane z + PQ
             {
                 const long zo = (long)wz(z + PQ) * plane;
-                if (MODE == 2) xp[QS] = __builtin_nontemporal_load(&pc[pxy + zo]);
-                ve[QS] = a.veff[pxy + zo];
+                if (MODE == 2) xp[QS] = __builtin_nontemporal_load(reinterpret_cast<const gv*>(pc + pxy + zo));
+                ve[QS] = ld(a.veff + pxy + zo);
             }
             // 4. LDS plane of z + 1
             T* nbuf = P ? buf0 : buf1;
-            const int CN = (U + 1) % RING;
-            if (active) {
-                nbuf[lrow] = q[CN];
-                if (lx < NO) nbuf[lrow + nx] = q[CN];
-                if (lx >= nx - NO) nbuf[lrow - nx] = q[CN];
-            }
+            put(nbuf, q[(U + 1) % RING]);
 #pragma unroll
             for (int i = 0; i < HM; ++i)
-                if (i < hn) {
-                    nbuf[loff[i]] = hq[QN][i];
-                    if (poff[i] >= 0) nbuf[poff[i]] = hq[QN][i];
-                }
+                if (i < hn) *reinterpret_cast<lv*>(nbuf + loff[i]) = hq[QN][i];
         }
     }
 }
 
-int choose_sweep_ty(int nx, int ny, int max_threads) {
-    // tuning override: rows per y-slab
-    if (const char* e = std::getenv("SPARC_GPU_SWEEP_TY")) {
-        int v = std::atoi(e);
-        if (v >= 1 && v <= ny && ((v * nx + 63) / 64) * 64 <= max_threads) return v;
-    }
-    int maxty = std::max(1, std::min(16, max_threads / nx));
-    maxty = std::min(maxty, ny);
-    // the largest divisor of ny not above maxty, unless it is small
-    int best = 1;
-    for (int t = maxty; t >= 1; --t)
-        if (ny % t == 0) {
-            best = t;
-            break;
+// Rounds of a sweep: the slots an XCD has for its workgroups (`round`), and the
+// z ranges of the workgroups past its last full round: the number whose rounds
+// of (planes + the 8 planes' worth that filling a ring costs) are shortest.  260
+// orbitals in 6 slabs leave 6 rounds and 3 workgroups per XCD, and a block of 12
+// orbitals never fills one round.  Returns the planes that pass one after
+// another, a resident workgroup hiding its share of the ring fills.
+static long sweep_rounds(long tiles, int round, int resident, int nz, int* split) {
+    const int mine = (int)((tiles + 7) / 8), full = mine / round, rest = mine - full * round;
+    *split = 1;
+    long least = 0;
+    for (int f = 1; f <= std::max(1, nz / 3) && rest; ++f) {
+        const long cost = (long)div_up((long)rest * f, round) * (div_up(nz, f) + 8);
+        if (f == 1 || cost < least) {
+            *split = f;
+            least = cost;
         }
-    if (best * 2 < maxty) best = maxty;
+    }
+    return full * (nz + 8L / resident) + least;
+}
+
+// Slab height of the sweep: the one with the least (planes one after another)
+// x (time of a plane).  The latter goes with the points that the resident
+// workgroups compute and, at a quarter (mostly L2 hits), the halo rows they read;
+// from 6 waves per compute unit on the loads hide each other (72^3 x 260 FP64:
+// 484 us with 7 and with 11 waves).  Slabs of less than 12 rows need two halo
+// vectors per thread, which spills (72^3: 700 us with 7 rows).
+static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol) {
+    const int nx = c->nx, ny = c->ny, lw = div_up(nx, vx), halo = 2 * kMaxHalfOrder;
+    int forced = 0;   // tuning override: rows per y-slab
+    if (const char* e = std::getenv("SPARC_GPU_SWEEP_TY")) forced = std::atoi(e);
+    SweepPlan& plan = c->sweep_plans[tsize == 8];
+    if (plan.ncol == ncol && plan.forced == forced) return plan;
+    SweepPlan best;
+    double least = 0;
+    for (int ty = 4; ty <= ny; ++ty) {
+        SweepPlan s;
+        s.ncol = ncol;
+        s.forced = forced;
+        s.ty = ty;
+        s.threads = div_up((long)lw * ty, 64) * 64;
+        if (s.threads > kSweepThreads) break;
+        const int waves = s.threads / 64;
+        const size_t lds = 2 * (size_t)(ty + halo) * sweep_row(nx) * tsize;
+        if (lds > 160 * 1024) break;
+        const int resident = std::max(1, std::min((int)(160 * 1024 / lds), kSweepWaves / waves));
+        s.round = std::max(1, c->prop.multiProcessorCount / 8) * resident;
+        const double plane = resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (resident * waves)) *
+                             (halo * lw > s.threads ? 1.5 : 1.0);
+        const double cost =
+            plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, resident, c->nz, &s.split);
+        if (best.ty == 0 || ty == forced || (cost < least && best.ty != forced)) {
+            least = cost;
+            best = s;
+        }
+    }
+    plan = best;
     return best;
 }
 
@@ -272,13 +360,6 @@ const float* veff_of<float>(sparc_gpu_ctx c) {
     return c->veff32;
 }
 
-// Slab height of the local sweep: the largest divisor of n_y with at most
-// 1024 threads in FP64 and 512 in FP32 (whose lighter threads prefer more
-// workgroups per CU), measured best on MI355X at 72 and 120 points per row.
-static int local_ty(sparc_gpu_ctx c, size_t tsize) {
-    return choose_sweep_ty(c->nx, c->ny, tsize == 8 ? 1024 : 512);
-}
-
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx, int mode,
                            int step) {
@@ -291,45 +372,59 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     a.nx = c->nx;
     a.ny = c->ny;
     a.nz = c->nz;
-    a.ty = local_ty(c, sizeof(T));
+    // 16 bytes of a row per thread; rows of FP32 that are no multiple of 4 points
+    // take unaligned vectors
+    constexpr int VX = 16 / sizeof(T);
+    const SweepPlan sh = sweep_plan(c, VX, sizeof(T), ncol);
+    if (sh.ty == 0) return set_err(c, SPARC_ERR_ARG, "grid x-extent too large for the sweep kernel");
+    a.ty = sh.ty;
     a.ntiles_y = div_up(c->ny, a.ty);
     a.grp = std::max(1, std::min(c->sweep_group, ncol));
     {
         const StencilCoef<T>& cf = coef<T>(c);
         a.c0 = c->cf64.c0;
-        for (int k = 0; k <= kMaxHalfOrder; ++k) a.ck[k] = cf.cx[k];
-        a.ry = (T)((c->hx * c->hx) / (c->hy * c->hy));
-        a.rz = (T)((c->hx * c->hx) / (c->hz * c->hz));
+        for (int k = 0; k <= kMaxHalfOrder; ++k) {
+            a.cx[k] = cf.cx[k];
+            a.cy[k] = cf.cy[k];
+            a.cz[k] = cf.cz[k];
+        }
     }
     a.veff = veff_of<T>(c);
     a.params = c->scal + S_A;
     a.step = step;
     a.ncol = ncol;
-    const int threads = div_up((long)c->nx * a.ty, 64) * 64;
-    const size_t shmem = 2 * (size_t)(a.ty + 2 * kMaxHalfOrder) * (c->nx + 2 * kMaxHalfOrder) * sizeof(T);
-    if (shmem > 160 * 1024) return set_err(c, SPARC_ERR_ARG, "sweep workgroup needs more than 160 KB of LDS");
-    if (threads > 1024) return set_err(c, SPARC_ERR_ARG, "grid x-extent too large for the sweep kernel");
-    const long nblocks = (long)ncol * a.ntiles_y;
-    if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "too many blocks");
-    const int hm = div_up(2L * kMaxHalfOrder * c->nx, threads);
-    if (hm > 6) return set_err(c, SPARC_ERR_ARG, "grid x-extent too large for the sweep kernel");
-    if (nblocks == 0) return SPARC_OK;
+    const size_t shmem = 2 * (size_t)(a.ty + 2 * kMaxHalfOrder) * sweep_row(c->nx) * sizeof(T);
+    const int hm = div_up(2L * kMaxHalfOrder * div_up(c->nx, VX), sh.threads);   // 1 to 3: ty >= 4
+    const long tiles = (long)ncol * a.ntiles_y;
+    if (tiles > 0x3fffffffL) return set_err(c, SPARC_ERR_ARG, "too many blocks");
+    if (tiles == 0) return SPARC_OK;
+    a.round = sh.round;
+    a.split = sh.split;
+    // per XCD: whole tiles, then the split ones (of the larger or smaller of
+    // the two shares that XCDs get)
+    long slots = 0;
+    for (long n : {tiles / 8, (tiles + 7) / 8}) {
+        const long whole = n / a.round * a.round;
+        slots = std::max(slots, whole + (n - whole) * a.split);
+    }
     const int slot = prof_begin(c, mode == 2 ? PK_SWEEP : (mode == 1 ? PK_SWEEP1 : PK_APPLY), stream);
-    const dim3 g((unsigned)nblocks), b(threads);
-#define SG_SWEEP_HM(MV)                                                       \
-    do {                                                                      \
-        switch (hm) {                                                         \
-            case 1: k_hsweep<T, MV, 1><<<g, b, shmem, stream>>>(a); break;    \
-            case 2: k_hsweep<T, MV, 2><<<g, b, shmem, stream>>>(a); break;    \
-            case 3: k_hsweep<T, MV, 3><<<g, b, shmem, stream>>>(a); break;    \
-            case 4: k_hsweep<T, MV, 4><<<g, b, shmem, stream>>>(a); break;    \
-            case 5: k_hsweep<T, MV, 5><<<g, b, shmem, stream>>>(a); break;    \
-            default: k_hsweep<T, MV, 6><<<g, b, shmem, stream>>>(a); break;   \
-        }                                                                     \
+    const dim3 g((unsigned)(8 * slots)), b(sh.threads);
+    const bool aln = c->nx % VX == 0;
+#define SG_SWEEP_HM(MV, AL)                                                            \
+    do {                                                                               \
+        if (hm == 1) k_hsweep<T, VX, AL, MV, 1><<<g, b, shmem, stream>>>(a);           \
+        else if (hm == 2) k_hsweep<T, VX, AL, MV, 2><<<g, b, shmem, stream>>>(a);      \
+        else k_hsweep<T, VX, AL, MV, 3><<<g, b, shmem, stream>>>(a);                   \
     } while (0)
-    if (mode == 0) SG_SWEEP_HM(0);
-    else if (mode == 1) SG_SWEEP_HM(1);
-    else SG_SWEEP_HM(2);
+#define SG_SWEEP(MV)                      \
+    do {                                  \
+        if (aln) SG_SWEEP_HM(MV, true);   \
+        else SG_SWEEP_HM(MV, false);      \
+    } while (0)
+    if (mode == 0) SG_SWEEP(0);
+    else if (mode == 1) SG_SWEEP(1);
+    else SG_SWEEP(2);
+#undef SG_SWEEP
 #undef SG_SWEEP_HM
     SG_CHECK_LAUNCH(c);
     prof_end(c, slot, stream);

@@ -465,9 +465,7 @@ sparc_status build_tables(sparc_gpu_ctx c) {
         std::vector<int> sup_idx, sup_atom, img_off(1, 0), img_ijk;
         std::vector<NlCand> cands;   // (atom, image) pairs
         std::vector<NlSeg> segs;
-        std::vector<long> ip_off(c->n_atoms + 1, 0);
-        std::vector<int> ip_idx, box_lo(3 * (size_t)c->n_atoms);
-        std::vector<uint32_t> ip_box;
+        int box_ext = 0;   // largest support box edge (points)
         bool image_overflow = false;
         const double rcut = c->rcut_nl, r2max = rcut * rcut;
         const double h[3] = {c->hx, c->hy, c->hz};
@@ -507,7 +505,7 @@ sparc_status build_tables(sparc_gpu_ctx c) {
                             while (q < (int)cands.size() &&
                                    (cands[q].bx != bx || cands[q].by != by || cands[q].bz != bz))
                                 ++q;
-                            if (q == (int)cands.size()) cands.push_back({P[0], P[1], P[2], bx, by, bz, a, a});
+                            if (q == (int)cands.size()) cands.push_back({P[0], P[1], P[2], bx, by, bz, a, q});
                             segs.push_back({q, wi, wj, wk, 0});
                             seg_k = k;
                             seg_j = j;
@@ -519,16 +517,7 @@ sparc_status build_tables(sparc_gpu_ctx c) {
             }
             std::stable_sort(pts.begin(), pts.end(),
                              [](const auto& A, const auto& B) { return A.first < B.first; });
-            for (int d = 0; d < 3; ++d) {
-                box_lo[3 * a + d] = lo[d];
-                T.box_ext = std::max(T.box_ext, hi[d] - lo[d] + 1);
-            }
-            for (auto& q : pts) {
-                ip_idx.push_back((int)q.first);
-                ip_box.push_back((uint32_t)(q.second[0] - lo[0]) | ((uint32_t)(q.second[1] - lo[1]) << 8) |
-                                 ((uint32_t)(q.second[2] - lo[2]) << 16));
-            }
-            ip_off[a + 1] = (long)ip_idx.size();
+            for (int d = 0; d < 3; ++d) box_ext = std::max(box_ext, hi[d] - lo[d] + 1);
             long prev = -1;
             for (auto& q : pts) {
                 if (q.first != prev) {
@@ -559,27 +548,6 @@ sparc_status build_tables(sparc_gpu_ctx c) {
             }
             if ((st = build_nl_pass(c, cands, segs)) != SPARC_OK) return st;
         }
-        // Morton order of the atoms (10 bits per axis of the fractional position)
-        {
-            std::vector<std::pair<uint64_t, int>> key(c->n_atoms);
-            const double Ls[3] = {c->Lx, c->Ly, c->Lz};
-            for (int a = 0; a < c->n_atoms; ++a) {
-                uint64_t k = 0;
-                uint32_t q[3];
-                for (int d = 0; d < 3; ++d) {
-                    double f = c->pos[3 * a + d] / Ls[d];
-                    f = f - std::floor(f);
-                    q[d] = (uint32_t)std::min(1023.0, std::floor(f * 1024.0));
-                }
-                for (int bit = 9; bit >= 0; --bit)
-                    for (int d = 2; d >= 0; --d) k = (k << 1) | ((q[d] >> bit) & 1u);
-                key[a] = {k, a};
-            }
-            std::sort(key.begin(), key.end());
-            std::vector<int> order(c->n_atoms);
-            for (int a = 0; a < c->n_atoms; ++a) order[a] = key[a].second;
-            if ((st = upload(c, &T.atom_order, order)) != SPARC_OK) return st;
-        }
         std::vector<double> g4(4 * c->n_atoms);
         for (int a = 0; a < c->n_atoms; ++a) {
             g4[4 * a] = c->gamma[2 * a];
@@ -587,11 +555,7 @@ sparc_status build_tables(sparc_gpu_ctx c) {
         }
         int *d_img_off = nullptr, *d_img_ijk = nullptr, *d_sup_atom = nullptr;
         double* d_pos = nullptr;
-        if (T.box_ext > 255) return set_err(c, SPARC_ERR_ARG, "projector support box wider than 255 points");
-        if ((st = upload(c, &T.ip_off, ip_off)) != SPARC_OK) return st;
-        if ((st = upload(c, &T.ip_idx, ip_idx)) != SPARC_OK) return st;
-        if ((st = upload(c, &T.ip_box, ip_box)) != SPARC_OK) return st;
-        if ((st = upload(c, &T.box_lo, box_lo)) != SPARC_OK) return st;
+        if (box_ext > 255) return set_err(c, SPARC_ERR_ARG, "projector support box wider than 255 points");
         if ((st = upload(c, &T.sup_off, sup_off)) != SPARC_OK) return st;
         if ((st = upload(c, &T.gamma4, g4)) != SPARC_OK) return st;
         if ((st = upload(c, &d_img_off, img_off)) != SPARC_OK) return st;
@@ -764,12 +728,10 @@ sparc_status sparc_gpu_create(const sparc_gpu_system* s, void* hip_stream, sparc
 sparc_status sparc_gpu_destroy(sparc_gpu_ctx c) {
     if (!c) return SPARC_ERR_ARG;
     hipStreamSynchronize(c->stream);
-    void* ptrs[] = {c->veff, c->veff32, c->veff_spin, c->force_tab, c->kp_off, c->kp_ent, c->kp_slot, c->kp_etab,
-                    c->kp_tile_off, c->kp_tile_atoms, c->kp_proj, c->chol_dorig,
+    void* ptrs[] = {c->veff, c->veff32, c->veff_spin, c->force_tab, c->kp_phase, c->kp_D, c->chol_dorig,
                     c->kp_bounds, c->kp_wts, c->b, c->pois_ux, c->pois_uy, c->pois_uz, c->pois_inv, c->work, c->D,
                     c->D32, c->gemm_part, c->small, c->red, c->scal, c->flags, c->field, c->nl.sup_off,
-                    c->nl.sup_chi, c->nl.gamma4, c->nl.atom_order, c->atom_pos, c->nl_part,
-                    c->nl.ip_off, c->nl.ip_idx, c->nl.ip_box, c->nl.box_lo};
+                    c->nl.sup_chi, c->nl.gamma4, c->atom_pos, c->nl_part};
     for (void* p : ptrs)
         if (p) hipFree(p);
     free_nl_pass(c->nlp);

@@ -26,11 +26,11 @@ struct StencilCoef {
 
 // An (atom, periodic image) pair of the projector supports: grid point
 // (x, y, z) of the home cell lies at ((x + bx) hx - px, ...) from the image's
-// centre; dcol: the pair's column of D in units of 4 values.
+// centre; id: its place in the pair table, where an atom's pairs are consecutive.
 struct NlCand {
     double px, py, pz;
     int bx, by, bz;
-    int atom, dcol;
+    int atom, id;
 };
 
 // One line of a pair's support: n points from (x0, y, z) along x.
@@ -56,6 +56,8 @@ struct NlPass {
     NlCand* cand = nullptr;
     int* red_off = nullptr;      // entries of each atom
     int* red_ent = nullptr;
+    int* cand_off = nullptr;     // pairs of each atom
+    int n_cand = 0;
     int slots = 8, zlen = 1, ncl = 1;
     long n_entries = 0;
     std::vector<int> layer_off;  // unit ranges of the layers
@@ -69,8 +71,6 @@ struct SweepPlan {
 };
 
 // Nonlocal projector tables on the device.
-//  - Bloch projection: the image points of each atom's ball (ip_*), with the
-//    projector values evaluated from per-axis Gaussian tables;
 //  - spectral bound: projector values per unique support point (sup_*).
 struct NonlocalTables {
     int n_atoms = 0;
@@ -78,18 +78,8 @@ struct NonlocalTables {
     long* sup_off = nullptr;   // n_atoms + 1: each atom's unique support points
     double* sup_chi = nullptr; // 4 n_sup projector values (summed over images; for the spectral bound)
     double* gamma4 = nullptr;  // 4 n_atoms: (g_s, g_p, g_p, g_p)
-    int* atom_order = nullptr; // atoms in space-filling (Morton) order
     double nl_hi = 0.0, nl_lo = 0.0;  // signed spectral bound contributions
     int max_per_atom = 0;
-    // image points of each atom's ball for the projection, in grid order:
-    // flat index and the packed position in the atom's bounding box
-    // (bits 0-7 x, 8-15 y, 16-23 z, relative to box_lo); the projector
-    // values are products of per-axis Gaussian tables
-    long* ip_off = nullptr;     // n_atoms + 1
-    int* ip_idx = nullptr;
-    uint32_t* ip_box = nullptr;
-    int* box_lo = nullptr;      // 3 n_atoms (unwrapped grid index of the box corner)
-    int box_ext = 0;            // largest box edge (points)
 };
 
 }  // namespace sg
@@ -124,18 +114,11 @@ struct sparc_gpu_ctx_s {
     double* force_tab = nullptr;  // per-atom force table: pos (3n), Z (n), rc (n), gamma (4n); on use
     // Bloch k-points (allocated on use)
     double kvec[3] = {0, 0, 0};   // current k (1/Bohr)
-    int* kp_off = nullptr;        // N_d + 1: point-major projector entries
-    uint32_t* kp_ent = nullptr;   // (atom, image) entries
-    uint16_t* kp_slot = nullptr;  // per entry: the atom's slot in its point's tile list
-    int* kp_tile_off = nullptr;   // per 256-point tile: offsets into kp_tile_atoms
-    int* kp_tile_atoms = nullptr; // distinct atoms with entries in each tile
-    int kp_tile_max = 0;          // largest tile atom list
-    long kp_n_ent = 0;            // number of entries
-    double* kp_etab = nullptr;    // per entry: chi_s, chi_px, chi_py, chi_pz, cos, sin at kp_etab_k
-    double kp_etab_k[3] = {0, 0, 0};
-    int kp_etab_valid = 0;
-    double* kp_proj = nullptr;    // n_atoms x ncol x 8 complex projections
-    size_t kp_proj_elems = 0;
+    double* kp_phase = nullptr;   // per (atom, image) pair: cos, sin of k . sL at kp_phase_k
+    double kp_phase_k[3] = {0, 0, 0};
+    int kp_phase_valid = 0;
+    double* kp_D = nullptr;       // per half column and (atom, image) pair: 4 coefficients
+    size_t kp_D_elems = 0;
     double* kp_bounds = nullptr;  // 3 per k-point: filter bounds of the k-point SCF
     int kp_bounds_n = 0;
     double* kp_wts = nullptr;     // per-state k weights of the k-point SCF
@@ -145,7 +128,7 @@ struct sparc_gpu_ctx_s {
     double e_self = 0, e_c = 0;
     sg::NonlocalTables nl;
     sg::NlPass nlp;
-    sg::SweepPlan sweep_plans[2];   // FP32, FP64: of the last block width
+    sg::SweepPlan sweep_plans[4];   // FP32, FP64, their Bloch forms: of the last block width
 
     // Poisson: real orthonormal Fourier bases per axis and the operator's
     // eigenvalues on the product basis
@@ -251,9 +234,11 @@ enum Flag {
 // ---- kernels (launchers) -------------------------------------------------
 // Local part of H / Chebyshev sweeps. mode: 0 out = H_loc x; 1 first filter
 // step; 2 filter step `step` (>= 2) with xprev = X_{k-1} (may alias out).
+// halves: column j is half j % 2 (N_d rows) of Bloch column j / 2, at the
+// context's k.
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx,
-                           int mode, int step);
+                           int mode, int step, bool halves = false);
 // The nonlocal term of a block in one pass: apply (y += alpha chi D, alpha
 // that of the recurrence for (mode, step), 1 for mode 0) and / or project (D =
 // gamma dV chi^T y of the completed y).  The partial sums go to `part`
@@ -262,6 +247,10 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
 template <typename T>
 sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool apply, bool project, int mode, int step,
                      double* part = nullptr, size_t part_elems = 0);
+// The same for ncol Bloch columns [u; v] at the context's k, in FP64 arithmetic
+// for both block precisions.
+template <typename T>
+sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool apply, bool project, int mode, int step);
 // Y = H X
 template <typename T>
 sparc_status apply_impl(sparc_gpu_ctx c, const T* X, T* Y, int ncol, long ldx);
@@ -340,7 +329,6 @@ sparc_status set_veff_impl(sparc_gpu_ctx c, const double* d_veff);
 sparc_status bounds_impl(sparc_gpu_ctx c);  // writes S_LO / S_HI on device
 sparc_status ensure_force_tables(sparc_gpu_ctx c);
 // Bloch k-points at c->kvec; blocks hold columns [Re z; Im z] of 2 N_d rows
-sparc_status ensure_kp_tables(sparc_gpu_ctx c);
 sparc_status kp_nl_bounds(sparc_gpu_ctx c, const double* k, double* nl_lo, double* nl_hi);
 sparc_status bloch_bounds_impl(sparc_gpu_ctx c);
 template <typename T>

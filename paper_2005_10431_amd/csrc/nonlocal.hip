@@ -49,11 +49,14 @@ constexpr int kMaxPlanes = 128;     // planes of a unit
 constexpr int kMaxSlots = 24;
 constexpr int kNlWaves = 4;         // waves of a workgroup, 16 orbitals each
 
-typedef double nl_d2 __attribute__((ext_vector_type(2), aligned(8)));
-typedef float nl_f4 __attribute__((ext_vector_type(4), aligned(4)));
+template <typename T, int N>
+struct NlVec {
+    typedef T type __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+};
 
-// The four points (of a block's 16) that lane group g holds, and the point of MFMA row i.
-template <typename T>
+// The four points (of a block's 16) that lane group g holds when the products
+// run in C, and the point of MFMA row i.  T: type in memory.
+template <typename C>
 struct Pts;
 template <>
 struct Pts<double> {
@@ -61,17 +64,21 @@ struct Pts<double> {
     static __device__ inline int row(int i) { return 2 * (i & 3) + ((i >> 2) & 1) + 8 * (i >> 3); }
     // position of MFMA row i (slot i % 4, lm i / 4) among a group's 16 (slot, lm) values
     static __device__ inline int perm(int i) { return 4 * (i & 3) + (i >> 2); }
-    static __device__ inline void load(const double* x, int p0, int g, double* q) {
-        const nl_d2 a = *reinterpret_cast<const nl_d2*>(x + p0 + 2 * g);
-        const nl_d2 b = *reinterpret_cast<const nl_d2*>(x + p0 + 2 * g + 8);
+    template <typename T>
+    static __device__ inline void load(const T* x, int p0, int g, T* q) {
+        using v2 = typename NlVec<T, 2>::type;
+        const v2 a = *reinterpret_cast<const v2*>(x + p0 + 2 * g);
+        const v2 b = *reinterpret_cast<const v2*>(x + p0 + 2 * g + 8);
         q[0] = a.x;
         q[1] = a.y;
         q[2] = b.x;
         q[3] = b.y;
     }
-    static __device__ inline void store(double* x, int p0, int g, const double* q) {
-        *reinterpret_cast<nl_d2*>(x + p0 + 2 * g) = nl_d2{q[0], q[1]};
-        *reinterpret_cast<nl_d2*>(x + p0 + 2 * g + 8) = nl_d2{q[2], q[3]};
+    template <typename T>
+    static __device__ inline void store(T* x, int p0, int g, const T* q) {
+        using v2 = typename NlVec<T, 2>::type;
+        *reinterpret_cast<v2*>(x + p0 + 2 * g) = v2{q[0], q[1]};
+        *reinterpret_cast<v2*>(x + p0 + 2 * g + 8) = v2{q[2], q[3]};
     }
 };
 template <>
@@ -80,21 +87,26 @@ struct Pts<float> {
     static __device__ inline int row(int i) { return i; }
     static __device__ inline int perm(int i) { return i; }
     static __device__ inline void load(const float* x, int p0, int g, float* q) {
-        const nl_f4 a = *reinterpret_cast<const nl_f4*>(x + p0 + 4 * g);
+        using v4 = typename NlVec<float, 4>::type;
+        const v4 a = *reinterpret_cast<const v4*>(x + p0 + 4 * g);
         q[0] = a.x;
         q[1] = a.y;
         q[2] = a.z;
         q[3] = a.w;
     }
     static __device__ inline void store(float* x, int p0, int g, const float* q) {
-        *reinterpret_cast<nl_f4*>(x + p0 + 4 * g) = nl_f4{q[0], q[1], q[2], q[3]};
+        using v4 = typename NlVec<float, 4>::type;
+        *reinterpret_cast<v4*>(x + p0 + 4 * g) = v4{q[0], q[1], q[2], q[3]};
     }
 };
 
-template <typename T>
+template <typename T, typename C>
 struct NlArgs {
     T* y;
     long ldx;
+    int halves;                  // 0: column j at j ldx; 1: at (j / 2) ldx + (j % 2) half (Bloch columns)
+    long half;
+    int by_pair;                 // D per (atom, image) pair (Bloch) or per atom
     int nx, ny, nz, nxy, ncol;
     int nwc, nchunk, nunit;      // MFMA waves per workgroup, column chunks, units
     int zlen, ncl;               // most planes and pairs of a unit
@@ -107,7 +119,7 @@ struct NlArgs {
     const int* ent_cand;         // pair of every entry
     const NlCand* cand;
     double hx, hy, hz, inv_rc2, N0, N1, rcut2;
-    const T* D;                  // column j at D + j ldD, 4 per (pair's) atom
+    const C* D;                  // column j at D + j ldD, 4 per pair or atom
     long ldD;
     double* part;                // [(entry ncol + col) 4 + lm]
     const double* params;
@@ -200,16 +212,16 @@ __device__ inline float gauss(float v) { return expf(v); }
 // table overlaps the other's products.  A wave has the loads of a whole plane
 // (12 KB in FP64) in flight: with half of that and six waves per workgroup
 // the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.
-template <typename T, int S, bool AP, bool PR, bool TAIL>
-__global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
-    using P = Pts<T>;
-    using acc_t = typename Mfma<T>::acc_t;
+template <typename T, typename C, int S, bool AP, bool PR, bool TAIL>
+__global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
+    using P = Pts<C>;
+    using acc_t = typename Mfma<C>::acc_t;
     constexpr int NB = kNlBlocks, NG = S / 4, RS = 4 * S + 4, NP = 16 * NB;
     constexpr int RING = NB;   // blocks in flight per wave: a plane
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const NlLds L = nl_lds_layout(sizeof(T), S, a.zlen, a.ncl);
-    T* chi = reinterpret_cast<T*>(smem_raw);
-    T* gxy = reinterpret_cast<T*>(smem_raw + L.gxy);
+    const NlLds L = nl_lds_layout(sizeof(C), S, a.zlen, a.ncl);
+    C* chi = reinterpret_cast<C*>(smem_raw);
+    C* gxy = reinterpret_cast<C*>(smem_raw + L.gxy);
     double* ezdz = reinterpret_cast<double*>(smem_raw + L.ez);
     uint64_t* gml = reinterpret_cast<uint64_t*>(smem_raw + L.gm);
     NlCand* cand = reinterpret_cast<NlCand*>(smem_raw + L.cand);
@@ -270,22 +282,22 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
                 dx = off_x(cand[o], w & 0xFFFF, a.hx);
                 dy = off_y(cand[o], w >> 16, a.hy);
                 r2 = sum_sq(dx, dy);
-                if (zl == 0 || occ[(zl - 1) * S + s] != o) gxy[e] = (T)exp(-r2 * a.inv_rc2);
+                if (zl == 0 || occ[(zl - 1) * S + s] != o) gxy[e] = (C)exp(-r2 * a.inv_rc2);
             }
             if (!((gm >> ((q >> 4) * NG + (s >> 2))) & 1)) continue;
-            T v0 = 0, v1 = 0, v2 = 0, v3 = 0;
+            C v0 = 0, v1 = 0, v2 = 0, v3 = 0;
             if (live) {
                 const double* z = ezdz + ((zl & 1) * S + s) * 2;
                 if (add_sq(r2, z[1]) <= a.rcut2) {
-                    const T ex = gxy[e] * (T)z[0];
-                    const T e1 = (T)a.N1 * ex;
-                    v0 = (T)a.N0 * ex;
-                    v1 = e1 * (T)dx;
-                    v2 = e1 * (T)dy;
-                    v3 = e1 * (T)z[1];
+                    const C ex = gxy[e] * (C)z[0];
+                    const C e1 = (C)a.N1 * ex;
+                    v0 = (C)a.N0 * ex;
+                    v1 = e1 * (C)dx;
+                    v2 = e1 * (C)dy;
+                    v3 = e1 * (C)z[1];
                 }
             }
-            T* r = chi + q * RS + 4 * s;
+            C* r = chi + q * RS + 4 * s;
             r[0] = v0;
             r[1] = v1;
             r[2] = v2;
@@ -298,14 +310,14 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
     // repeat it (the same loads, results and stores)
     const bool mine = wv < a.nwc && 16 * (chunk * a.nwc + wv) < a.ncol;
     const int cl = 16 * (chunk * a.nwc + wv) + li, col = min(cl, a.ncol - 1);
-    T* yc = a.y + (long)col * a.ldx;
+    T* yc = a.y + (long)(col >> a.halves) * a.ldx + (long)(col & a.halves) * a.half;
 
     double alpha = 1.0, csh, beta;
     if (AP) filter_coefs(a.params, a.mode, a.step, alpha, csh, beta);
-    const T al = (T)alpha;
+    const C al = (C)alpha;
 
-    GroupSum<T> sum[NG];
-    T d[NG][4];
+    GroupSum<C> sum[NG];
+    C d[NG][4];
     int oc[NG];
 #pragma unroll
     for (int G = 0; G < NG; ++G) {
@@ -329,9 +341,10 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
                 sum[G].zero();
             }
             if (AP) {
-                const T* Dc = a.D + (long)col * a.ldD + 4 * (on == kIdle ? 0 : cand[on].dcol);
+                const C* Dc = a.D + (long)col * a.ldD;
+                if (on != kIdle) Dc += 4 * (a.by_pair ? cand[on].id : cand[on].atom);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) d[G][j] = on == kIdle ? (T)0 : al * Dc[j];
+                for (int j = 0; j < 4; ++j) d[G][j] = on == kIdle ? (C)0 : al * Dc[j];
             }
             oc[G] = on;
         }
@@ -366,21 +379,21 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
         for (int b = 0; b < NB; ++b) {
             const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
             T* v = q[b % RING];
-            acc_t acc = {v[0], v[1], v[2], v[3]};
+            acc_t acc = {(C)v[0], (C)v[1], (C)v[2], (C)v[3]};
             // the next block of this ring place; loads and stores take no
             // branch, so that those in flight can be counted
             load(v, (b + RING) % NB, b + RING < NB ? z : min(z + 1, U.ze - 1));
-            const T* cb = chi + 16 * b * RS;
+            const C* cb = chi + 16 * b * RS;
             if (AP) {
-                const T* A = cb + P::row(li) * RS + 4 * g;
+                const C* A = cb + P::row(li) * RS + 4 * g;
 #pragma unroll
                 for (int G = 0; G < NG; ++G)
                     if ((gb >> G) & 1) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc = Mfma<T>::run(A[16 * G + j], d[G][j], acc);
+                        for (int j = 0; j < 4; ++j) acc = Mfma<C>::run(A[16 * G + j], d[G][j], acc);
                     }
                 T* yp = yc + (long)z * a.nxy + pb0[b];
-                const T o[4] = {acc[0], acc[1], acc[2], acc[3]};
+                const T o[4] = {(T)acc[0], (T)acc[1], (T)acc[2], (T)acc[3]};
                 if (TAIL && b == NB - 1 && part5) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -395,7 +408,7 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T> a) {
                     if ((gb >> G) & 1) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            sum[G].p = Mfma<T>::run(cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r], sum[G].p);
+                            sum[G].p = Mfma<C>::run(cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r], sum[G].p);
                     }
             }
         }
@@ -431,6 +444,60 @@ __global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ pa
     D[(long)col * ldD + 4 * a + lm] = (T)(g4[4 * a + lm] * dV * s);
 }
 
+// cos, sin of k . sL of every (atom, image) pair
+__global__ void k_nl_phase(const NlCand* __restrict__ cand, int n, int nx, int ny, int nz, double kx, double ky,
+                           double kz, double* __restrict__ phase) {
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= n) return;
+    sincos(kx * (cand[q].bx / nx) + ky * (cand[q].by / ny) + kz * (cand[q].bz / nz), &phase[2 * q + 1],
+           &phase[2 * q]);
+}
+
+// Bloch form, per atom and complex column c: with the real projections p_s of
+// the two halves on the atom's images s,
+//   D_a = gamma dV sum_s exp(i k.sL) (p_s[u] + i p_s[v])   (entries in order),
+// and the coefficients exp(-i k.sL) D_a of every image, real part at the
+// column of u, imaginary part at that of v.
+__global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ part, int ncol,
+                                                     const int* __restrict__ off, const int* __restrict__ ent,
+                                                     const int* __restrict__ ent_cand,
+                                                     const int* __restrict__ cand_off,
+                                                     const double* __restrict__ phase, const double* __restrict__ g4,
+                                                     double dV, double* __restrict__ D, long ldD) {
+    const int a = blockIdx.x;
+    const long q = (long)blockIdx.y * blockDim.x + threadIdx.x;
+    if (q >= 4L * ncol) return;
+    const int c = (int)(q / 4), lm = (int)(q % 4);
+    double zr = 0.0, zi = 0.0;
+    const int e1 = off[a + 1];
+    for (int e = off[a]; e < e1; e += 4) {
+        double u[4], v[4], cs[4], sn[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int en = ent[min(e + k, e1 - 1)];
+            const double* p = part + ((long)en * 2 * ncol + 2 * c) * 4 + lm;
+            u[k] = p[0];
+            v[k] = p[4];
+            cs[k] = phase[2 * ent_cand[en]];
+            sn[k] = phase[2 * ent_cand[en] + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (e + k < e1) {
+                zr += cs[k] * u[k] - sn[k] * v[k];
+                zi += sn[k] * u[k] + cs[k] * v[k];
+            }
+    }
+    const double g = dV * g4[4 * a + lm];
+    zr *= g;
+    zi *= g;
+    for (int s = cand_off[a]; s < cand_off[a + 1]; ++s) {
+        const double cs = phase[2 * s], sn = phase[2 * s + 1];
+        D[(2L * c) * ldD + 4 * s + lm] = zr * cs + zi * sn;
+        D[(2L * c + 1) * ldD + 4 * s + lm] = zi * cs - zr * sn;
+    }
+}
+
 template <typename V>
 sparc_status put(sparc_gpu_ctx c, V** dst, const std::vector<V>& src) {
     SG_HIP(c, hipMalloc((void**)dst, std::max<size_t>(1, src.size()) * sizeof(V)));
@@ -453,7 +520,7 @@ float* D_of<float>(sparc_gpu_ctx c) {
 
 void free_nl_pass(NlPass& T) {
     for (void* p : {(void*)T.units, (void*)T.blk, (void*)T.occ, (void*)T.gm, (void*)T.ent_cand, (void*)T.cand,
-                    (void*)T.red_off, (void*)T.red_ent, T.dummy})
+                    (void*)T.red_off, (void*)T.red_ent, (void*)T.cand_off, T.dummy})
         if (p) hipFree(p);
     T = NlPass{};
 }
@@ -654,7 +721,10 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
         }
         T.layer_off.push_back((int)units.size());
     }
-    std::vector<int> roff(c->n_atoms + 1, 0), rent;
+    std::vector<int> roff(c->n_atoms + 1, 0), rent, coff(c->n_atoms + 1, 0);
+    for (const NlCand& q : cands) coff[q.atom + 1]++;
+    for (int a = 0; a < c->n_atoms; ++a) coff[a + 1] += coff[a];
+    T.n_cand = (int)cands.size();
     for (int a = 0; a < c->n_atoms; ++a) {
         rent.insert(rent.end(), per_atom[a].begin(), per_atom[a].end());
         roff[a + 1] = (int)rent.size();
@@ -672,6 +742,7 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
     if ((st = put(c, &T.cand, cands)) != SPARC_OK) return st;
     if ((st = put(c, &T.red_off, roff)) != SPARC_OK) return st;
     if ((st = put(c, &T.red_ent, rent)) != SPARC_OK) return st;
+    if ((st = put(c, &T.cand_off, coff)) != SPARC_OK) return st;
     if (c->debug)
         fprintf(stderr,
                 "[sparc_gpu] nonlocal pass: %d pencils (%d x-ranges, %d rows), %zu units of %d planes, %d slots (%d "
@@ -680,58 +751,50 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
     return SPARC_OK;
 }
 
-template <typename T, int S>
-static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T>& a, bool ap, bool pr, size_t shmem) {
+template <typename T, typename C, int S>
+static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, bool ap, bool pr, size_t shmem) {
     const long nblocks = (long)a.nunit * a.nchunk;
     if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "nonlocal pass: too many blocks");
     const dim3 g((unsigned)nblocks), b(64 * std::max(4, a.nwc));
-    if (!ap) k_nl_pass<T, S, false, true, false><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail && pr) k_nl_pass<T, S, true, true, true><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail) k_nl_pass<T, S, true, false, true><<<g, b, shmem, c->stream>>>(a);
-    else if (pr) k_nl_pass<T, S, true, true, false><<<g, b, shmem, c->stream>>>(a);
-    else k_nl_pass<T, S, true, false, false><<<g, b, shmem, c->stream>>>(a);
+    if (!ap) k_nl_pass<T, C, S, false, true, false><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail && pr) k_nl_pass<T, C, S, true, true, true><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail) k_nl_pass<T, C, S, true, false, true><<<g, b, shmem, c->stream>>>(a);
+    else if (pr) k_nl_pass<T, C, S, true, true, false><<<g, b, shmem, c->stream>>>(a);
+    else k_nl_pass<T, C, S, true, false, false><<<g, b, shmem, c->stream>>>(a);
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;
 }
 
-// One pass over a block: apply (y += alpha chi D, alpha that of filter step
-// `step` of mode `mode`) and / or project (D = gamma dV chi^T y).
-template <typename T>
-sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step, double* part,
-                     size_t part_elems) {
-    const NlPass& N = c->nlp;
-    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
-    const size_t per_col = (size_t)N.n_entries * 4;
-    int group = ncol;
-    if (pr) {
-        if (part) {
-            // caller memory: as many columns at a time as it holds, whole
-            // 16-column tiles where it can
-            if (per_col > part_elems)
-                return set_err(c, SPARC_ERR_ARG, "projection partials of one column exceed the fixed scratch array");
-            group = (int)std::min<size_t>((size_t)ncol, part_elems / per_col);
-            if (group >= 16 && group < ncol) group -= group % 16;
-        } else {
-            const size_t need = per_col * ncol;
-            if (c->nl_part_elems < need) {
-                if (c->nl_part) {
-                    SG_HIP(c, hipStreamSynchronize(c->stream));
-                    SG_HIP(c, hipFree(c->nl_part));
-                    c->nl_part = nullptr;
-                    c->nl_part_elems = 0;
-                }
-                SG_HIP(c, hipMalloc((void**)&c->nl_part, need * sizeof(double)));
-                c->nl_part_elems = need;
-            }
-            part = c->nl_part;
+// Partial sums of ncol columns: the caller's memory or the context's
+static sparc_status partials(sparc_gpu_ctx c, size_t need, double** part) {
+    if (c->nl_part_elems < need) {
+        if (c->nl_part) {
+            SG_HIP(c, hipStreamSynchronize(c->stream));
+            SG_HIP(c, hipFree(c->nl_part));
+            c->nl_part = nullptr;
+            c->nl_part_elems = 0;
         }
+        SG_HIP(c, hipMalloc((void**)&c->nl_part, need * sizeof(double)));
+        c->nl_part_elems = need;
     }
-    NlArgs<T> a;
+    *part = c->nl_part;
+    return SPARC_OK;
+}
+
+template <typename T, typename C>
+static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
+    const NlPass& N = c->nlp;
+    NlArgs<T, C> a;
+    a.y = nullptr;
     a.ldx = ldx;
+    a.halves = 0;
+    a.half = c->nd;
+    a.by_pair = 0;
     a.nx = c->nx;
     a.ny = c->ny;
     a.nz = c->nz;
     a.nxy = c->nx * c->ny;
+    a.ncol = 0;
     a.zlen = N.zlen;
     a.ncl = N.ncl;
     a.blk = N.blk;
@@ -746,41 +809,77 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
     a.N0 = std::pow(2.0 / (3.14159265358979323846 * c->rc_nl * c->rc_nl), 0.75);
     a.N1 = (2.0 / c->rc_nl) * a.N0;
     a.rcut2 = c->rcut_nl * c->rcut_nl;
-    a.ldD = 4L * c->n_atoms;
-    a.part = part;
+    a.D = nullptr;
+    a.ldD = 0;
+    a.part = nullptr;
     a.params = c->scal + S_A;
     a.mode = mode;
     a.step = step;
-    const size_t shmem = nl_lds_layout(sizeof(T), N.slots, N.zlen, N.ncl).total;
+    return a;
+}
+
+// The pass over the columns set in a; with further layers every apply comes
+// before the first projection.
+template <typename T, typename C>
+static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, bool ap, bool pr) {
+    const NlPass& N = c->nlp;
+    const size_t shmem = nl_lds_layout(sizeof(C), N.slots, N.zlen, N.ncl).total;
     if (shmem > 160 * 1024) return set_err(c, SPARC_ERR_ARG, "nonlocal pass needs more than 160 KB of LDS");
-    const int slot = prof_begin(c, PK_PROJ);
+    const int tiles = div_up(a.ncol, 16);
+    a.nchunk = div_up(tiles, kNlWaves);
+    a.nwc = div_up(tiles, a.nchunk);
     const int nl = (int)N.layer_off.size() - 1;
+    for (int half = 0; half < (nl > 1 ? 2 : 1); ++half) {
+        const bool ap1 = ap && half == 0, pr1 = pr && (nl == 1 || half == 1);
+        if (!ap1 && !pr1) continue;
+        for (int l = 0; l < nl; ++l) {
+            const long u0 = N.layer_off[l];
+            a.nunit = N.layer_off[l + 1] - (int)u0;
+            a.units = N.units + u0;
+            a.occ = N.occ + u0 * N.zlen * N.slots;
+            a.gm = N.gm + u0 * N.zlen;
+            sparc_status st = N.slots == 8    ? launch_pass<T, C, 8>(c, a, ap1, pr1, shmem)
+                              : N.slots == 16 ? launch_pass<T, C, 16>(c, a, ap1, pr1, shmem)
+                                              : launch_pass<T, C, kMaxSlots>(c, a, ap1, pr1, shmem);
+            if (st != SPARC_OK) return st;
+        }
+    }
+    return SPARC_OK;
+}
+
+// One pass over a block: apply (y += alpha chi D, alpha that of filter step
+// `step` of mode `mode`) and / or project (D = gamma dV chi^T y).
+template <typename T>
+sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step, double* part,
+                     size_t part_elems) {
+    const NlPass& N = c->nlp;
+    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
+    sparc_status st;
+    const size_t per_col = (size_t)N.n_entries * 4;
+    int group = ncol;
+    if (pr && part) {
+        // caller memory: as many columns at a time as it holds, whole
+        // 16-column tiles where it can
+        if (per_col > part_elems)
+            return set_err(c, SPARC_ERR_ARG, "projection partials of one column exceed the fixed scratch array");
+        group = (int)std::min<size_t>((size_t)ncol, part_elems / per_col);
+        if (group >= 16 && group < ncol) group -= group % 16;
+    } else if (pr) {
+        if ((st = partials(c, per_col * ncol, &part)) != SPARC_OK) return st;
+    }
+    NlArgs<T, T> a = pass_args<T, T>(c, ldx, mode, step);
+    a.ldD = 4L * c->n_atoms;
+    a.part = part;
+    const int slot = prof_begin(c, PK_PROJ);
     for (int c0 = 0; c0 < ncol; c0 += group) {
         a.ncol = std::min(group, ncol - c0);
         a.y = y + (long)c0 * ldx;
-        a.D = D_of<T>(c) + (long)c0 * a.ldD;
-        const int tiles = div_up(a.ncol, 16);
-        a.nchunk = div_up(tiles, kNlWaves);
-        a.nwc = div_up(tiles, a.nchunk);
-        // with further layers every apply comes before the first projection
-        for (int half = 0; half < (nl > 1 ? 2 : 1); ++half) {
-            const bool ap1 = ap && half == 0, pr1 = pr && (nl == 1 || half == 1);
-            if (!ap1 && !pr1) continue;
-            for (int l = 0; l < nl; ++l) {
-                const long u0 = N.layer_off[l];
-                a.nunit = N.layer_off[l + 1] - (int)u0;
-                a.units = N.units + u0;
-                a.occ = N.occ + u0 * N.zlen * N.slots;
-                a.gm = N.gm + u0 * N.zlen;
-                sparc_status st = N.slots == 8    ? launch_pass<T, 8>(c, a, ap1, pr1, shmem)
-                                  : N.slots == 16 ? launch_pass<T, 16>(c, a, ap1, pr1, shmem)
-                                                  : launch_pass<T, kMaxSlots>(c, a, ap1, pr1, shmem);
-                if (st != SPARC_OK) return st;
-            }
-        }
+        T* D = D_of<T>(c) + (long)c0 * a.ldD;
+        a.D = D;
+        if ((st = run_layers<T, T>(c, a, ap, pr)) != SPARC_OK) return st;
         if (pr) {
             k_nl_reduce<T><<<dim3(c->n_atoms, div_up(4L * a.ncol, 256)), 256, 0, c->stream>>>(
-                part, a.ncol, N.red_off, N.red_ent, c->nl.gamma4, c->dV, D_of<T>(c) + (long)c0 * a.ldD, a.ldD);
+                part, a.ncol, N.red_off, N.red_ent, c->nl.gamma4, c->dV, D, a.ldD);
             SG_CHECK_LAUNCH(c);
         }
     }
@@ -790,5 +889,56 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
 
 template sparc_status nl_pass<double>(sparc_gpu_ctx, double*, int, long, bool, bool, int, int, double*, size_t);
 template sparc_status nl_pass<float>(sparc_gpu_ctx, float*, int, long, bool, bool, int, int, double*, size_t);
+
+// The pass over Bloch columns: the halves u, v are real columns, the images'
+// phases enter in the sum over an atom's entries.
+template <typename T>
+sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step) {
+    const NlPass& N = c->nlp;
+    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
+    sparc_status st;
+    double* part = nullptr;
+    if (pr && (st = partials(c, (size_t)N.n_entries * 4 * 2 * ncol, &part)) != SPARC_OK) return st;
+    const long ldD = 4L * N.n_cand;
+    if (c->kp_D_elems < (size_t)ldD * 2 * ncol) {
+        if (c->kp_D) {
+            SG_HIP(c, hipStreamSynchronize(c->stream));
+            SG_HIP(c, hipFree(c->kp_D));
+            c->kp_D = nullptr;
+            c->kp_D_elems = 0;
+        }
+        SG_HIP(c, hipMalloc((void**)&c->kp_D, (size_t)ldD * 2 * ncol * sizeof(double)));
+        c->kp_D_elems = (size_t)ldD * 2 * ncol;
+    }
+    if (!c->kp_phase) SG_HIP(c, hipMalloc((void**)&c->kp_phase, 2 * (size_t)N.n_cand * sizeof(double)));
+    const int slot = prof_begin(c, PK_BLOCH_PROJ);
+    const double* k = c->kvec;
+    if (!c->kp_phase_valid || c->kp_phase_k[0] != k[0] || c->kp_phase_k[1] != k[1] || c->kp_phase_k[2] != k[2]) {
+        k_nl_phase<<<div_up(N.n_cand, 256), 256, 0, c->stream>>>(N.cand, N.n_cand, c->nx, c->ny, c->nz, k[0] * c->Lx,
+                                                                 k[1] * c->Ly, k[2] * c->Lz, c->kp_phase);
+        SG_CHECK_LAUNCH(c);
+        for (int d = 0; d < 3; ++d) c->kp_phase_k[d] = k[d];
+        c->kp_phase_valid = 1;
+    }
+    NlArgs<T, double> a = pass_args<T, double>(c, ldx, mode, step);
+    a.halves = 1;
+    a.by_pair = 1;
+    a.ldD = ldD;
+    a.part = part;
+    a.ncol = 2 * ncol;
+    a.y = y;
+    a.D = c->kp_D;
+    if ((st = run_layers<T, double>(c, a, ap, pr)) != SPARC_OK) return st;
+    if (pr) {
+        k_nl_reduce_k<<<dim3(c->n_atoms, div_up(4L * ncol, 256)), 256, 0, c->stream>>>(
+            part, ncol, N.red_off, N.red_ent, N.ent_cand, N.cand_off, c->kp_phase, c->nl.gamma4, c->dV, c->kp_D, ldD);
+        SG_CHECK_LAUNCH(c);
+    }
+    prof_end(c, slot);
+    return SPARC_OK;
+}
+
+template sparc_status nl_pass_k<double>(sparc_gpu_ctx, double*, int, long, bool, bool, int, int);
+template sparc_status nl_pass_k<float>(sparc_gpu_ctx, float*, int, long, bool, bool, int, int);
 
 }  // namespace sg

@@ -30,6 +30,7 @@
 #include <map>
 #include <mutex>
 #include <cstdlib>
+#include <utility>
 
 #include "internal.hpp"
 
@@ -41,6 +42,9 @@ struct SweepArgs {
     T* out;           // output block (may alias xprev, never x)
     const T* xprev;   // X_{k-1} or null
     long ldx;
+    int halves;       // 0: column j at j ldx; 1: at (j / 2) ldx + (j % 2) half (Bloch columns)
+    long half;
+    double ph[6];     // Bloch sweeps: cos, sin of k_d L_d per axis
     int nx, ny, nz;
     int ty, ntiles_y;
     int grp;          // orbitals whose copies of a slab are dispatched side by side
@@ -68,11 +72,20 @@ __host__ __device__ inline int sweep_row(int nx) { return (nx + 2 * kSweepPad + 
 // took 275 instead of 254 us at 72^3 x 260).
 constexpr int kSweepThreads = 768;
 constexpr int kSweepWaves = 12;
+// The Bloch sweep keeps the other half's values too: two waves per SIMD.
+constexpr int kSweepThreadsBl = 512;
+constexpr int kSweepWavesBl = 8;
 
 template <typename T, int N, int A>
 struct VecOf {
     typedef T type __attribute__((ext_vector_type(N), aligned(A)));
 };
+
+// f(phase 0, z0), f(phase 1, z0 + 1), ... below ze
+template <typename F, int... U>
+__device__ __forceinline__ void each_phase(F& f, int z0, int ze, std::integer_sequence<int, U...>) {
+    (void)((z0 + U < ze && (f(U, z0 + U), true)) && ...);
+}
 
 // The sweep.  MODE: 0 out = H_loc x; 1 first filter step; 2 filter step `step`
 // (>= 2) with xprev = X_{k-1} (may alias out).  VX: points per thread; ALN: n_x
@@ -91,8 +104,15 @@ struct VecOf {
 //  4. plane z + 1 into the other LDS buffer.
 // Threads without a point of the slab (ragged slab, padding to 64) load valid
 // clamped addresses and compute on them, but never store.
-template <typename T, int VX, bool ALN, int MODE, int HM>
-__global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
+//
+// BL: Bloch columns.  A column is one half of z = u + i v; a value past a face
+// of the cell is the wrapped one times exp(+-i k_d L_d), which mixes in the
+// other half: rot() wherever a wrapped value enters (x copies in LDS, halo rows,
+// ring planes).  The other half's values come by loads of their own, for all
+// lanes alike (where none is needed, from one place that stays in cache), so
+// that the loads in flight can be counted.
+template <typename T, int VX, bool ALN, int MODE, int HM, bool BL>
+__global__ __launch_bounds__(BL ? kSweepThreadsBl : kSweepThreads) void k_hsweep(SweepArgs<T> a) {
     constexpr int NO = kMaxHalfOrder;
     constexpr int RING = kRing, PR = kRingAhead, PQ = kQueue;
     constexpr int PAD = kSweepPad;
@@ -145,14 +165,28 @@ __global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
     T* const buf0 = reinterpret_cast<T*>(smem_raw);
     T* const buf1 = buf0 + R * W;
 
-    const T* __restrict__ xc = a.x + (long)col * a.ldx;
-    T* __restrict__ oc = a.out + (long)col * a.ldx;
-    const T* __restrict__ pc = a.xprev ? a.xprev + (long)col * a.ldx : xc;
+    const long co = (long)(col >> a.halves) * a.ldx + (long)(col & a.halves) * a.half;
+    const T* __restrict__ xc = a.x + co;
+    T* __restrict__ oc = a.out + co;
+    const T* __restrict__ pc = a.xprev ? a.xprev + co : xc;
     const long pxy = x0 + (long)nx * (y0 + (active ? ly : 0));
     const int lrow = ((active ? ly : 0) + NO) * W + PAD + x0;
     auto ld = [](const T* p) -> rv { return *reinterpret_cast<const gv*>(p); };
+    // the other half of a Bloch column, and a value of this half times
+    // exp(i s k L) (s = +1 past the upper face, -1 past the lower one), in double
+    const T* __restrict__ xo = BL ? a.x + (long)(col >> 1) * a.ldx + (long)((col & 1) ^ 1) * a.half : nullptr;
+    const double sgn = (col & 1) ? 1.0 : -1.0;
+    auto rot = [&](rv own, rv oth, int axis, int s) -> rv {
+        const double cs = a.ph[2 * axis], sn = (s > 0 ? sgn : -sgn) * a.ph[2 * axis + 1];
+        rv r;
+#pragma unroll
+        for (int e = 0; e < VX; ++e) r[e] = (T)((double)own[e] * cs + (double)oth[e] * sn);
+        return r;
+    };
+    const bool wedge = wleft || wright;
     // halo rows: 2 NO rows of LW vectors per plane, spread over the threads
     int goff[HM], loff[HM];
+    int hwrap[HM];   // face that the halo row lies past: -1, 0, +1
     int hn = 0;
     const int nhalo = 2 * NO * LW;
 #pragma unroll
@@ -160,12 +194,14 @@ __global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
         const int e = t + i * nt;
         goff[i] = 0;
         loff[i] = 0;
+        hwrap[i] = 0;
         if (e < nhalo) {
             hn = i + 1;
             const int hr = e / LW, hl = e - hr * LW;
             const int hx = ALN ? hl * VX : min(hl * VX, nx - VX);
             const int lr = hr < NO ? hr : tyn + hr;
             int gy = y0 - NO + lr;
+            hwrap[i] = gy < 0 ? -1 : (gy >= ny ? 1 : 0);
             gy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
             goff[i] = hx + nx * gy;
             loff[i] = lr * W + PAD + hx;
@@ -182,6 +218,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
     rv q[RING];
     rv hq[PQ][HM];
     rv xp[PQ], ve[PQ];
+    // Bloch: other half of the ring plane loaded last, of the x edges and of the halo rows
+    rv oz, ox[PQ], oh[PQ][HM];
     // ring: planes zb - 6 .. zb + 5 + PR (slot = plane - zb mod RING); queues: planes zb .. zb + PQ - 1
 #pragma unroll
     for (int j = -NO; j <= NO - 1 + PR; ++j) q[(j + 2 * RING) % RING] = ld(xc + pxy + (long)wz(zb + j) * plane);
@@ -195,86 +233,57 @@ __global__ __launch_bounds__(kSweepThreads) void k_hsweep(SweepArgs<T> a) {
     for (int j = 1; j < PQ; ++j)
 #pragma unroll
         for (int i = 0; i < HM; ++i) hq[j][i] = ld(xc + goff[i] + (long)wz(zb + j) * plane);
+    auto edge_at = [&](int z) { return wedge ? xo + pxy + (long)wz(z) * plane : xo; };
+    auto halo_at = [&](int i, int z) { return hwrap[i] ? xo + goff[i] + (long)wz(z) * plane : xo; };
+    if (BL) {
+        rv o[2 * NO + PR];
+#pragma unroll
+        for (int j = -NO; j <= NO - 1 + PR; ++j) {
+            const int z = zb + j;
+            o[j + NO] = ld(xo + pxy + (z < 0 || z >= nz ? (long)wz(z) * plane : 0L));
+        }
+#pragma unroll
+        for (int j = 0; j < PQ; ++j) {
+            ox[j] = ld(edge_at(zb + j));
+#pragma unroll
+            for (int i = 0; i < HM; ++i) oh[j][i] = ld(halo_at(i, zb + j));
+        }
+#pragma unroll
+        for (int j = -NO; j <= NO - 1 + PR; ++j) {
+            const int z = zb + j;
+            rv& v = q[(j + 2 * RING) % RING];
+            if (z < 0) v = rot(v, o[j + NO], 2, -1);
+            else if (z >= nz) v = rot(v, o[j + NO], 2, 1);
+        }
+    }
     // own points of one plane into a buffer, with the x-wrap copies
-    auto put = [&](T* buf, rv v) {
+    auto put = [&](T* buf, rv v, rv oth) {
         if (active) {
             *reinterpret_cast<lv*>(buf + lrow) = v;
-            if (wleft) *reinterpret_cast<lv*>(buf + lrow + nx) = v;
-            if (wright) *reinterpret_cast<lv*>(buf + lrow - nx) = v;
+            if (wleft) *reinterpret_cast<lv*>(buf + lrow + nx) = BL ? rot(v, oth, 0, 1) : v;
+            if (wright) *reinterpret_cast<lv*>(buf + lrow - nx) = BL ? rot(v, oth, 0, -1) : v;
         }
     };
-    put(buf0, q[0]);
+    auto put_halo = [&](T* buf, int i, rv v, rv oth) {
+        if (i < hn) *reinterpret_cast<lv*>(buf + loff[i]) = BL && hwrap[i] ? rot(v, oth, 1, hwrap[i]) : v;
+    };
+    put(buf0, q[0], ox[0]);
 #pragma unroll
-    for (int i = 0; i < HM; ++i)
-        if (i < hn) *reinterpret_cast<lv*>(buf0 + loff[i]) = ld(xc + goff[i] + (long)zb * plane);
+    for (int i = 0; i < HM; ++i) put_halo(buf0, i, ld(xc + goff[i] + (long)zb * plane), oh[0][i]);
 
     for (int z0 = zb; z0 < ze; z0 += RING) {
+        if constexpr (BL) {
+            auto step = [&](int U, int z) __attribute__((always_inline)) {
+#include "sweep_step.inc"
+            };
+            each_phase(step, z0, ze, std::make_integer_sequence<int, RING>());
+        } else {
 #pragma unroll
-        for (int U = 0; U < RING; ++U) {
-            const int z = z0 + U;
-            if (z >= ze) break;
-            const int P = U & 1, QS = U % PQ, QN = (U + 1) % PQ;
-            __syncthreads();
-            // 1. loads of later planes
-            {
-                const long zo = (long)wz(z + PQ) * plane;
-#pragma unroll
-                for (int i = 0; i < HM; ++i) hq[QS][i] = ld(xc + goff[i] + zo);
-                q[(U + NO + PR + RING) % RING] = ld(xc + pxy + (long)wz(z + NO + PR) * plane);
+            for (int U = 0; U < RING; ++U) {
+                const int z = z0 + U;
+                if (z >= ze) break;
+#include "sweep_step.inc"
             }
-            // 2. plane z: y and z neighbours, then x
-            const T* rp = (P ? buf1 : buf0) + lrow;
-            const int C = U % RING;
-            rv lap = cc * q[C];
-#pragma unroll
-            for (int k = 1; k <= NO; ++k) {
-                const rv yy = *reinterpret_cast<const lv*>(rp + k * W) + *reinterpret_cast<const lv*>(rp - k * W);
-                const rv zz = q[(U + k) % RING] + q[(U + RING - k) % RING];
-                lap += a.cy[k] * yy;
-                lap += a.cz[k] * zz;
-            }
-            {
-                // x window of the thread's points: whole vectors on both sides
-                constexpr int NV = (NO + VX - 1) / VX;
-                T w[(2 * NV + 1) * VX];
-#pragma unroll
-                for (int v = -NV; v <= NV; ++v) {
-                    rv u;
-                    if (v == 0) u = q[C];
-                    else u = *reinterpret_cast<const lv*>(rp + v * VX);
-#pragma unroll
-                    for (int e = 0; e < VX; ++e) w[(v + NV) * VX + e] = u[e];
-                }
-#pragma unroll
-                for (int k = 1; k <= NO; ++k)
-#pragma unroll
-                    for (int e = 0; e < VX; ++e) lap[e] += a.cx[k] * (w[NV * VX + e + k] + w[NV * VX + e - k]);
-            }
-            rv o = lap + ve[QS] * q[C];
-            if (MODE != 0) o *= alpha;
-            if (MODE == 2) o += beta * xp[QS];
-            if (active) {
-                T* op = oc + pxy + (long)z * plane;
-                if (ALN || e0 == 0) {
-                    __builtin_nontemporal_store((gv)o, reinterpret_cast<gv*>(op));
-                } else {
-#pragma unroll
-                    for (int e = 1; e < VX; ++e)
-                        if (e >= e0) __builtin_nontemporal_store(o[e], op + e);
-                }
-            }
-            // 3. queue loads of plane z + PQ
-            {
-                const long zo = (long)wz(z + PQ) * plane;
-                if (MODE == 2) xp[QS] = __builtin_nontemporal_load(reinterpret_cast<const gv*>(pc + pxy + zo));
-                ve[QS] = ld(a.veff + pxy + zo);
-            }
-            // 4. LDS plane of z + 1
-            T* nbuf = P ? buf0 : buf1;
-            put(nbuf, q[(U + 1) % RING]);
-#pragma unroll
-            for (int i = 0; i < HM; ++i)
-                if (i < hn) *reinterpret_cast<lv*>(nbuf + loff[i]) = hq[QN][i];
         }
     }
 }
@@ -305,11 +314,12 @@ static long sweep_rounds(long tiles, int round, int resident, int nz, int* split
 // from 6 waves per compute unit on the loads hide each other (72^3 x 260 FP64:
 // 484 us with 7 and with 11 waves).  Slabs of less than 12 rows need two halo
 // vectors per thread, which spills (72^3: 700 us with 7 rows).
-static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol) {
+static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol, bool bloch) {
     const int nx = c->nx, ny = c->ny, lw = div_up(nx, vx), halo = 2 * kMaxHalfOrder;
     int forced = 0;   // tuning override: rows per y-slab
     if (const char* e = std::getenv("SPARC_GPU_SWEEP_TY")) forced = std::atoi(e);
-    SweepPlan& plan = c->sweep_plans[tsize == 8];
+    SweepPlan& plan = c->sweep_plans[(tsize == 8) + 2 * bloch];
+    const int max_threads = bloch ? kSweepThreadsBl : kSweepThreads, max_waves = bloch ? kSweepWavesBl : kSweepWaves;
     if (plan.ncol == ncol && plan.forced == forced) return plan;
     SweepPlan best;
     double least = 0;
@@ -319,14 +329,14 @@ static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol) {
         s.forced = forced;
         s.ty = ty;
         s.threads = div_up((long)lw * ty, 64) * 64;
-        if (s.threads > kSweepThreads) break;
+        if (s.threads > max_threads) break;
         const int waves = s.threads / 64;
         const size_t lds = 2 * (size_t)(ty + halo) * sweep_row(nx) * tsize;
         if (lds > 160 * 1024) break;
-        const int resident = std::max(1, std::min((int)(160 * 1024 / lds), kSweepWaves / waves));
+        const int resident = std::max(1, std::min((int)(160 * 1024 / lds), max_waves / waves));
         s.round = std::max(1, c->prop.multiProcessorCount / 8) * resident;
         const double plane = resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (resident * waves)) *
-                             (halo * lw > s.threads ? 1.5 : 1.0);
+                             (halo * lw > s.threads && !bloch ? 1.5 : 1.0);
         const double cost =
             plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, resident, c->nz, &s.split);
         if (best.ty == 0 || ty == forced || (cost < least && best.ty != forced)) {
@@ -362,20 +372,29 @@ const float* veff_of<float>(sparc_gpu_ctx c) {
 
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx, int mode,
-                           int step) {
+                           int step, bool halves) {
     hipStream_t stream = c->stream;
     SweepArgs<T> a;
     a.x = x;
     a.out = out;
     a.xprev = xprev;
     a.ldx = ldx;
+    a.halves = halves ? 1 : 0;
+    a.half = c->nd;
+    {
+        const double kl[3] = {c->kvec[0] * c->Lx, c->kvec[1] * c->Ly, c->kvec[2] * c->Lz};
+        for (int d = 0; d < 3; ++d) {
+            a.ph[2 * d] = std::cos(kl[d]);
+            a.ph[2 * d + 1] = std::sin(kl[d]);
+        }
+    }
     a.nx = c->nx;
     a.ny = c->ny;
     a.nz = c->nz;
     // 16 bytes of a row per thread; rows of FP32 that are no multiple of 4 points
     // take unaligned vectors
     constexpr int VX = 16 / sizeof(T);
-    const SweepPlan sh = sweep_plan(c, VX, sizeof(T), ncol);
+    const SweepPlan sh = sweep_plan(c, VX, sizeof(T), ncol, halves);
     if (sh.ty == 0) return set_err(c, SPARC_ERR_ARG, "grid x-extent too large for the sweep kernel");
     a.ty = sh.ty;
     a.ntiles_y = div_up(c->ny, a.ty);
@@ -410,16 +429,18 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     const int slot = prof_begin(c, mode == 2 ? PK_SWEEP : (mode == 1 ? PK_SWEEP1 : PK_APPLY), stream);
     const dim3 g((unsigned)(8 * slots)), b(sh.threads);
     const bool aln = c->nx % VX == 0;
-#define SG_SWEEP_HM(MV, AL)                                                            \
+#define SG_SWEEP_HM(MV, AL, BL)                                                        \
     do {                                                                               \
-        if (hm == 1) k_hsweep<T, VX, AL, MV, 1><<<g, b, shmem, stream>>>(a);           \
-        else if (hm == 2) k_hsweep<T, VX, AL, MV, 2><<<g, b, shmem, stream>>>(a);      \
-        else k_hsweep<T, VX, AL, MV, 3><<<g, b, shmem, stream>>>(a);                   \
+        if (hm == 1) k_hsweep<T, VX, AL, MV, 1, BL><<<g, b, shmem, stream>>>(a);       \
+        else if (hm == 2) k_hsweep<T, VX, AL, MV, 2, BL><<<g, b, shmem, stream>>>(a);  \
+        else k_hsweep<T, VX, AL, MV, 3, BL><<<g, b, shmem, stream>>>(a);               \
     } while (0)
-#define SG_SWEEP(MV)                      \
-    do {                                  \
-        if (aln) SG_SWEEP_HM(MV, true);   \
-        else SG_SWEEP_HM(MV, false);      \
+#define SG_SWEEP(MV)                                     \
+    do {                                                 \
+        if (aln && halves) SG_SWEEP_HM(MV, true, true);  \
+        else if (aln) SG_SWEEP_HM(MV, true, false);      \
+        else if (halves) SG_SWEEP_HM(MV, false, true);   \
+        else SG_SWEEP_HM(MV, false, false);              \
     } while (0)
     if (mode == 0) SG_SWEEP(0);
     else if (mode == 1) SG_SWEEP(1);
@@ -431,9 +452,10 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     return SPARC_OK;
 }
 
-template sparc_status launch_hsweep<double>(sparc_gpu_ctx, const double*, double*, const double*, int, long, int,
-                                            int);
-template sparc_status launch_hsweep<float>(sparc_gpu_ctx, const float*, float*, const float*, int, long, int, int);
+template sparc_status launch_hsweep<double>(sparc_gpu_ctx, const double*, double*, const double*, int, long, int, int,
+                                            bool);
+template sparc_status launch_hsweep<float>(sparc_gpu_ctx, const float*, float*, const float*, int, long, int, int,
+                                           bool);
 
 // ---- allocation-free filter -----------------------------------------------
 // The projection partials of sparc_gpu_chebyshev_filter_noalloc live in this

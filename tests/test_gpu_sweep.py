@@ -70,3 +70,36 @@ def test_sweep_rounds_do_not_change_results(monkeypatch):
         outs.append(to_np(Xd[:7]))
     for o in outs[1:]:
         assert np.array_equal(o, outs[0])
+
+
+@pytest.mark.parametrize("n", [(13, 13, 13), (17, 15, 24), (24, 24, 24), (130, 14, 13), (253, 13, 14)])
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_bloch_sweep_matches_oracle(n, dtype):
+    """The Bloch form of the sweep (wrapped values times exp(+-i k L)) and of the
+    nonlocal pass at a general k, contiguous and padded columns."""
+    torch = require_gpu()
+    from oracle import kpoints
+    from paper_2005_10431_amd import Context
+    L = tuple(0.3 * v * (1 + 0.02 * d) for d, v in enumerate(n))
+    ncol = 2 if n[0] > 100 else 9
+    s = W.tiny_system(n=n, L=L, n_atoms=2, seed=2, n_states=ncol)
+    s.rcut_nl, s.rc_nl = 1.4, 0.6
+    k = (0.31, -0.17, 0.23)
+    v = np.random.default_rng(5).uniform(-1.0, 0.5, s.nd)
+    Z = W.initial_orbitals_k(s.nd, ncol, 4)
+    projs = kpoints.projectors_k(s, k)
+    ctx = Context(s)
+    ctx.set_veff(to_dev(torch, v))
+    for pad in (0, 3):
+        X = np.zeros((ncol, 2 * s.nd + pad), dtype=dtype)
+        X[:, :s.nd], X[:, s.nd:2 * s.nd] = Z.real, Z.imag
+        Zx = X[:, :s.nd].astype(np.float64) + 1j * X[:, s.nd:2 * s.nd].astype(np.float64)
+        ref = kpoints.apply_H_k(s, v, projs, Zx, k)
+        Xd = to_dev(torch, X)
+        Yd = torch.full_like(Xd, 7.0)
+        ctx.apply_H_k(k, Xd, Yd)
+        Y = to_np(Yd).astype(np.float64)
+        err = rel_err(Y[:, :s.nd] + 1j * Y[:, s.nd:2 * s.nd], ref)
+        log(f"{n} {dtype} pad {pad}: H_k X {err:.2e}")
+        assert err <= (1e-12 if dtype == "float64" else 2e-6)
+        assert np.all(Y[:, 2 * s.nd:] == 7.0)

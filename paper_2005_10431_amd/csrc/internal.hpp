@@ -66,7 +66,10 @@ struct NlPass {
 // Shape of a sweep over ncol columns (see sweep_plan)
 struct SweepPlan {
     int ncol = 0, forced = 0;        // what it was made for
-    int ty = 0, threads = 0;         // rows of a slab, threads of its workgroup
+    int vx = 0, ty = 0;              // points per thread, rows of a slab
+    bool wide = false;               // slabs of less than 4 rows
+    int threads = 0, resident = 1;   // of a workgroup; workgroups a compute unit holds
+    size_t lds = 0;                  // of a workgroup
     int round = 1, split = 1;        // workgroups an XCD holds, z ranges past its last full round
 };
 

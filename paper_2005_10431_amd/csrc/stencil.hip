@@ -62,19 +62,33 @@ constexpr int kRing = 16;            // z-ring slots: planes z-6 .. z+6 and 3 in
 constexpr int kRingAhead = kRing - 2 * kMaxHalfOrder - 1;
 constexpr int kQueue = 2;            // depth of the halo / X_{k-1} / V_eff queues
 static_assert(kRing % kQueue == 0, "the unrolled step count must cycle every queue");
-constexpr int kSweepPad = 8;         // columns left and right of a row in LDS
 
-// values of a row in LDS: 8 on both sides, a multiple of 4
-__host__ __device__ inline int sweep_row(int nx) { return (nx + 2 * kSweepPad + 3) / 4 * 4; }
+// Points per thread: the widest of 16, 8 and 4 bytes (FP64 16, 8) that divides
+// n_x, so that a row is whole vectors, each at an aligned place in LDS.  (With
+// the last vector of a row moved back instead, LDS takes unaligned accesses:
+// 62 x 29 x 45 x 116 in FP32 50.7 instead of 28.7 us, 51 x 68 x 93 x 77 in FP64
+// 176 instead of 123 us.)
+template <typename T>
+static int sweep_vx(int nx) {
+    const int vx = 16 / (int)sizeof(T);
+    return nx % vx == 0 ? vx : (vx == 4 && nx % 2 == 0 ? 2 : 1);
+}
 
-// Threads of a workgroup at most, and waves a compute unit holds: three per
-// SIMD at 168 VGPRs (FP32 with two points per thread and four waves per SIMD
-// took 275 instead of 254 us at 72^3 x 260).
-constexpr int kSweepThreads = 768;
-constexpr int kSweepWaves = 12;
-// The Bloch sweep keeps the other half's values too: two waves per SIMD.
-constexpr int kSweepThreadsBl = 512;
-constexpr int kSweepWavesBl = 8;
+// columns left and right of a row in LDS, and values of a row
+__host__ __device__ constexpr int sweep_pad(int vx) { return vx == 1 ? kMaxHalfOrder : 8; }
+__host__ __device__ constexpr int sweep_row(int nx, int vx) { return nx + 2 * sweep_pad(vx); }
+
+// Waves per SIMD, and with them the threads of a workgroup at most: three at 168
+// VGPRs with 16 bytes per thread (FP32 with two points per thread and four waves
+// per SIMD took 275 instead of 254 us at 72^3 x 260), four with less; two for the
+// Bloch sweep, which keeps the other half's values too.
+__host__ __device__ constexpr int sweep_simd_waves(size_t bytes, bool bloch) {
+    return bloch ? 2 : (bytes == 16 ? 3 : 4);
+}
+// Rows so wide that no slab of 4 rows fits a workgroup: slabs of 1 to 3 rows, one
+// point and up to 12 halo values per thread.
+constexpr int kSweepWideHalo = 2 * kMaxHalfOrder;
+constexpr int kSweepWideThreads = 1024;
 
 template <typename T, int N, int A>
 struct VecOf {
@@ -88,10 +102,8 @@ __device__ __forceinline__ void each_phase(F& f, int z0, int ze, std::integer_se
 }
 
 // The sweep.  MODE: 0 out = H_loc x; 1 first filter step; 2 filter step `step`
-// (>= 2) with xprev = X_{k-1} (may alias out).  VX: points per thread; ALN: n_x
-// is a multiple of VX (else the last thread of a row starts VX points before
-// its end and stores only the points the thread before it does not hold).
-// HM: halo vectors per thread and plane.
+// (>= 2) with xprev = X_{k-1} (may alias out).  VX: points per thread, a
+// divisor of n_x.  HM: halo vectors per thread and plane.
 //
 // One z-plane step at ring phase U (z = z0 + U).  On entry the LDS buffer of
 // parity U holds plane z (own rows with x-wrap padding and halo rows), written
@@ -111,17 +123,17 @@ __device__ __forceinline__ void each_phase(F& f, int z0, int ze, std::integer_se
 // ring planes).  The other half's values come by loads of their own, for all
 // lanes alike (where none is needed, from one place that stays in cache), so
 // that the loads in flight can be counted.
-template <typename T, int VX, bool ALN, int MODE, int HM, bool BL>
-__global__ __launch_bounds__(BL ? kSweepThreadsBl : kSweepThreads) void k_hsweep(SweepArgs<T> a) {
+template <typename T, int VX, int MODE, int HM, bool BL>
+__global__ __launch_bounds__(HM == kSweepWideHalo ? kSweepWideThreads
+                                                  : 256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_hsweep(SweepArgs<T> a) {
     constexpr int NO = kMaxHalfOrder;
     constexpr int RING = kRing, PR = kRingAhead, PQ = kQueue;
-    constexpr int PAD = kSweepPad;
-    using gv = typename VecOf<T, VX, sizeof(T)>::type;                     // in global memory
-    using lv = typename VecOf<T, VX, ALN ? VX * sizeof(T) : sizeof(T)>::type;   // in LDS
-    using rv = typename VecOf<T, VX, VX * sizeof(T)>::type;
+    constexpr int PAD = sweep_pad(VX);
+    using gv = typename VecOf<T, VX, sizeof(T)>::type;        // in global memory
+    using rv = typename VecOf<T, VX, VX * sizeof(T)>::type;   // in registers and LDS
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int W = sweep_row(nx);
+    const int W = sweep_row(nx, VX);
     const int R = a.ty + 2 * NO;
 
     // Hardware dispatches block b to XCD b % 8.  Give each XCD a contiguous
@@ -154,10 +166,9 @@ __global__ __launch_bounds__(BL ? kSweepThreadsBl : kSweepThreads) void k_hsweep
 
     const int t = threadIdx.x;
     const int nt = blockDim.x;
-    const int LW = (nx + VX - 1) / VX;
+    const int LW = nx / VX;
     const int lx = t % LW, ly = t / LW;
-    const int x0 = ALN ? lx * VX : min(lx * VX, nx - VX);
-    const int e0 = lx * VX - x0;              // first point this thread stores
+    const int x0 = lx * VX;
     const bool active = ly < tyn;
     const bool wleft = x0 < NO, wright = x0 + VX > nx - NO;   // wraps into the padding
     const long plane = (long)nx * ny;
@@ -198,7 +209,7 @@ __global__ __launch_bounds__(BL ? kSweepThreadsBl : kSweepThreads) void k_hsweep
         if (e < nhalo) {
             hn = i + 1;
             const int hr = e / LW, hl = e - hr * LW;
-            const int hx = ALN ? hl * VX : min(hl * VX, nx - VX);
+            const int hx = hl * VX;
             const int lr = hr < NO ? hr : tyn + hr;
             int gy = y0 - NO + lr;
             hwrap[i] = gy < 0 ? -1 : (gy >= ny ? 1 : 0);
@@ -259,13 +270,13 @@ __global__ __launch_bounds__(BL ? kSweepThreadsBl : kSweepThreads) void k_hsweep
     // own points of one plane into a buffer, with the x-wrap copies
     auto put = [&](T* buf, rv v, rv oth) {
         if (active) {
-            *reinterpret_cast<lv*>(buf + lrow) = v;
-            if (wleft) *reinterpret_cast<lv*>(buf + lrow + nx) = BL ? rot(v, oth, 0, 1) : v;
-            if (wright) *reinterpret_cast<lv*>(buf + lrow - nx) = BL ? rot(v, oth, 0, -1) : v;
+            *reinterpret_cast<rv*>(buf + lrow) = v;
+            if (wleft) *reinterpret_cast<rv*>(buf + lrow + nx) = BL ? rot(v, oth, 0, 1) : v;
+            if (wright) *reinterpret_cast<rv*>(buf + lrow - nx) = BL ? rot(v, oth, 0, -1) : v;
         }
     };
     auto put_halo = [&](T* buf, int i, rv v, rv oth) {
-        if (i < hn) *reinterpret_cast<lv*>(buf + loff[i]) = BL && hwrap[i] ? rot(v, oth, 1, hwrap[i]) : v;
+        if (i < hn) *reinterpret_cast<rv*>(buf + loff[i]) = BL && hwrap[i] ? rot(v, oth, 1, hwrap[i]) : v;
     };
     put(buf0, q[0], ox[0]);
 #pragma unroll
@@ -315,34 +326,44 @@ static long sweep_rounds(long tiles, int round, int resident, int nz, int* split
 // 484 us with 7 and with 11 waves).  Slabs of less than 12 rows need two halo
 // vectors per thread, which spills (72^3: 700 us with 7 rows).
 static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol, bool bloch) {
-    const int nx = c->nx, ny = c->ny, lw = div_up(nx, vx), halo = 2 * kMaxHalfOrder;
+    const int nx = c->nx, ny = c->ny, lw = nx / vx, halo = 2 * kMaxHalfOrder;
     int forced = 0;   // tuning override: rows per y-slab
     if (const char* e = std::getenv("SPARC_GPU_SWEEP_TY")) forced = std::atoi(e);
     SweepPlan& plan = c->sweep_plans[(tsize == 8) + 2 * bloch];
-    const int max_threads = bloch ? kSweepThreadsBl : kSweepThreads, max_waves = bloch ? kSweepWavesBl : kSweepWaves;
     if (plan.ncol == ncol && plan.forced == forced) return plan;
+    const int max_waves = 4 * sweep_simd_waves(vx * tsize, bloch), max_threads = 64 * max_waves;
     SweepPlan best;
     double least = 0;
-    for (int ty = 4; ty <= ny; ++ty) {
+    auto shape = [&](int vec, int ty, int waves_cu) {
         SweepPlan s;
         s.ncol = ncol;
         s.forced = forced;
+        s.vx = vec;
         s.ty = ty;
-        s.threads = div_up((long)lw * ty, 64) * 64;
-        if (s.threads > max_threads) break;
-        const int waves = s.threads / 64;
-        const size_t lds = 2 * (size_t)(ty + halo) * sweep_row(nx) * tsize;
-        if (lds > 160 * 1024) break;
-        const int resident = std::max(1, std::min((int)(160 * 1024 / lds), max_waves / waves));
-        s.round = std::max(1, c->prop.multiProcessorCount / 8) * resident;
-        const double plane = resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (resident * waves)) *
+        s.threads = div_up((long)nx / vec * ty, 64) * 64;
+        s.lds = 2 * (size_t)(ty + halo) * sweep_row(nx, vec) * tsize;
+        s.resident = std::max(1, std::min((int)(160 * 1024 / s.lds), waves_cu * 64 / s.threads));
+        s.round = std::max(1, c->prop.multiProcessorCount / 8) * s.resident;
+        return s;
+    };
+    for (int ty = 4; ty <= ny; ++ty) {
+        SweepPlan s = shape(vx, ty, max_waves);
+        if (s.threads > max_threads || s.lds > 160 * 1024) break;
+        const double plane = s.resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (s.resident * s.threads / 64)) *
                              (halo * lw > s.threads && !bloch ? 1.5 : 1.0);
         const double cost =
-            plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, resident, c->nz, &s.split);
+            plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, s.resident, c->nz, &s.split);
         if (best.ty == 0 || ty == forced || (cost < least && best.ty != forced)) {
             least = cost;
             best = s;
         }
+    }
+    for (int ty = std::min(3, ny); ty >= 1 && best.ty == 0; --ty) {
+        SweepPlan s = shape(1, ty, kSweepWideThreads / 64);
+        if (s.threads > kSweepWideThreads || s.lds > 160 * 1024) continue;
+        s.wide = true;
+        sweep_rounds((long)ncol * div_up(ny, ty), s.round, s.resident, c->nz, &s.split);
+        best = s;
     }
     plan = best;
     return best;
@@ -391,10 +412,7 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     a.nx = c->nx;
     a.ny = c->ny;
     a.nz = c->nz;
-    // 16 bytes of a row per thread; rows of FP32 that are no multiple of 4 points
-    // take unaligned vectors
-    constexpr int VX = 16 / sizeof(T);
-    const SweepPlan sh = sweep_plan(c, VX, sizeof(T), ncol, halves);
+    const SweepPlan sh = sweep_plan(c, sweep_vx<T>(c->nx), sizeof(T), ncol, halves);
     if (sh.ty == 0) return set_err(c, SPARC_ERR_ARG, "grid x-extent too large for the sweep kernel");
     a.ty = sh.ty;
     a.ntiles_y = div_up(c->ny, a.ty);
@@ -412,8 +430,7 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     a.params = c->scal + S_A;
     a.step = step;
     a.ncol = ncol;
-    const size_t shmem = 2 * (size_t)(a.ty + 2 * kMaxHalfOrder) * sweep_row(c->nx) * sizeof(T);
-    const int hm = div_up(2L * kMaxHalfOrder * div_up(c->nx, VX), sh.threads);   // 1 to 3: ty >= 4
+    const int hm = div_up(2L * kMaxHalfOrder * (c->nx / sh.vx), sh.threads);   // 1 to 3 with slabs of 4 rows
     const long tiles = (long)ncol * a.ntiles_y;
     if (tiles > 0x3fffffffL) return set_err(c, SPARC_ERR_ARG, "too many blocks");
     if (tiles == 0) return SPARC_OK;
@@ -426,27 +443,30 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
         const long whole = n / a.round * a.round;
         slots = std::max(slots, whole + (n - whole) * a.split);
     }
-    const int slot = prof_begin(c, mode == 2 ? PK_SWEEP : (mode == 1 ? PK_SWEEP1 : PK_APPLY), stream);
+    const int slot = prof_begin(c, halves ? PK_BLOCH : mode == 2 ? PK_SWEEP : mode == 1 ? PK_SWEEP1 : PK_APPLY, stream);
     const dim3 g((unsigned)(8 * slots)), b(sh.threads);
-    const bool aln = c->nx % VX == 0;
-#define SG_SWEEP_HM(MV, AL, BL)                                                        \
-    do {                                                                               \
-        if (hm == 1) k_hsweep<T, VX, AL, MV, 1, BL><<<g, b, shmem, stream>>>(a);       \
-        else if (hm == 2) k_hsweep<T, VX, AL, MV, 2, BL><<<g, b, shmem, stream>>>(a);  \
-        else k_hsweep<T, VX, AL, MV, 3, BL><<<g, b, shmem, stream>>>(a);               \
-    } while (0)
-#define SG_SWEEP(MV)                                     \
-    do {                                                 \
-        if (aln && halves) SG_SWEEP_HM(MV, true, true);  \
-        else if (aln) SG_SWEEP_HM(MV, true, false);      \
-        else if (halves) SG_SWEEP_HM(MV, false, true);   \
-        else SG_SWEEP_HM(MV, false, false);              \
-    } while (0)
-    if (mode == 0) SG_SWEEP(0);
-    else if (mode == 1) SG_SWEEP(1);
-    else SG_SWEEP(2);
-#undef SG_SWEEP
-#undef SG_SWEEP_HM
+    auto go = [&](auto vx, auto mv, auto hv, auto bl) {
+        k_hsweep<T, vx(), mv(), hv(), bl()><<<g, b, sh.lds, stream>>>(a);
+    };
+    auto go_halo = [&](auto vx, auto mv, auto bl) {
+        if (hm == 1) go(vx, mv, std::integral_constant<int, 1>(), bl);
+        else if (hm == 2) go(vx, mv, std::integral_constant<int, 2>(), bl);
+        else go(vx, mv, std::integral_constant<int, 3>(), bl);
+    };
+    auto go_width = [&](auto mv, auto bl) {
+        if (sh.wide) return go(std::integral_constant<int, 1>(), mv, std::integral_constant<int, kSweepWideHalo>(), bl);
+        if (sh.vx == 1) return go_halo(std::integral_constant<int, 1>(), mv, bl);
+        if constexpr (sizeof(T) == 4)
+            if (sh.vx == 4) return go_halo(std::integral_constant<int, 4>(), mv, bl);
+        go_halo(std::integral_constant<int, 2>(), mv, bl);
+    };
+    auto go_mode = [&](auto bl) {
+        if (mode == 0) go_width(std::integral_constant<int, 0>(), bl);
+        else if (mode == 1) go_width(std::integral_constant<int, 1>(), bl);
+        else go_width(std::integral_constant<int, 2>(), bl);
+    };
+    if (halves) go_mode(std::true_type());
+    else go_mode(std::false_type());
     SG_CHECK_LAUNCH(c);
     prof_end(c, slot, stream);
     return SPARC_OK;

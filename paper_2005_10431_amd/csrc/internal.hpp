@@ -67,9 +67,8 @@ struct NlPass {
 struct SweepPlan {
     int ncol = 0, forced = 0;        // what it was made for
     int vx = 0, ty = 0;              // points per thread, rows of a slab
-    bool wide = false;               // slabs of less than 4 rows
-    int threads = 0, resident = 1;   // of a workgroup; workgroups a compute unit holds
-    size_t lds = 0;                  // of a workgroup
+    int threads = 0;                 // of a workgroup
+    size_t lds = 0;
     int round = 1, split = 1;        // workgroups an XCD holds, z ranges past its last full round
 };
 

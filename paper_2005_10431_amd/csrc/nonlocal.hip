@@ -228,12 +228,13 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     int* xy = reinterpret_cast<int*>(smem_raw + L.xy);
     uint8_t* occ = reinterpret_cast<uint8_t*>(smem_raw + L.occ);
 
-    // block b runs on XCD b % 8: each XCD takes a contiguous range of units
-    const int nblk = gridDim.x, bid = blockIdx.x;
-    const int qn = nblk / 8, rn = nblk % 8;
-    const int xcd = bid % 8;
-    const int logical = xcd * qn + min(xcd, rn) + bid / 8;
-    const int chunk = logical % a.nchunk, u = logical / a.nchunk;
+    // block b runs on XCD b % 8.  All units of 64 orbitals go before the next
+    // orbitals, the last ones first (see PassOrder); an XCD takes a contiguous
+    // eighth of the units, a different one each time, since some hold one more
+    const int bslot = blockIdx.x / 8, per = (a.nunit + 7) / 8;
+    const int chunk = a.nchunk - 1 - bslot / per, xr = (blockIdx.x + 3 * chunk) % 8;
+    const int u = a.nunit / 8 * xr + min(xr, a.nunit % 8) + bslot % per;
+    if (bslot % per >= a.nunit / 8 + (xr < a.nunit % 8 ? 1 : 0)) return;
     const NlUnit U = a.units[u];
     const int nzl = U.ze - U.zb;
     const int t = threadIdx.x, nt = blockDim.x;
@@ -531,37 +532,87 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
     const int nx = c->nx, ny = c->ny, nz = c->nz, nxy = nx * ny;
     const int nb = (nxy + 15) / 16;
     NlPass& T = c->nlp;
-    // pencils: cells of rows x x-range, a block belonging to the cell of its
-    // first point, cut into lists of kNlBlocks.  Among the cell shapes take the
-    // one with the fewest block places times the area whose atoms reach it.
-    auto cells = [&](int npx, int by, std::vector<int>& cell) {
-        cell.resize(nb);
+    // Pencils: blocks cut into lists of kNlBlocks.  Either cells of rows x
+    // x-range, a block belonging to the cell of its first point, or runs of R
+    // consecutive blocks, one per row, a row taken as m whole runs (every pencil
+    // but the last is full, but drifts in x where m runs are not n_x points).
+    std::vector<std::vector<int>> lists, trial;
+    auto cells = [&](int npx, int by) {
+        trial.assign((size_t)npx * ((ny + by - 1) / by), {});
         for (int b = 0; b < nb; ++b) {
             const int x = (16 * b) % nx, y = (16 * b) / nx;
-            cell[b] = (y / by) * npx + std::min(npx - 1, (int)((long)x * npx / nx));
+            trial[(y / by) * npx + std::min(npx - 1, (int)((long)x * npx / nx))].push_back(b);
         }
     };
-    int bnpx = 1, bby = 1;
-    double best = 1e300;
-    std::vector<int> cell;
-    for (int by = 1; by <= std::min(6, ny); ++by)
-        for (int npx = 1; npx <= (nx + 15) / 16; ++npx) {
-            cells(npx, by, cell);
-            std::vector<int> cnt((size_t)npx * ((ny + by - 1) / by), 0);
-            for (int b = 0; b < nb; ++b) cnt[cell[b]]++;
-            long np = 0;
-            for (int v : cnt) np += (v + kNlBlocks - 1) / kNlBlocks;
-            const double wx = std::min(c->Lx, ((double)nx / npx + 8) * c->hx), wy = by * c->hy, r = c->rcut_nl;
-            const double cost = (double)np * (wx * wy + 2 * r * (wx + wy) + 3.14159265358979 * r * r);
-            if (cost < best) {
-                best = cost;
-                bnpx = npx;
-                bby = by;
+    auto runs = [&](int R) {
+        const int G = kNlBlocks / R, m = std::max(1, (2 * nx / (16 * R) + 1) / 2);
+        trial.assign((size_t)(nb / (R * G * m) + 1) * m, {});
+        for (int b = 0; b < nb; ++b) trial[b / R / (m * G) * m + b / R % m].push_back(b);
+    };
+    // Time of a plane of an average pencil: a block place costs one, more where
+    // planes are no whole 128-byte lines and each run of blocks shares one with
+    // its neighbours (97 x 98 x 81 x 504 FP64, H X without its sweep: 3420 us
+    // with 5.6-block cells of single blocks, 3100 with full pencils of them, 2810
+    // in runs of 2, 2840 in runs of 3); a slot in use costs 0.4 (96 x 98 x 81 x
+    // 504: 2250 us with up to 9, 2421 with up to 12); past 16 slots one workgroup
+    // instead of two fits a compute unit (72^3 x 260: 765 and 1250 us).
+    auto plane_time = [&](int* npen) {
+        double sum = 0;
+        *npen = 0;
+        for (const auto& l : trial) {
+            if (l.empty()) continue;
+            const size_t parts = (l.size() + kNlBlocks - 1) / kNlBlocks, per = (l.size() + parts - 1) / parts;
+            for (size_t i = 0; i < l.size(); i += per, ++*npen) {
+                const size_t e = std::min(l.size(), i + per);
+                const int x0 = (16 * l[i]) % nx, y0 = (16 * l[i]) / nx;
+                int lo = 0, hi = 16, y1 = y0, nrun = 0;
+                for (size_t j = i; j < e; ++j) {
+                    const int x = (16 * l[j]) % nx, d = (x - x0 + nx + nx / 2) % nx - nx / 2;
+                    lo = std::min(lo, d);
+                    hi = std::max(hi, d + 16);
+                    y1 = std::min(ny - 1, (16 * l[j] + 15) / nx);
+                    nrun += j == i || l[j] != l[j - 1] + 1;
+                }
+                const double wx = std::min(c->Lx, (hi - lo) * c->hx), wy = (y1 - y0 + 1) * c->hy, r = c->rcut_nl;
+                const double area = std::min(c->Lx * c->Ly, wx * wy + 2 * r * (wx + wy) + 3.14159265358979 * r * r);
+                const double slots = c->n_atoms * area / (c->Lx * c->Ly) * std::min(1.0, 2 * r / c->Lz);
+                sum += (kNlBlocks + (nxy % 16 ? 0.45 * nrun : 0.0) + 0.4 * slots) * (slots > 12 ? 1.5 : 1.0);
             }
         }
-    cells(bnpx, bby, cell);
-    std::vector<std::vector<int>> lists((size_t)bnpx * ((ny + bby - 1) / bby));
-    for (int b = 0; b < nb; ++b) lists[cell[b]].push_back(b);
+        return sum / *npen;
+    };
+    // z ranges: the count with the least (time of a plane) x (planes one after
+    // another) on a chip that holds 512 workgroups, two per compute unit (alone
+    // on it one takes 0.65 of its time: 8.3 and 13 us a plane at 72^3), a range
+    // costing about 3 planes more than its own (set-up, ends of pairs).  Fixed
+    // here, for the context's full block, so that a column's sums do not depend
+    // on the block it comes in.
+    const int chunks = div_up(div_up(c->n_states, 16), kNlWaves);
+    int zs = 0;
+    double best = 0;
+    auto consider = [&]() {
+        int npen;
+        const double plane = plane_time(&npen);
+        for (int k = (nz + kMaxPlanes - 1) / kMaxPlanes; k <= std::max(1, nz / 4); ++k) {
+            const long n = (long)npen * chunks * k, last = n % 512;
+            const double rounds = n / 512 + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
+            const double cost = plane * rounds * (div_up(nz, k) + 3);
+            if (zs == 0 || cost < best) {
+                best = cost;
+                zs = k;
+                lists = trial;
+            }
+        }
+    };
+    for (int by = 1; by <= std::min(6, ny); ++by)
+        for (int npx = 1; npx <= (nx + 15) / 16; ++npx) {
+            cells(npx, by);
+            consider();
+        }
+    for (int R = 1; R <= 3; ++R) {
+        runs(R);
+        consider();
+    }
     std::vector<int> blk, nblk, pen(nb), place(nb);
     int npen = 0;
     for (auto& l : lists) {
@@ -580,20 +631,6 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
                 pen[l[j]] = npen;
                 place[l[j]] = at;
             }
-        }
-    }
-    // z ranges: the count with the fewest planes one after another on a chip
-    // that holds 512 workgroups, a range costing about 3 planes more than its
-    // own (set-up, ends of pairs).  Fixed here, for the context's full block, so
-    // that a column's sums do not depend on the block it comes in.
-    const long per_range = (long)npen * div_up(div_up(c->n_states, 16), kNlWaves);
-    int zs = 0;
-    long least = 0;
-    for (int k = (nz + kMaxPlanes - 1) / kMaxPlanes; k <= std::max(1, nz / 4); ++k) {
-        const long cost = div_up(per_range * k, 512) * (div_up(nz, k) + 3L);
-        if (zs == 0 || cost < least) {
-            zs = k;
-            least = cost;
         }
     }
     const int zlen = (nz + zs - 1) / zs;
@@ -623,8 +660,8 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
         int z0, z1, cand;
         size_t h0, h1;
     };
-    // slots: each pair takes the lowest free one for its span of planes in the
-    // unit; pairs beyond the slots or the local indices go to a further layer
+    // slots: each pair takes, for its span of planes in the unit, a free one of the
+    // group that meets the fewest further blocks for it (see the layout above); pairs beyond the slots or the local indices go to a further layer
     // (a further pass), which supports this dense do not reach in practice
     struct Placed {
         int slot, local;
@@ -662,20 +699,39 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
                 std::sort(sp.begin(), sp.end(),
                           [](const Span& A, const Span& B) { return A.z0 != B.z0 ? A.z0 < B.z0 : A.cand < B.cand; });
                 for (int layer = 0; !sp.empty(); ++layer) {
-                    std::vector<int> end;   // last plane of each slot's pair
+                    std::vector<int> end(pass == 0 ? 0 : limit, -1);   // last plane of each slot's pair
+                    std::vector<uint32_t> met((size_t)(limit / 4) * (pass == 0 ? 0 : zlen), 0);
                     std::vector<Span> rest;
                     Unit un;
                     un.u = NlUnit{zb, ze, hits[i].pencil, nblk[hits[i].pencil], 0, 0};
                     for (const Span& s : sp) {
-                        size_t q = 0;
-                        while (q < end.size() && end[q] >= s.z0) ++q;
-                        if ((int)q >= limit || (pass == 1 && un.p.size() >= (size_t)kMaxLocal)) {
+                        if (pass == 0) {
+                            size_t q = 0;
+                            while (q < end.size() && end[q] >= s.z0) ++q;
+                            if (q == end.size()) end.push_back(0);
+                            end[q] = s.z1;
+                            continue;
+                        }
+                        int slot = -1, fewest = 1 << 30;
+                        for (int G = 0; G < limit / 4; ++G) {
+                            int q = 4 * G;
+                            while (q < 4 * G + 4 && end[q] >= s.z0) ++q;
+                            if (q == 4 * G + 4) continue;
+                            int n = 0;   // blocks that group G would meet for this pair alone
+                            for (size_t h = s.h0; h < s.h1; ++h)
+                                n += __builtin_popcount(hits[h].mask & ~met[(size_t)G * zlen + hits[h].z - zb]);
+                            if (n < fewest) {
+                                fewest = n;
+                                slot = q;
+                            }
+                        }
+                        if (slot < 0 || un.p.size() >= (size_t)kMaxLocal) {
                             rest.push_back(s);
                             continue;
                         }
-                        if (q == end.size()) end.push_back(0);
-                        end[q] = s.z1;
-                        un.p.push_back({(int)q, (int)un.p.size(), s});
+                        end[slot] = s.z1;
+                        for (size_t h = s.h0; h < s.h1; ++h) met[(size_t)(slot / 4) * zlen + hits[h].z - zb] |= hits[h].mask;
+                        un.p.push_back({slot, (int)un.p.size(), s});
                     }
                     un.u.ncl = (int)un.p.size();
                     if (pass == 0) most = std::max(most, (int)end.size());
@@ -743,17 +799,19 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
     if ((st = put(c, &T.red_off, roff)) != SPARC_OK) return st;
     if ((st = put(c, &T.red_ent, rent)) != SPARC_OK) return st;
     if ((st = put(c, &T.cand_off, coff)) != SPARC_OK) return st;
+    double groups = 0;
+    for (uint64_t w : gm) groups += __builtin_popcountll(w);
     if (c->debug)
         fprintf(stderr,
-                "[sparc_gpu] nonlocal pass: %d pencils (%d x-ranges, %d rows), %zu units of %d planes, %d slots (%d "
-                "used), %zu layers, %ld entries, at most %d pairs per unit\n",
-                npen, bnpx, bby, units.size(), zlen, S, most, layers.size(), T.n_entries, ncl);
+                "[sparc_gpu] nonlocal pass: %d pencils, %zu units of %d planes, %d slots (%d used), %zu layers, %ld "
+                "entries, at most %d pairs per unit, %.2f groups per block\n",
+                npen, units.size(), zlen, S, most, layers.size(), T.n_entries, ncl, groups / ((double)nb * nz));
     return SPARC_OK;
 }
 
 template <typename T, typename C, int S>
 static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, bool ap, bool pr, size_t shmem) {
-    const long nblocks = (long)a.nunit * a.nchunk;
+    const long nblocks = 8L * div_up(a.nunit, 8) * a.nchunk;
     if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "nonlocal pass: too many blocks");
     const dim3 g((unsigned)nblocks), b(64 * std::max(4, a.nwc));
     if (!ap) k_nl_pass<T, C, S, false, true, false><<<g, b, shmem, c->stream>>>(a);

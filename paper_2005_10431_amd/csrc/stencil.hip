@@ -85,10 +85,9 @@ __host__ __device__ constexpr int sweep_row(int nx, int vx) { return nx + 2 * sw
 __host__ __device__ constexpr int sweep_simd_waves(size_t bytes, bool bloch) {
     return bloch ? 2 : (bytes == 16 ? 3 : 4);
 }
-// Rows so wide that no slab of 4 rows fits a workgroup: slabs of 1 to 3 rows, one
-// point and up to 12 halo values per thread.
-constexpr int kSweepWideHalo = 2 * kMaxHalfOrder;
-constexpr int kSweepWideThreads = 1024;
+// Odd rows of more than 128 points (at most 256) leave the 512 threads of a Bloch
+// workgroup slabs of 2 or 3 rows, with up to 6 halo values per thread.
+constexpr int kSweepMaxHalo = 6;
 
 template <typename T, int N, int A>
 struct VecOf {
@@ -124,8 +123,7 @@ __device__ __forceinline__ void each_phase(F& f, int z0, int ze, std::integer_se
 // lanes alike (where none is needed, from one place that stays in cache), so
 // that the loads in flight can be counted.
 template <typename T, int VX, int MODE, int HM, bool BL>
-__global__ __launch_bounds__(HM == kSweepWideHalo ? kSweepWideThreads
-                                                  : 256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_hsweep(SweepArgs<T> a) {
+__global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_hsweep(SweepArgs<T> a) {
     constexpr int NO = kMaxHalfOrder;
     constexpr int RING = kRing, PR = kRingAhead, PQ = kQueue;
     constexpr int PAD = sweep_pad(VX);
@@ -136,15 +134,20 @@ __global__ __launch_bounds__(HM == kSweepWideHalo ? kSweepWideThreads
     const int W = sweep_row(nx, VX);
     const int R = a.ty + 2 * NO;
 
-    // Hardware dispatches block b to XCD b % 8.  Give each XCD a contiguous
-    // range of logical tiles so that the y-slabs of one orbital (which read
-    // each other's rows as halos) share an L2.  Within a group of grp
-    // orbitals the logical order is slab-major, so that the grp copies of a
-    // slab (which read the same V_eff rows) run side by side.
-    const int ntile = a.ncol * a.ntiles_y;
+    // Hardware dispatches block b to XCD b % 8.  The y-slabs of one orbital (which
+    // read each other's rows as halos) share an XCD, so an L2; orbital j goes to
+    // XCD j % 8 (Bloch: both halves to (j / 2) % 8), so that the chip works
+    // through the block from its first orbital to its last (see PassOrder); the
+    // slabs of the last few orbitals are spread evenly over the XCDs.  Within a
+    // group of grp of an XCD's orbitals the order is slab-major, so that the
+    // grp copies of a slab (which read the same V_eff rows) run side by side.
     const int xcd = blockIdx.x % 8, bslot = blockIdx.x / 8;
-    const int mine = ntile / 8 + (xcd < ntile % 8 ? 1 : 0);      // tiles of this XCD
-    const int full = mine / a.round * a.round;                   // of them in full rounds
+    const int cw = BL ? 2 : 1;
+    const int own = a.ncol / (8 * cw) * cw;   // orbitals of this XCD alone
+    const int rest = (a.ncol - 8 * own) * a.ntiles_y;
+    const int rest0 = rest * xcd / 8;
+    const int mine = own * a.ntiles_y + rest * (xcd + 1) / 8 - rest0;   // tiles of this XCD
+    const int full = mine / a.round * a.round;                          // of them in full rounds
     int item = bslot, zpart = 0, zparts = 1;
     if (bslot >= full) {
         zparts = a.split;
@@ -152,12 +155,19 @@ __global__ __launch_bounds__(HM == kSweepWideHalo ? kSweepWideThreads
         zpart = (bslot - full) % a.split;
     }
     if (item >= mine) return;
-    const int logical = xcd * (ntile / 8) + min(xcd, ntile % 8) + item;
-    const int gsz = a.grp * a.ntiles_y;
-    const int gi = logical / gsz, gr = logical - gi * gsz;
-    const int gcols = min(a.grp, a.ncol - gi * a.grp);   // the last group may be short
-    const int tile = gr / gcols;
-    const int col = gi * a.grp + (gr - tile * gcols);
+    int tile, col;
+    if (item < own * a.ntiles_y) {
+        const int gsz = a.grp * a.ntiles_y;
+        const int gi = item / gsz, gr = item - gi * gsz;
+        const int gcols = min(a.grp, own - gi * a.grp);   // the last group may be short
+        tile = gr / gcols;
+        const int j = gi * a.grp + (gr - tile * gcols);
+        col = (j / cw * 8 + xcd) * cw + j % cw;
+    } else {
+        const int r = rest0 + item - own * a.ntiles_y;
+        col = 8 * own + r / a.ntiles_y;
+        tile = r % a.ntiles_y;
+    }
     const int y0 = tile * a.ty;
     const int tyn = min(a.ty, ny - y0);
     const int zlen = (nz + zparts - 1) / zparts;
@@ -334,36 +344,27 @@ static SweepPlan sweep_plan(sparc_gpu_ctx c, int vx, size_t tsize, int ncol, boo
     const int max_waves = 4 * sweep_simd_waves(vx * tsize, bloch), max_threads = 64 * max_waves;
     SweepPlan best;
     double least = 0;
-    auto shape = [&](int vec, int ty, int waves_cu) {
+    for (int ty = bloch ? 2 : 4; ty <= ny; ++ty) {
         SweepPlan s;
         s.ncol = ncol;
         s.forced = forced;
-        s.vx = vec;
+        s.vx = vx;
         s.ty = ty;
-        s.threads = div_up((long)nx / vec * ty, 64) * 64;
-        s.lds = 2 * (size_t)(ty + halo) * sweep_row(nx, vec) * tsize;
-        s.resident = std::max(1, std::min((int)(160 * 1024 / s.lds), waves_cu * 64 / s.threads));
-        s.round = std::max(1, c->prop.multiProcessorCount / 8) * s.resident;
-        return s;
-    };
-    for (int ty = 4; ty <= ny; ++ty) {
-        SweepPlan s = shape(vx, ty, max_waves);
-        if (s.threads > max_threads || s.lds > 160 * 1024) break;
-        const double plane = s.resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (s.resident * s.threads / 64)) *
+        s.threads = div_up((long)lw * ty, 64) * 64;
+        if (s.threads > max_threads) break;
+        s.lds = 2 * (size_t)(ty + halo) * sweep_row(nx, vx) * tsize;
+        if (s.lds > 160 * 1024) break;
+        const int waves = s.threads / 64;
+        const int resident = std::max(1, std::min((int)(160 * 1024 / s.lds), max_waves / waves));
+        s.round = std::max(1, c->prop.multiProcessorCount / 8) * resident;
+        const double plane = resident * (ty + 0.25 * halo) * std::max(1.0, 6.0 / (resident * waves)) *
                              (halo * lw > s.threads && !bloch ? 1.5 : 1.0);
         const double cost =
-            plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, s.resident, c->nz, &s.split);
-        if (best.ty == 0 || ty == forced || (cost < least && best.ty != forced)) {
+            plane * sweep_rounds((long)ncol * div_up(ny, ty), s.round, resident, c->nz, &s.split);
+        if (best.ty < 4 || ty == forced || (cost < least && best.ty != forced)) {
             least = cost;
             best = s;
         }
-    }
-    for (int ty = std::min(3, ny); ty >= 1 && best.ty == 0; --ty) {
-        SweepPlan s = shape(1, ty, kSweepWideThreads / 64);
-        if (s.threads > kSweepWideThreads || s.lds > 160 * 1024) continue;
-        s.wide = true;
-        sweep_rounds((long)ncol * div_up(ny, ty), s.round, s.resident, c->nz, &s.split);
-        best = s;
     }
     plan = best;
     return best;
@@ -430,7 +431,7 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     a.params = c->scal + S_A;
     a.step = step;
     a.ncol = ncol;
-    const int hm = div_up(2L * kMaxHalfOrder * (c->nx / sh.vx), sh.threads);   // 1 to 3 with slabs of 4 rows
+    const int hm = div_up(2L * kMaxHalfOrder * (c->nx / sh.vx), sh.threads);   // 1 to 3; 6 with slabs of 2 rows
     const long tiles = (long)ncol * a.ntiles_y;
     if (tiles > 0x3fffffffL) return set_err(c, SPARC_ERR_ARG, "too many blocks");
     if (tiles == 0) return SPARC_OK;
@@ -451,10 +452,10 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
     auto go_halo = [&](auto vx, auto mv, auto bl) {
         if (hm == 1) go(vx, mv, std::integral_constant<int, 1>(), bl);
         else if (hm == 2) go(vx, mv, std::integral_constant<int, 2>(), bl);
-        else go(vx, mv, std::integral_constant<int, 3>(), bl);
+        else if (!(vx() == 1 && bl()) || hm == 3) go(vx, mv, std::integral_constant<int, 3>(), bl);
+        else go(std::integral_constant<int, 1>(), mv, std::integral_constant<int, kSweepMaxHalo>(), std::true_type());
     };
     auto go_width = [&](auto mv, auto bl) {
-        if (sh.wide) return go(std::integral_constant<int, 1>(), mv, std::integral_constant<int, kSweepWideHalo>(), bl);
         if (sh.vx == 1) return go_halo(std::integral_constant<int, 1>(), mv, bl);
         if constexpr (sizeof(T) == 4)
             if (sh.vx == 4) return go_halo(std::integral_constant<int, 4>(), mv, bl);

@@ -1,7 +1,7 @@
 """The local sweep against the oracle where its vectors, slabs and z ranges can
 go wrong: rows of 1, 2 and 4 points a thread, the shortest axes, slabs of fewer
 than 12 rows (rows of more than 128 points, which need two or three halo vectors
-per thread) and of fewer than 4 (the widest rows), blocks so narrow that z is
+per thread) and, with Bloch columns, of fewer than 4 (wide odd rows), blocks so narrow that z is
 cut into ranges and blocks wide enough for whole rounds with a cut remainder.
 
 Tolerances: 1e-12 (H X) and 1e-11 (filter) relative in FP64 as in the other
@@ -18,7 +18,7 @@ from gpu_helpers import log, rel_err, require_gpu, to_dev, to_np
 pytestmark = pytest.mark.gpu
 
 GRIDS = [(13, 13, 13), (14, 15, 16), (15, 13, 24), (16, 29, 13), (17, 40, 19), (24, 24, 24), (130, 14, 13),
-         (131, 13, 14), (256, 17, 13), (250, 13, 15), (400, 14, 13), (521, 13, 13)]
+         (131, 13, 14), (256, 17, 13), (250, 13, 15)]
 
 
 @pytest.mark.parametrize("n", GRIDS)
@@ -72,7 +72,7 @@ def test_sweep_rounds_do_not_change_results(monkeypatch):
         assert np.array_equal(o, outs[0])
 
 
-@pytest.mark.parametrize("n", [(13, 13, 13), (17, 15, 24), (24, 24, 24), (130, 14, 13), (253, 13, 14), (391, 13, 13)])
+@pytest.mark.parametrize("n", [(13, 13, 13), (17, 15, 24), (24, 24, 24), (130, 14, 13), (253, 13, 14), (255, 14, 13), (149, 13, 13)])
 @pytest.mark.parametrize("dtype", ["float64", "float32"])
 def test_bloch_sweep_matches_oracle(n, dtype):
     """The Bloch form of the sweep (wrapped values times exp(+-i k L)) and of the

@@ -385,13 +385,24 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
             // branch, so that those in flight can be counted
             load(v, (b + RING) % NB, b + RING < NB ? z : min(z + 1, U.ze - 1));
             const C* cb = chi + 16 * b * RS;
+            // with both products the operands of the second are read along with
+            // the first's, so that only one wait on LDS is left per group
+            // (72^3 x 260: FP32 590 -> 550 us a degree, FP64 within 1%)
+            C pr[NG][4];
             if (AP) {
                 const C* A = cb + P::row(li) * RS + 4 * g;
 #pragma unroll
                 for (int G = 0; G < NG; ++G)
                     if ((gb >> G) & 1) {
+                        C w[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc = Mfma<C>::run(A[16 * G + j], d[G][j], acc);
+                        for (int j = 0; j < 4; ++j) w[j] = A[16 * G + j];
+                        if (PR) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) pr[G][r] = cb[P::of(g, r) * RS + 16 * G + P::perm(li)];
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc = Mfma<C>::run(w[j], d[G][j], acc);
                     }
                 T* yp = yc + (long)z * a.nxy + pb0[b];
                 const T o[4] = {(T)acc[0], (T)acc[1], (T)acc[2], (T)acc[3]};
@@ -409,7 +420,8 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
                     if ((gb >> G) & 1) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            sum[G].p = Mfma<C>::run(cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r], sum[G].p);
+                            sum[G].p = Mfma<C>::run(AP ? pr[G][r] : cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r],
+                                                    sum[G].p);
                     }
             }
         }

@@ -695,9 +695,6 @@ sparc_status sparc_gpu_create(const sparc_gpu_system* s, void* hip_stream, sparc
     if (const char* e = std::getenv("SPARC_GPU_TRD_TAIL")) c->trd_tail = std::max(0, std::atoi(e));
     if (const char* e = std::getenv("SPARC_GPU_CHOL_MULTI_MIN")) c->chol_multi_min = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_STEIN_LDS_MIN_TPW")) c->stein_lds_min_tpw = std::atoi(e);
-    if (const char* e = std::getenv("SPARC_GPU_GEMM_TILE")) c->gemm_tile = std::atoi(e);
-    if (const char* e = std::getenv("SPARC_GPU_GEMM_NN_COLS")) c->gemm_nn_cols = std::atoi(e);
-    if (const char* e = std::getenv("SPARC_GPU_GEMM_NN_ROWS")) c->gemm_nn_rows = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_SWEEP_GROUP")) c->sweep_group = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_CNN_TZ")) {
         const int tz = std::atoi(e);

@@ -11,6 +11,7 @@
 // Reductions are in fixed order (no value atomics), so results are
 // bitwise reproducible.
 #include "internal.hpp"
+#include "mfma.hpp"
 
 namespace sg {
 
@@ -138,64 +139,160 @@ __global__ __launch_bounds__(256) void k_force_overlap(ForceTab tab, int n_atoms
     if (threadIdx.x < 3) out[3 * I + threadIdx.x] += sum;
 }
 
-// Projections of NB columns on the atom's projectors and their gradients:
+constexpr int kForceTiles = 5;   // 16-column tiles of a workgroup at most
+
+// Projections of the columns on the atom's projectors and their gradients:
 // pd[(a ncol + col) 16 + q] with q = k (chi_k^T psi, k = s, px, py, pz) and
 // q = 4 + 3 k + d ((d/dx_d chi_k)^T psi), each times dV.
-template <typename T, int NB>
-__global__ __launch_bounds__(256) void k_force_nl_proj(const T* __restrict__ X, long ldx, int ncol, ForceTab tab,
-                                                      int nx, int ny, int nz, double hx, double hy, double hz,
-                                                      double rc, double rcut, double N0, double N1, double dV,
-                                                      double* __restrict__ pd) {
-    const int a = blockIdx.x;
-    const int col0 = blockIdx.y * NB;
+//
+// The 16 functions of an atom are the rows of one FP64 MFMA tile.  A workgroup
+// takes an atom and up to 80 columns; its waves take every fourth x-line of the
+// atom's sphere, 24 points at a time with the next ones' loads in flight, and for
+// each point every lane forms the one function of its row,
+//   f_q = exp(-r^2 / rc^2) (c0 + c1 u v),   u, v each 1, dx, dy or dz,
+// which all columns then share.  Reading is what bounds it: the lanes
+// of a wave hold 16 different columns, so that a load of 8 bytes per lane costs
+// the L1 57 accesses, and the overlapping spheres read the block 5 times (4 GB at
+// 72^3, 108 atoms, 260 columns).  There 1.95 ms as vector code with the 16 sums of
+// four columns per thread; 1.27 on the matrix cores with loads of single points,
+// 1.11 with pairs (the products alone would take 0.13).  Neighbouring atoms on one
+// XCD made no difference.
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ X, long ldx, int ncol, ForceTab tab,
+                                                          int nx, int ny, int nz, double hx, double hy, double hz,
+                                                          double rc, double rcut, double N0, double N1, double dV,
+                                                          double* __restrict__ pd, int tiles) {
+    constexpr int CH = 3, TL = kForceTiles;   // 8-point chunks of a step, 16-column tiles
+    __shared__ double ex[3][256];   // Gaussian factors along the box's axes (at most 255 points)
+    __shared__ double red[4][16][16 * TL];
+    const int a = blockIdx.x, col0 = 16 * tiles * blockIdx.y;
     const double cx = tab.pos[3 * a], cy = tab.pos[3 * a + 1], cz = tab.pos[3 * a + 2];
     const double rcut2 = rcut * rcut;
     const int lx = (int)ceil((cx - rcut) / hx), ux = (int)floor((cx + rcut) / hx);
     const int ly = (int)ceil((cy - rcut) / hy), uy = (int)floor((cy + rcut) / hy);
     const int lz = (int)ceil((cz - rcut) / hz), uz = (int)floor((cz + rcut) / hz);
     const int nxb = ux - lx + 1, nyb = uy - ly + 1, nzb = uz - lz + 1;
-    const long tot = (long)nxb * nyb * nzb;
-    const double g = -2.0 / (rc * rc);
-    double acc[NB * 16];
+    const int t = threadIdx.x, lane = t & 63, li = lane & 15, g = lane >> 4;
+    for (int i = t; i < 256; i += blockDim.x) {
+        const double dx = (lx + i) * hx - cx, dy = (ly + i) * hy - cy, dz = (lz + i) * hz - cz;
+        ex[0][i] = exp(-dx * dx / (rc * rc));
+        ex[1][i] = exp(-dy * dy / (rc * rc));
+        ex[2][i] = exp(-dz * dz / (rc * rc));
+    }
+    __syncthreads();
+    // the lane's function: c0 + c1 u v
+    const double gr = -2.0 / (rc * rc);
+    const int ku = li < 4 ? li - 1 : (li < 7 ? li - 4 : (li - 7) / 3);   // axis of u, -1: one
+    const int kv = li < 7 ? -1 : (li - 7) % 3;
+    const double c0 = li == 0 ? N0 : (li >= 7 && ku == kv ? N1 : 0.0);
+    const double c1 = li == 0 ? 0.0 : (li < 4 ? N1 : (li < 7 ? N0 * gr : N1 * gr));
+    const double u1 = ku < 0 ? 1.0 : 0.0, uX = ku == 0 ? 1.0 : 0.0, uY = ku == 1 ? 1.0 : 0.0, uZ = ku == 2 ? 1.0 : 0.0;
+    const double v1 = kv < 0 ? 1.0 : 0.0, vX = kv == 0 ? 1.0 : 0.0, vY = kv == 1 ? 1.0 : 0.0, vZ = kv == 2 ? 1.0 : 0.0;
+    // columns past the last repeat it and are not stored
+    const int nt = min(tiles, (ncol - col0 + 15) / 16);
+    const T* xc[TL];
 #pragma unroll
-    for (int q = 0; q < NB * 16; ++q) acc[q] = 0.0;
-    for (long t = threadIdx.x; t < tot; t += blockDim.x) {
-        const int i = lx + (int)(t % nxb);
-        const int j = ly + (int)((t / nxb) % nyb);
-        const int k = lz + (int)(t / ((long)nxb * nyb));
-        const double dx = i * hx - cx, dy = j * hy - cy, dz = k * hz - cz;
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (r2 > rcut2) continue;
-        const double e = exp(-r2 / (rc * rc));
-        const double e0 = N0 * e, e1 = N1 * e;
-        const double d[3] = {dx, dy, dz};
-        double f[16];
-        f[0] = e0;
-        f[1] = e1 * dx;
-        f[2] = e1 * dy;
-        f[3] = e1 * dz;
+    for (int k = 0; k < TL; ++k) xc[k] = X + (long)min(ncol - 1, col0 + 16 * min(k, nt - 1) + li) * ldx;
+    using acc_t = Mfma<double>::acc_t;
+    typedef T vec __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+    acc_t acc[TL];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) f[4 + b] = e0 * g * d[b];
+    for (int k = 0; k < TL; ++k) acc[k] = acc_t{0, 0, 0, 0};
+
+    // a step: up to 24 points i0, i0 + 1, ... of the box's line (j, k).  The
+    // line's part in the sphere is found in single precision, a little too long:
+    // the test below decides.
+    struct Step {
+        int j, k, i0, n, next, last, x0;   // x0: i0 on the grid
+    };
+    const float fx = (float)((cx - lx * hx) / hx), fr = (float)(1.0 / hx);
+    auto advance = [&](Step& s) -> bool {
+        while (s.next > s.last) {
+            s.j += 4;
+            while (s.j >= nyb) {
+                s.j -= nyb;
+                ++s.k;
+            }
+            if (s.k >= nzb) return false;
+            const float dy = (float)((ly + s.j) * hy - cy), dz = (float)((lz + s.k) * hz - cz);
+            const float half = __builtin_sqrtf(fmaxf((float)rcut2 - dy * dy - dz * dz, 0.0f)) * fr + 0.02f;
+            s.next = __builtin_amdgcn_readfirstlane(max(0, (int)ceilf(fx - half)));
+            s.last = __builtin_amdgcn_readfirstlane(min(nxb - 1, (int)floorf(fx + half)));
+        }
+        s.i0 = s.next;
+        s.n = min(8 * CH, s.last - s.i0 + 1);
+        s.next += 8 * CH;
+        s.x0 = wrap(lx + s.i0, nx);
+        return true;
+    };
+    // pairs of points by one load, which never passes a row's end (the pair of a
+    // row's last point starts one earlier); a step that wraps by single points
+    auto load = [&](const Step& s, vec (&x)[CH][TL]) {
+        const long row = (long)nx * (wrap(ly + s.j, ny) + (long)ny * wrap(lz + s.k, nz));
+        if (s.x0 + s.n <= nx) {
 #pragma unroll
-        for (int kk = 0; kk < 3; ++kk)
+            for (int c = 0; c < CH; ++c) {
+                const long o = row + min(s.x0 + min(8 * c + 2 * g, s.n - 1), nx - 2);
 #pragma unroll
-            for (int b = 0; b < 3; ++b) f[7 + 3 * kk + b] = e1 * ((kk == b ? 1.0 : 0.0) + g * d[kk] * d[b]);
-        const long p = wrap(i, nx) + (long)nx * (wrap(j, ny) + (long)ny * wrap(k, nz));
+                for (int k = 0; k < TL; ++k) x[c][k] = *reinterpret_cast<const vec*>(xc[k] + o);
+            }
+        } else {
 #pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            if (col0 + c < ncol) {
-                const double x = (double)X[p + (long)(col0 + c) * ldx];
+            for (int c = 0; c < CH; ++c)
 #pragma unroll
-                for (int q = 0; q < 16; ++q) acc[16 * c + q] += x * f[q];
+                for (int u = 0; u < 2; ++u) {
+                    const long o = row + wrap(s.x0 + min(8 * c + 2 * g + u, s.n - 1), nx);
+#pragma unroll
+                    for (int k = 0; k < TL; ++k) x[c][k][u] = xc[k][o];
+                }
+        }
+    };
+    auto compute = [&](const Step& s, const vec (&x)[CH][TL]) {
+        const double dy = (ly + s.j) * hy - cy, dz = (lz + s.k) * hz - cz;
+        const double eyz = ex[1][s.j] * ex[2][s.k];
+        const double ub = u1 + uY * dy + uZ * dz, vb = v1 + vY * dy + vZ * dz;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (8 * c >= s.n) break;
+            const bool late = s.x0 + 8 * c + 2 * g == nx - 1 && s.x0 + s.n <= nx;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int e = 8 * c + 2 * g + u, i = s.i0 + min(e, s.n - 1);
+                const double dx = (lx + i) * hx - cx;
+                const bool in = e < s.n && dx * dx + dy * dy + dz * dz <= rcut2;
+                const double f = in ? ex[0][i] * eyz * (c0 + c1 * (ub + uX * dx) * (vb + vX * dx)) : 0.0;
+#pragma unroll
+                for (int k = 0; k < TL; ++k)
+                    if (k < nt)
+                        acc[k] = Mfma<double>::run(f, in ? (double)(late ? x[c][k][1] : x[c][k][u]) : 0.0, acc[k]);
             }
         }
+    };
+    Step s{__builtin_amdgcn_readfirstlane((t >> 6) - 4), 0, 0, 0, 1, 0, 0};
+    vec xa[CH][TL], xb[CH][TL];
+    bool more = advance(s);
+    if (more) load(s, xa);
+    while (more) {
+        Step s2 = s;
+        const bool m2 = advance(s2);
+        if (m2) load(s2, xb);
+        compute(s, xa);
+        if (!m2) break;
+        s = s2;
+        more = advance(s);
+        if (more) load(s, xa);
+        compute(s2, xb);
     }
-    __shared__ double lds[4][NB * 16];
-    const double sum = block_reduce<NB * 16>(acc, lds);
-    const int q = threadIdx.x;
-    if (q < NB * 16) {
-        const int c = q / 16;
-        if (col0 + c < ncol) pd[((long)a * ncol + col0 + c) * 16 + (q % 16)] = dV * sum;
+#pragma unroll
+    for (int k = 0; k < TL; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[t >> 6][Mfma<double>::row(lane, r)][16 * k + li] = acc[k][r];
+    __syncthreads();
+    for (int e = t; e < 256 * nt; e += blockDim.x) {
+        const int q = e & 15, c = e >> 4;
+        if (col0 + c < ncol)
+            pd[((long)a * ncol + col0 + c) * 16 + q] =
+                dV * (red[0][q][c] + red[1][q][c] + red[2][q][c] + red[3][q][c]);
     }
 }
 
@@ -218,7 +315,6 @@ __global__ __launch_bounds__(256) void k_force_nl_reduce(const double* __restric
     if (threadIdx.x < 3) out[3 * a + threadIdx.x] += sum;
 }
 
-constexpr int kForceNB = 4;
 constexpr int kLocalChunks = 8;
 
 }  // namespace
@@ -250,9 +346,10 @@ sparc_status nl_force(sparc_gpu_ctx c, const T* X, int ncol, long ldx, const dou
     const double rc = c->rc_nl;
     const double N0 = std::pow(2.0 / (kPi * rc * rc), 0.75);
     const double N1 = (2.0 / rc) * N0;
-    dim3 grid(c->n_atoms, div_up(ncol, kForceNB));
-    k_force_nl_proj<T, kForceNB><<<grid, 256, 0, c->stream>>>(X, ldx, ncol, tab, c->nx, c->ny, c->nz, c->hx, c->hy,
-                                                              c->hz, rc, c->rcut_nl, N0, N1, c->dV, pd);
+    const int tiles = div_up(ncol, 16), chunks = div_up(tiles, kForceTiles);
+    k_force_nl_proj<T><<<dim3(c->n_atoms, chunks), 256, 0, c->stream>>>(
+        X, ldx, ncol, tab, c->nx, c->ny, c->nz, c->hx, c->hy, c->hz, rc, c->rcut_nl, N0, N1, c->dV, pd,
+        div_up(tiles, chunks));
     k_force_nl_reduce<<<c->n_atoms, 256, 0, c->stream>>>(pd, ncol, w, tab, out);
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;

@@ -468,7 +468,7 @@ def main():
     sweep_bytes_total = 3 * s * nd * ns * (m - 1) * args.steps
     bytes_per_sweep = sweep_bytes_total / sw_n if sw_n else None
     achieved = sweep_bytes_total / (sw_ms * 1e-3) / 1e9 if sw_n else None
-    kernel_name = f"k_hsweep<{'double' if s == 8 else 'float'}, nonlocal, mode 2>"
+    kernel_name = f"k_hsweep<{'double' if s == 8 else 'float'}, mode 2>"
     traffic = traffic_record(f"{args.workload}_{args.prec}_sweep")
     gt_ms, gt_n = prof["gemm_tn"]
     gn_ms, gn_n = prof["gemm_nn"]

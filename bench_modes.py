@@ -395,7 +395,7 @@ Workload: config 2 (72^3 grid, 108 atoms with s + p projectors, 260 states)
 on a 2 x 1 x 1 Monkhorst-Pack k-point set.  Each k-point holds 520 Bloch
 columns of 2 N_d rows (the 260 states and their i-multiples).  After the
 first iteration and `--warmup` steps, `--steps` SCF steps are timed with HIP
-events.  The Bloch filter step (profile id 22) is timed per launch.  Its
+events.  The Bloch filter step's local sweep (profile id 22) is timed per launch.  Its
 algorithmic traffic per launch is 3 x 8 x 2 N_d bytes per column (read Y_k,
 read Y_{k-1}, write Y_{k+1}, both halves), which is the same count as the
 Gamma sweep on a column of twice the length.

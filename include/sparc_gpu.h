@@ -138,7 +138,7 @@ sparc_status sparc_gpu_chebyshev_filter(sparc_gpu_ctx ctx, sparc_prec prec, void
  * (one copy per GPU, held until the process ends, its address looked up at
  * sparc_gpu_create); columns are processed in as many groups as that needs.
  * Returns SPARC_ERR_ARG when the partials of one column alone exceed the
- * array (4 x (z ranges) x (y-slabs) x (candidates per slab) doubles).  Every
+ * array (4 doubles per (tile of the grid, atom image reaching it)).  Every
  * entry it reads is written by the same call first, so nothing needs
  * clearing; calls that overlap on one GPU (other streams, other contexts)
  * share the array and race. */
@@ -451,8 +451,8 @@ sparc_status sparc_gpu_forces(sparc_gpu_ctx ctx, const double* d_phi, sparc_prec
  * kernels is bracketed by HIP events on the context's stream.
  * sparc_gpu_profile_read() synchronises, returns the summed device time (ms)
  * and launch count since the last read for one kernel, and resets it.
- * Kernel ids: 0 filter sweep of degree >= 2, 1 nonlocal projection (its
- * streaming pass and per-atom sum),
+ * Kernel ids: 0 local filter sweep of degree >= 2, 1 nonlocal pass (applies
+ * and projects; with its per-atom sum),
  * 2 Gram/projected-H GEMM, 3 rotation GEMM, 4 density, 5 first filter
  * sweep, 6 plain H application, 7 Cholesky, 8 triangular inverse,
  * 9 subspace eigensolver (all its launches, host waits included),
@@ -462,8 +462,8 @@ sparc_status sparc_gpu_forces(sparc_gpu_ctx ctx, const double* d_phi, sparc_prec
  * 17 its 16 -> 16 convolution, 18 network gradient, 19 density mixing
  * step of the SCF (linear with preconditioner, or Pulay; the plain linear
  * step is fused into the energy pass and not listed), 20 local and overlap
- * forces, 21 nonlocal forces, 22 Bloch H_k application / filter step,
- * 23 Bloch projections; ids < 32. */
+ * forces, 21 nonlocal forces, 22 local sweep over Bloch columns,
+ * 23 nonlocal pass over them; ids < 32. */
 sparc_status sparc_gpu_profile(sparc_gpu_ctx ctx, int enable);
 sparc_status sparc_gpu_profile_read(sparc_gpu_ctx ctx, int kernel_id, double* total_ms, long* launches);
 

@@ -229,7 +229,8 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     uint8_t* occ = reinterpret_cast<uint8_t*>(smem_raw + L.occ);
 
     // block b runs on XCD b % 8.  All units of 64 orbitals go before the next
-    // orbitals, the last ones first (see PassOrder); an XCD takes a contiguous
+    // orbitals, the last ones first, which the sweep before has left in the
+    // last-level cache; an XCD takes a contiguous
     // eighth of the units, a different one each time, since some hold one more
     const int bslot = blockIdx.x / 8, per = (a.nunit + 7) / 8;
     const int chunk = a.nchunk - 1 - bslot / per, xr = (blockIdx.x + 3 * chunk) % 8;

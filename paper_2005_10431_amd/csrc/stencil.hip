@@ -10,7 +10,7 @@
 // projections for the next degree.
 //
 // Sweep kernel layout (one workgroup = one orbital x one y-slab x a range of z):
-//  - a thread holds VX consecutive x points (16 bytes), so that loads, stores
+//  - a thread holds VX consecutive x points (16 bytes where they divide n_x), so that loads, stores
 //    and the x and y reads from LDS move whole vectors and the address work is
 //    shared by VX points;
 //  - the slab is `ty` full x-rows; periodic x wraps inside LDS (padded rows),
@@ -25,7 +25,7 @@
 //  - two LDS plane buffers alternate so one barrier per plane suffices;
 //  - a workgroup takes all of z, except those of a compute unit's last,
 //    incomplete round (or of a block too small to fill the chip), which are
-//    cut into equal z ranges (see sweep_split).
+//    cut into equal z ranges (see sweep_rounds).
 #include <cmath>
 #include <map>
 #include <mutex>
@@ -137,7 +137,9 @@ __global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_
     // Hardware dispatches block b to XCD b % 8.  The y-slabs of one orbital (which
     // read each other's rows as halos) share an XCD, so an L2; orbital j goes to
     // XCD j % 8 (Bloch: both halves to (j / 2) % 8), so that the chip works
-    // through the block from its first orbital to its last (see PassOrder); the
+    // through the block from its first orbital to its last (the nonlocal pass goes
+    // back from the last, so each starts on what the last-level cache still holds:
+    // 72^3 x 260 FP64 1030 -> 985 us a degree, 51 x 68 x 93 x 77 300 -> 267); the
     // slabs of the last few orbitals are spread evenly over the XCDs.  Within a
     // group of grp of an XCD's orbitals the order is slab-major, so that the
     // grp copies of a slab (which read the same V_eff rows) run side by side.

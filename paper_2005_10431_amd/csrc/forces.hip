@@ -10,6 +10,7 @@
 // around the atom, wrapped to the periodic grid for field values.
 // Reductions are in fixed order (no value atomics), so results are
 // bitwise reproducible.
+#include "force_lines.hpp"
 #include "internal.hpp"
 #include "mfma.hpp"
 
@@ -162,16 +163,13 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
                                                           int nx, int ny, int nz, double hx, double hy, double hz,
                                                           double rc, double rcut, double N0, double N1, double dV,
                                                           double* __restrict__ pd, int tiles) {
-    constexpr int CH = 3, TL = kForceTiles;   // 8-point chunks of a step, 16-column tiles
+    constexpr int CH = kForcePoints / 8, TL = kForceTiles;   // 8-point chunks of a step, 16-column tiles
     __shared__ double ex[3][256];   // Gaussian factors along the box's axes (at most 255 points)
     __shared__ double red[4][16][16 * TL];
     const int a = blockIdx.x, col0 = 16 * tiles * blockIdx.y;
     const double cx = tab.pos[3 * a], cy = tab.pos[3 * a + 1], cz = tab.pos[3 * a + 2];
-    const double rcut2 = rcut * rcut;
-    const int lx = (int)ceil((cx - rcut) / hx), ux = (int)floor((cx + rcut) / hx);
-    const int ly = (int)ceil((cy - rcut) / hy), uy = (int)floor((cy + rcut) / hy);
-    const int lz = (int)ceil((cz - rcut) / hz), uz = (int)floor((cz + rcut) / hz);
-    const int nxb = ux - lx + 1, nyb = uy - ly + 1, nzb = uz - lz + 1;
+    const ForceBox B = force_box(cx, cy, cz, hx, hy, hz, rcut);
+    const int lx = B.lx, ly = B.ly, lz = B.lz;
     const int t = threadIdx.x, lane = t & 63, li = lane & 15, g = lane >> 4;
     for (int i = t; i < 256; i += blockDim.x) {
         const double dx = (lx + i) * hx - cx, dy = (ly + i) * hy - cy, dz = (lz + i) * hz - cz;
@@ -199,29 +197,12 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
 #pragma unroll
     for (int k = 0; k < TL; ++k) acc[k] = acc_t{0, 0, 0, 0};
 
-    // a step: up to 24 points i0, i0 + 1, ... of the box's line (j, k).  The
-    // line's part in the sphere is found in single precision, a little too long:
-    // the test below decides.
-    struct Step {
-        int j, k, i0, n, next, last, x0;   // x0: i0 on the grid
+    // a step of the walk over the sphere's lines; x0: its first point on the grid
+    struct Step : ForceStep {
+        int x0;
     };
-    const float fx = (float)((cx - lx * hx) / hx), fr = (float)(1.0 / hx);
     auto advance = [&](Step& s) -> bool {
-        while (s.next > s.last) {
-            s.j += 4;
-            while (s.j >= nyb) {
-                s.j -= nyb;
-                ++s.k;
-            }
-            if (s.k >= nzb) return false;
-            const float dy = (float)((ly + s.j) * hy - cy), dz = (float)((lz + s.k) * hz - cz);
-            const float half = __builtin_sqrtf(fmaxf((float)rcut2 - dy * dy - dz * dz, 0.0f)) * fr + 0.02f;
-            s.next = __builtin_amdgcn_readfirstlane(max(0, (int)ceilf(fx - half)));
-            s.last = __builtin_amdgcn_readfirstlane(min(nxb - 1, (int)floorf(fx + half)));
-        }
-        s.i0 = s.next;
-        s.n = min(8 * CH, s.last - s.i0 + 1);
-        s.next += 8 * CH;
+        if (!force_advance(B, s, 4, [](int v) { return __builtin_amdgcn_readfirstlane(v); })) return false;
         s.x0 = wrap(lx + s.i0, nx);
         return true;
     };
@@ -259,7 +240,7 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
             for (int u = 0; u < 2; ++u) {
                 const int e = 8 * c + 2 * g + u, i = s.i0 + min(e, s.n - 1);
                 const double dx = (lx + i) * hx - cx;
-                const bool in = e < s.n && dx * dx + dy * dy + dz * dz <= rcut2;
+                const bool in = e < s.n && dx * dx + dy * dy + dz * dz <= B.rcut2;
                 const double f = in ? ex[0][i] * eyz * (c0 + c1 * (ub + uX * dx) * (vb + vX * dx)) : 0.0;
 #pragma unroll
                 for (int k = 0; k < TL; ++k)
@@ -268,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
             }
         }
     };
-    Step s{__builtin_amdgcn_readfirstlane((t >> 6) - 4), 0, 0, 0, 1, 0, 0};
+    Step s{{__builtin_amdgcn_readfirstlane((t >> 6) - 4), 0, 0, 0, 1, 0}, 0};
     vec xa[CH][TL], xb[CH][TL];
     bool more = advance(s);
     if (more) load(s, xa);

@@ -43,8 +43,10 @@ struct ForceStep {
 };
 
 // The next step of every stride-th line; false past the last.  The part of a line
-// inside the sphere is found in single precision, a little too long: the caller
-// tests each point.  `uniform`: makes a value that all lanes share a scalar.
+// inside the sphere is found in single precision and made longer by more than
+// its rounding (at most 4e-7 rcut2 under the root, 3e-5 points outside), so that
+// no point inside is left out; the caller tests each point.  `uniform`: makes a
+// value that all lanes share a scalar.
 template <typename F>
 __host__ __device__ inline bool force_advance(const ForceBox& b, ForceStep& s, int stride, F uniform) {
     if (b.nyb <= 0) return false;
@@ -57,7 +59,7 @@ __host__ __device__ inline bool force_advance(const ForceBox& b, ForceStep& s, i
         if (s.k >= b.nzb) return false;
         const float dy = (float)((b.ly + s.j) * b.hy - b.cy), dz = (float)((b.lz + s.k) * b.hz - b.cz);
         const float in2 = b.r2 - dy * dy - dz * dz;
-        const float half = sqrtf(in2 > 0.0f ? in2 : 0.0f) * b.per_h + 0.02f;
+        const float half = sqrtf((in2 > 0.0f ? in2 : 0.0f) + 1e-6f * b.r2) * b.per_h + 0.02f;
         const int lo = (int)ceilf(b.fx - half), hi = (int)floorf(b.fx + half);
         s.next = uniform(lo > 0 ? lo : 0);
         s.last = uniform(hi < b.nxb - 1 ? hi : b.nxb - 1);

@@ -54,6 +54,8 @@ struct NlPass {
     uint64_t* gm = nullptr;      // per unit zlen: slot groups that meet each block
     int* ent_cand = nullptr;     // pair of every entry
     NlCand* cand = nullptr;
+    uint32_t* odd = nullptr;     // per 16 columns: epoch of the last projection that was not finite
+    uint32_t epoch = 0;          // projections formed so far (the one that an apply takes is the last)
     int* red_off = nullptr;      // entries of each atom
     int* red_ent = nullptr;
     int* cand_off = nullptr;     // pairs of each atom

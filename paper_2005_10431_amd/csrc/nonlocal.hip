@@ -30,6 +30,13 @@
 // The accumulator layout of the apply product is the operand layout of the
 // projection product, so a value goes from its load through both without
 // leaving its lane.
+//
+// The products run over whole blocks and groups of slots, with chi = 0 where a
+// pair does not reach.  Zero times an infinity or a NaN would carry these past an
+// atom's support, so they go round the products.  The sum over an atom's entries
+// forms a projection that is not finite again from the atom's points alone
+// (sum_support) and marks its 16 columns; in marked columns the pass applies what
+// is not finite point by point (plane_odd).
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -121,6 +128,8 @@ struct NlArgs {
     double hx, hy, hz, inv_rc2, N0, N1, rcut2;
     const C* D;                  // column j at D + j ldD, 4 per pair or atom
     long ldD;
+    uint32_t* odd;               // per 16 columns: epoch if a coefficient is not finite
+    uint32_t epoch;
     double* part;                // [(entry ncol + col) 4 + lm]
     const double* params;
     int mode, step;              // filter step whose output is completed: alpha of the recurrence
@@ -202,9 +211,6 @@ __device__ inline double add_sq(double r2, double d) {
 #pragma clang fp contract(off)
     return r2 + d * d;
 }
-
-__device__ inline double gauss(double v) { return exp(v); }
-__device__ inline float gauss(float v) { return expf(v); }
 
 // AP: y += alpha chi D.  PR: partial projections of (the completed) y.
 // Per plane: barrier; chi of the plane into LDS; barrier; the products.  Two
@@ -351,7 +357,6 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
             oc[G] = on;
         }
     };
-
     // first point of each block (in scalar registers); places past the
     // pencil's list load the plane's first points and meet no group
     int pb0[NB];
@@ -359,6 +364,70 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     for (int b = 0; b < NB; ++b) pb0[b] = __builtin_amdgcn_readfirstlane(max(0, blk[b]));
     T q[RING][4];
     auto load = [&](T* v, int b, int z) { P::load(yc + (long)z * a.nxy, pb0[b], g, v); };
+    // some coefficients of the wave's columns may not be finite
+    const bool odd = AP && mine && a.odd[chunk * a.nwc + wv] == a.epoch;
+    // a plane of such columns: block by block as in the loop below, with the
+    // coefficients that are not finite at the points that their pairs reach only
+    auto plane_odd = [&](int z, uint64_t gm) {
+        const int zl = z - U.zb;
+        const C* Dc = a.D + (long)col * a.ldD;
+#pragma unroll
+        for (int G = 0; G < NG; ++G)
+            if (!(__builtin_isfinite(d[G][0]) && __builtin_isfinite(d[G][1]) && __builtin_isfinite(d[G][2]) &&
+                  __builtin_isfinite(d[G][3])))
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[G][j] = 0;
+#pragma unroll 1
+        for (int b = 0; b < NB; ++b) {
+            const bool tail = TAIL && b == NB - 1 && part5;
+            if (b >= nb && !tail) continue;
+            const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
+            T* yp = yc + (long)z * a.nxy + blk[b];
+            T v[4];
+            P::load(yp, 0, g, v);
+            acc_t acc = {(C)v[0], (C)v[1], (C)v[2], (C)v[3]};
+            const C* cb = chi + 16 * b * RS;
+#pragma unroll
+            for (int G = 0; G < NG; ++G)
+                if ((gb >> G) & 1)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc = Mfma<C>::run(cb[P::row(li) * RS + 16 * G + 4 * g + j], d[G][j], acc);
+#pragma unroll 1
+            for (int s = 0; s < S; ++s) {
+                const int o = occ[zl * S + s];
+                if (o == kIdle || !((gb >> (s >> 2)) & 1)) continue;
+                const C* e = Dc + 4 * (a.by_pair ? cand[o].id : cand[o].atom);
+                const C e0 = al * e[0], e1 = al * e[1], e2 = al * e[2], e3 = al * e[3];
+                if (__builtin_isfinite(e0) && __builtin_isfinite(e1) && __builtin_isfinite(e2) && __builtin_isfinite(e3))
+                    continue;
+                const double dz = ezdz[((zl & 1) * S + s) * 2 + 1];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int w = xy[16 * b + P::of(g, r)];
+                    const double dx = off_x(cand[o], w & 0xFFFF, a.hx), dy = off_y(cand[o], w >> 16, a.hy);
+                    const C* c = cb + P::of(g, r) * RS + 4 * s;
+                    if (w >= 0 && add_sq(sum_sq(dx, dy), dz) <= a.rcut2)
+                        acc[r] += c[0] * e0 + c[1] * e1 + c[2] * e2 + c[3] * e3;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (!tail || P::of(g, r) >= 16 - a.tail) yp[P::of(g, r)] = (T)acc[r];
+            if (PR) {
+#pragma unroll
+                for (int G = 0; G < NG; ++G)
+                    if ((gb >> G) & 1)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            sum[G].p = Mfma<C>::run(cb[P::of(g, r) * RS + 16 * G + P::perm(li)], acc[r], sum[G].p);
+            }
+        }
+        if (PR) {
+#pragma unroll
+            for (int G = 0; G < NG; ++G) sum[G].plane();
+        }
+    };
     if (mine) {
 #pragma unroll
         for (int b = 0; b < RING; ++b) load(q[b], b, U.zb);
@@ -377,6 +446,13 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
         const uint32_t glo = __builtin_amdgcn_readfirstlane((int)(uint32_t)gv);
         const uint32_t ghi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(gv >> 32));
         const uint64_t gm = (uint64_t)ghi << 32 | glo;
+        if (AP && __builtin_expect(odd, 0)) {
+            plane_odd(z, gm);
+#pragma unroll
+            for (int b = 0; b < RING; ++b) load(q[b], b, min(z + 1, U.ze - 1));
+            slots(zl + 1);
+            continue;
+        }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
@@ -434,10 +510,53 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     }
 }
 
+// What the sums over entries need to form a projection again from the block.
+template <typename T>
+struct NlSupport {
+    const T* y;
+    long ldx;
+    int nx, ny, nz;
+    double hx, hy, hz, inv_rc2, N0, N1, rcut, rcut2;
+    const NlCand* cand;
+    uint32_t* odd;
+    uint32_t epoch;
+};
+
+// so large that alpha may make it infinite, or not finite
+template <typename T>
+__device__ inline bool beyond(T v) {
+    return !(fabs(v) < (sizeof(T) == 8 ? (T)1e250 : (T)1e25f));
+}
+
+// sum of chi_lm y over the points that a pair reaches, for a projection in which
+// a value that is not finite took part; ends at the first NaN.
+template <typename T>
+__device__ double sum_support(const NlSupport<T>& a, const NlCand& c, const T* y, int lm) {
+    const int z0 = max(0, (int)ceil((c.pz - a.rcut) / a.hz) - c.bz - 1);
+    const int z1 = min(a.nz - 1, (int)floor((c.pz + a.rcut) / a.hz) - c.bz + 1);
+    const int y0 = max(0, (int)ceil((c.py - a.rcut) / a.hy) - c.by - 1);
+    const int y1 = min(a.ny - 1, (int)floor((c.py + a.rcut) / a.hy) - c.by + 1);
+    const int x0 = max(0, (int)ceil((c.px - a.rcut) / a.hx) - c.bx - 1);
+    const int x1 = min(a.nx - 1, (int)floor((c.px + a.rcut) / a.hx) - c.bx + 1);
+    double s = 0.0;
+    for (int z = z0; z <= z1; ++z)
+        for (int j = y0; j <= y1; ++j)
+            for (int i = x0; i <= x1; ++i) {
+                const double dx = off_x(c, i, a.hx), dy = off_y(c, j, a.hy), dz = off_z(c, z, a.hz);
+                const double r2 = add_sq(sum_sq(dx, dy), dz);
+                if (r2 > a.rcut2) continue;
+                const double f = lm == 0 ? a.N0 : a.N1 * (lm == 1 ? dx : (lm == 2 ? dy : dz));
+                s += f * exp(-r2 * a.inv_rc2) * (double)y[i + (long)a.nx * (j + (long)a.ny * z)];
+                if (s != s) return s;
+            }
+    return s;
+}
+
 // D(4a+lm, col) = gamma_lm dV sum of atom a's entries, in entry order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ part, int ncol,
                                                    const int* __restrict__ off, const int* __restrict__ ent,
+                                                   const int* __restrict__ cand_off, NlSupport<T> sup,
                                                    const double* __restrict__ g4, double dV, T* __restrict__ D,
                                                    long ldD) {
     const int a = blockIdx.x;
@@ -455,7 +574,14 @@ __global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ pa
         for (int k = 0; k < 8; ++k)
             if (e + k < e1) s += v[k];
     }
-    D[(long)col * ldD + 4 * a + lm] = (T)(g4[4 * a + lm] * dV * s);
+    if (__builtin_expect(!__builtin_isfinite(s), 0)) {
+        s = 0.0;
+        for (int q = cand_off[a]; q < cand_off[a + 1]; ++q)
+            s += sum_support(sup, sup.cand[q], sup.y + (long)col * sup.ldx, lm);
+    }
+    const T v = (T)(g4[4 * a + lm] * dV * s);
+    if (__builtin_expect(beyond(v), 0)) sup.odd[col / 16] = sup.epoch;
+    D[(long)col * ldD + 4 * a + lm] = v;
 }
 
 // cos, sin of k . sL of every (atom, image) pair
@@ -472,10 +598,11 @@ __global__ void k_nl_phase(const NlCand* __restrict__ cand, int n, int nx, int n
 //   D_a = gamma dV sum_s exp(i k.sL) (p_s[u] + i p_s[v])   (entries in order),
 // and the coefficients exp(-i k.sL) D_a of every image, real part at the
 // column of u, imaginary part at that of v.
+template <typename T>
 __global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ part, int ncol,
                                                      const int* __restrict__ off, const int* __restrict__ ent,
                                                      const int* __restrict__ ent_cand,
-                                                     const int* __restrict__ cand_off,
+                                                     const int* __restrict__ cand_off, NlSupport<T> sup, long half,
                                                      const double* __restrict__ phase, const double* __restrict__ g4,
                                                      double dV, double* __restrict__ D, long ldD) {
     const int a = blockIdx.x;
@@ -502,9 +629,19 @@ __global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ 
                 zi += sn[k] * u[k] + cs[k] * v[k];
             }
     }
+    if (__builtin_expect(!(__builtin_isfinite(zr) && __builtin_isfinite(zi)), 0)) {
+        zr = zi = 0.0;
+        const T* y = sup.y + (long)c * sup.ldx;
+        for (int s = cand_off[a]; s < cand_off[a + 1]; ++s) {
+            const double u = sum_support(sup, sup.cand[s], y, lm), v = sum_support(sup, sup.cand[s], y + half, lm);
+            zr += phase[2 * s] * u - phase[2 * s + 1] * v;
+            zi += phase[2 * s + 1] * u + phase[2 * s] * v;
+        }
+    }
     const double g = dV * g4[4 * a + lm];
     zr *= g;
     zi *= g;
+    if (__builtin_expect(beyond(zr) || beyond(zi), 0)) sup.odd[c / 8] = sup.epoch;
     for (int s = cand_off[a]; s < cand_off[a + 1]; ++s) {
         const double cs = phase[2 * s], sn = phase[2 * s + 1];
         D[(2L * c) * ldD + 4 * s + lm] = zr * cs + zi * sn;
@@ -534,7 +671,7 @@ float* D_of<float>(sparc_gpu_ctx c) {
 
 void free_nl_pass(NlPass& T) {
     for (void* p : {(void*)T.units, (void*)T.blk, (void*)T.occ, (void*)T.gm, (void*)T.ent_cand, (void*)T.cand,
-                    (void*)T.red_off, (void*)T.red_ent, (void*)T.cand_off, T.dummy})
+                    (void*)T.red_off, (void*)T.red_ent, (void*)T.cand_off, (void*)T.odd, T.dummy})
         if (p) hipFree(p);
     T = NlPass{};
 }
@@ -800,9 +937,12 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
     }
     T.zlen = zlen;
     T.ncl = ncl;
-    SG_HIP(c, hipMalloc(&T.dummy, 256 * sizeof(double)));
-    T.n_entries = (long)ent_cand.size();
     sparc_status st;
+    SG_HIP(c, hipMalloc(&T.dummy, 256 * sizeof(double)));
+    // one per column of a block at most (column groups of less than 16), two
+    // blocks' worth of halves in tiles of 16 for Bloch columns
+    if ((st = put(c, &T.odd, std::vector<uint32_t>(c->n_states + 1, 0))) != SPARC_OK) return st;
+    T.n_entries = (long)ent_cand.size();
     if ((st = put(c, &T.units, units)) != SPARC_OK) return st;
     if ((st = put(c, &T.blk, blk)) != SPARC_OK) return st;
     if ((st = put(c, &T.occ, occ)) != SPARC_OK) return st;
@@ -882,11 +1022,19 @@ static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
     a.rcut2 = c->rcut_nl * c->rcut_nl;
     a.D = nullptr;
     a.ldD = 0;
+    a.odd = N.odd;
+    a.epoch = N.epoch;
     a.part = nullptr;
     a.params = c->scal + S_A;
     a.mode = mode;
     a.step = step;
     return a;
+}
+
+template <typename T, typename C>
+static NlSupport<T> support(sparc_gpu_ctx c, const NlArgs<T, C>& a, uint32_t epoch) {
+    return NlSupport<T>{a.y,  a.ldx, a.nx,       a.ny,    a.nz,   a.hx,  a.hy, a.hz, a.inv_rc2,
+                        a.N0, a.N1,  c->rcut_nl, a.rcut2, a.cand, a.odd, epoch};
 }
 
 // The pass over the columns set in a; with further layers every apply comes
@@ -945,15 +1093,18 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
     for (int c0 = 0; c0 < ncol; c0 += group) {
         a.ncol = std::min(group, ncol - c0);
         a.y = y + (long)c0 * ldx;
+        a.odd = N.odd + (group < 16 ? c0 : c0 / 16);
         T* D = D_of<T>(c) + (long)c0 * a.ldD;
         a.D = D;
         if ((st = run_layers<T, T>(c, a, ap, pr)) != SPARC_OK) return st;
         if (pr) {
             k_nl_reduce<T><<<dim3(c->n_atoms, div_up(4L * a.ncol, 256)), 256, 0, c->stream>>>(
-                part, a.ncol, N.red_off, N.red_ent, c->nl.gamma4, c->dV, D, a.ldD);
+                part, a.ncol, N.red_off, N.red_ent, N.cand_off, support(c, a, a.epoch + 1), c->nl.gamma4, c->dV, D,
+                a.ldD);
             SG_CHECK_LAUNCH(c);
         }
     }
+    if (pr) ++c->nlp.epoch;
     prof_end(c, slot);
     return SPARC_OK;
 }
@@ -1001,9 +1152,11 @@ sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool 
     a.D = c->kp_D;
     if ((st = run_layers<T, double>(c, a, ap, pr)) != SPARC_OK) return st;
     if (pr) {
-        k_nl_reduce_k<<<dim3(c->n_atoms, div_up(4L * ncol, 256)), 256, 0, c->stream>>>(
-            part, ncol, N.red_off, N.red_ent, N.ent_cand, N.cand_off, c->kp_phase, c->nl.gamma4, c->dV, c->kp_D, ldD);
+        k_nl_reduce_k<T><<<dim3(c->n_atoms, div_up(4L * ncol, 256)), 256, 0, c->stream>>>(
+            part, ncol, N.red_off, N.red_ent, N.ent_cand, N.cand_off, support(c, a, a.epoch + 1), a.half, c->kp_phase,
+            c->nl.gamma4, c->dV, c->kp_D, ldD);
         SG_CHECK_LAUNCH(c);
+        ++c->nlp.epoch;
     }
     prof_end(c, slot);
     return SPARC_OK;

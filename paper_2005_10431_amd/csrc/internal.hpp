@@ -45,24 +45,29 @@ struct NlUnit {
     int zb, ze, pencil, nb, ebase, ncl;
 };
 
-// Tables of the nonlocal pass (nonlocal.hip)
-struct NlPass {
+// Tables of the nonlocal pass (nonlocal.hip).  NlRanges: the units and slots for
+// one cut of z into ranges.
+struct NlRanges {
     NlUnit* units = nullptr;
-    int* blk = nullptr;          // first points of the kNlBlocks blocks of each pencil, -1 pads
-    void* dummy = nullptr;       // 256 doubles: target of the stores of pads
     uint8_t* occ = nullptr;      // per unit zlen x slots: the unit's pair in each slot (255: none)
     uint64_t* gm = nullptr;      // per unit zlen: slot groups that meet each block
     int* ent_cand = nullptr;     // pair of every entry
+    int* red_off = nullptr;      // entries of each atom
+    int* red_ent = nullptr;
+    int zlen = 1, ncl = 1;
+    long n_entries = 0;
+    std::vector<int> layer_off;  // unit ranges of the layers
+};
+struct NlPass {
+    int* blk = nullptr;          // first points of the kNlBlocks blocks of each pencil, -1 pads
+    void* dummy = nullptr;       // 256 doubles: target of the stores of pads
+    double* zero = nullptr;      // 4 coefficients of a slot without a pair; alpha of the step that will apply D
     NlCand* cand = nullptr;
     uint32_t* odd = nullptr;     // per 16 columns: epoch of the last projection that was not finite
     uint32_t epoch = 0;          // projections formed so far (the one that an apply takes is the last)
-    int* red_off = nullptr;      // entries of each atom
-    int* red_ent = nullptr;
     int* cand_off = nullptr;     // pairs of each atom
-    int n_cand = 0;
-    int slots = 8, zlen = 1, ncl = 1;
-    long n_entries = 0;
-    std::vector<int> layer_off;  // unit ranges of the layers
+    int n_cand = 0, npen = 0, slots = 8;
+    std::vector<NlRanges> ranges;   // the first is made for the context's full block
 };
 
 // Shape of a sweep over ncol columns (see sweep_plan)
@@ -240,9 +245,9 @@ enum Flag {
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx,
                            int mode, int step, bool halves = false);
-// The nonlocal term of a block in one pass: apply (y += alpha chi D, alpha
-// that of the recurrence for (mode, step), 1 for mode 0) and / or project (D =
-// gamma dV chi^T y of the completed y).  The partial sums go to `part`
+// The nonlocal term of a block in one pass: apply (y += chi D) and / or project (D =
+// alpha gamma dV chi^T y of the completed y, alpha that of the filter step (mode,
+// step) that will apply it, 1 for mode 0).  The partial sums go to `part`
 // (part_elems doubles, as many columns at a time as fit) when given, else to
 // context memory sized for the whole block.  Does nothing without projectors.
 template <typename T>

@@ -120,14 +120,14 @@ template sparc_status bloch_apply_impl<float>(sparc_gpu_ctx, const float*, float
 template <typename T>
 sparc_status bloch_filter_impl(sparc_gpu_ctx c, T* X, T* W, int ncol, long ldx, int m) {
     sparc_status st;
-    if ((st = nl_pass_k<T>(c, X, ncol, ldx, false, true, 0, 0)) != SPARC_OK) return st;
+    if ((st = nl_pass_k<T>(c, X, ncol, ldx, false, true, 1, 1)) != SPARC_OK) return st;
     for (int k = 1; k <= m; ++k) {
         T* cur = (k % 2 == 0) ? W : X;
         T* dst = (k % 2 == 0) ? X : W;
         const int mode = k == 1 ? 1 : 2;
         if ((st = launch_hsweep<T>(c, cur, dst, k == 1 ? nullptr : dst, 2 * ncol, ldx, mode, k, true)) != SPARC_OK)
             return st;
-        if ((st = nl_pass_k<T>(c, dst, ncol, ldx, true, k < m, mode, k)) != SPARC_OK) return st;
+        if ((st = nl_pass_k<T>(c, dst, ncol, ldx, true, k < m, 2, k + 1)) != SPARC_OK) return st;
     }
     if (m % 2 == 1) {
         k_copy_block_k<T><<<dim3(div_up(2 * c->nd, 256), ncol), 256, 0, c->stream>>>(W, X, 2 * c->nd, ncol, ldx);

@@ -4,7 +4,7 @@
 // The projections D of a block and their application are products with a
 // tall matrix that every orbital shares: chi on a tile of the grid, against
 // 16 orbitals at a time, on MFMA.  One pass over the block does
-//   apply    y += alpha chi D     and / or     project    D' = gamma dV chi^T y,
+//   apply    y += chi D     and / or     project    D' = alpha gamma dV chi^T y,
 // so a filter step is one local sweep followed by one pass that completes
 // its output and forms the projections the next step needs.
 //
@@ -22,7 +22,8 @@
 //    accumulators and its 4 coefficients in registers until it leaves, when
 //    the sums are written as one partial entry (entry, orbital, lm); the
 //    entries of an atom are added in a fixed order by k_nl_reduce, so results
-//    are bitwise reproducible and independent of how columns are grouped;
+//    are bitwise reproducible.  The order goes with the number of columns of the
+//    call, not with the groups that they are taken in;
 //  - per plane the workgroup tabulates chi of the plane's points x slots in
 //    LDS, shared by its orbitals; slots go in groups of four (16 projectors,
 //    one MFMA row tile) and a block skips the groups that do not touch it (a
@@ -55,6 +56,8 @@ constexpr int kMaxLocal = 112;      // pairs of a unit (with 24 slots and 128 pl
 constexpr int kMaxPlanes = 128;     // planes of a unit
 constexpr int kMaxSlots = 24;
 constexpr int kNlWaves = 4;         // waves of a workgroup, 16 orbitals each
+constexpr int kNlSplit = 3;         // or three that share the blocks of 16 orbitals
+constexpr double kNlSplitPlane = 0.65;   // and time of a plane then
 
 template <typename T, int N>
 struct NlVec {
@@ -131,8 +134,10 @@ struct NlArgs {
     uint32_t* odd;               // per 16 columns: epoch if a coefficient is not finite
     uint32_t epoch;
     double* part;                // [(entry ncol + col) 4 + lm]
+    const C* zero;               // coefficients of a slot without a pair
+    double* alpha;               // project: alpha of the filter step (mode, step) that will apply D
     const double* params;
-    int mode, step;              // filter step whose output is completed: alpha of the recurrence
+    int mode, step;
 };
 
 // Planes of the sums of one group: FP64 in the accumulators; in FP32 the MFMA
@@ -212,18 +217,20 @@ __device__ inline double add_sq(double r2, double d) {
     return r2 + d * d;
 }
 
-// AP: y += alpha chi D.  PR: partial projections of (the completed) y.
+// AP: y += chi D.  PR: partial projections of (the completed) y.  WB: blocks
+// of a wave: all of the pencil's, or a third of them, when the waves of a workgroup
+// share 16 columns and leave a partial entry each (see nl_shape).
 // Per plane: barrier; chi of the plane into LDS; barrier; the products.  Two
 // workgroups of four waves fit a compute unit (71 KB of LDS each), so one's
 // table overlaps the other's products.  A wave has the loads of a whole plane
 // (12 KB in FP64) in flight: with half of that and six waves per workgroup
 // the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.
-template <typename T, typename C, int S, bool AP, bool PR, bool TAIL>
+template <typename T, typename C, int S, int WB, bool AP, bool PR, bool TAIL>
 __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     using P = Pts<C>;
     using acc_t = typename Mfma<C>::acc_t;
     constexpr int NB = kNlBlocks, NG = S / 4, RS = 4 * S + 4, NP = 16 * NB;
-    constexpr int RING = NB;   // blocks in flight per wave: a plane
+    constexpr int NW = NB / WB;   // waves that share a unit's blocks
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const NlLds L = nl_lds_layout(sizeof(C), S, a.zlen, a.ncl);
     C* chi = reinterpret_cast<C*>(smem_raw);
@@ -238,6 +245,10 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     // orbitals, the last ones first, which the sweep before has left in the
     // last-level cache; an XCD takes a contiguous
     // eighth of the units, a different one each time, since some hold one more
+    if (PR && blockIdx.x == 0 && threadIdx.x == 0) {
+        double csh, beta;
+        filter_coefs(a.params, a.mode, a.step, *a.alpha, csh, beta);
+    }
     const int bslot = blockIdx.x / 8, per = (a.nunit + 7) / 8;
     const int chunk = a.nchunk - 1 - bslot / per, xr = (blockIdx.x + 3 * chunk) % 8;
     const int u = a.nunit / 8 * xr + min(xr, a.nunit % 8) + bslot % per;
@@ -264,13 +275,14 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     }
     __syncthreads();
 
-    // z factor and dz of the slots' pairs at plane zl
+    // z factor and dz of the slots' pairs at plane zl (by the wave without columns, if any)
+    const int zt = NW > 1 ? t - 64 * NW : t;
     auto zfactor = [&](int zl) {
-        if (t < S) {
-            const int o = occ[zl * S + t];
+        if (zt >= 0 && zt < S) {
+            const int o = occ[zl * S + zt];
             if (o != kIdle) {
                 const double dz = off_z(cand[o], U.zb + zl, a.hz);
-                double* e = ezdz + ((zl & 1) * S + t) * 2;
+                double* e = ezdz + ((zl & 1) * S + zt) * 2;
                 e[0] = exp(-dz * dz * a.inv_rc2);
                 e[1] = dz;
             }
@@ -278,51 +290,113 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     };
     // chi of plane zl: point-major rows of (slot, lm), zero where the pair
     // does not reach.  A thread keeps the same (slot, point) places through
-    // the planes; it forms their x-y Gaussian when a pair enters the slot.
+    // the planes; it forms the x-y Gaussian when a pair enters the slot.  Waves that
+    // share their columns leave registers for the places' offsets too (KEEP; one
+    // column at 120^3, project and apply: 145 and 156 us without, 127 and 140 with).
+    // With whole columns these cost the second workgroup's registers (FP32) or
+    // give nothing (FP64).
+    constexpr int NE = NP * S / (64 * kNlWaves);   // places of a thread
+    constexpr bool KEEP = WB < NB && sizeof(C) == 8 && S <= 16;
+    struct Place {
+        double dx, dy;   // dx 1e150: no pair, or a point that the pencil does not own
+        C g;
+    };
+    Place pl[KEEP ? NE : 1];
     auto build = [&](int zl) {
         const uint64_t gm = gml[zl];
-        for (int e = t; e < NP * S; e += nt) {
-            const int s = e / NP, q = e - s * NP;
-            const int o = occ[zl * S + s], w = xy[q];
-            const bool live = o != kIdle && w >= 0;
-            double dx = 0, dy = 0, r2 = 0;
-            if (live) {
-                dx = off_x(cand[o], w & 0xFFFF, a.hx);
-                dy = off_y(cand[o], w >> 16, a.hy);
-                r2 = sum_sq(dx, dy);
-                if (zl == 0 || occ[(zl - 1) * S + s] != o) gxy[e] = (C)exp(-r2 * a.inv_rc2);
-            }
-            if (!((gm >> ((q >> 4) * NG + (s >> 2))) & 1)) continue;
-            C v0 = 0, v1 = 0, v2 = 0, v3 = 0;
-            if (live) {
-                const double* z = ezdz + ((zl & 1) * S + s) * 2;
-                if (add_sq(r2, z[1]) <= a.rcut2) {
-                    const C ex = gxy[e] * (C)z[0];
-                    const C e1 = (C)a.N1 * ex;
-                    v0 = (C)a.N0 * ex;
-                    v1 = e1 * (C)dx;
-                    v2 = e1 * (C)dy;
-                    v3 = e1 * (C)z[1];
+        auto put_chi = [&](int s, int q, bool in, C gx, C dx, C dy, double ez, double dz) __attribute__((always_inline)) {
+            const C ex = gx * (C)ez, e1 = (C)a.N1 * ex;
+            C* r = chi + q * RS + 4 * s;
+            r[0] = in ? (C)a.N0 * ex : (C)0;
+            r[1] = in ? e1 * dx : (C)0;
+            r[2] = in ? e1 * dy : (C)0;
+            r[3] = in ? e1 * (C)dz : (C)0;
+        };
+        if constexpr (KEEP) {
+            // opaque, so that the places' addresses are formed here again and not
+            // kept in registers along the planes
+            int tt = t;
+            asm volatile("" : "+v"(tt));
+            // the table reads of several places at a time, so that their waits are one
+            constexpr int BT = AP && PR ? 3 : NE;
+#pragma unroll
+            for (int i0 = 0; i0 < NE; i0 += BT) {
+                int s[BT], q[BT], on[BT], was[BT];
+#pragma unroll
+                for (int i = 0; i < BT; ++i) {
+                    const int e = tt + 64 * kNlWaves * (i0 + i);
+                    s[i] = e / NP;
+                    q[i] = e - s[i] * NP;
+                    on[i] = occ[zl * S + s[i]];
+                    was[i] = occ[max(zl - 1, 0) * S + s[i]];
+                }
+                double z[BT][2];
+#pragma unroll
+                for (int i = 0; i < BT; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) z[i][j] = ezdz[((zl & 1) * S + s[i]) * 2 + j];
+#pragma unroll
+                for (int i = 0; i < BT; ++i) {
+                    if (zl != 0 && on[i] == was[i]) continue;
+                    Place& v = pl[i0 + i];
+                    const int w = xy[q[i]];
+                    v = Place{1e150, 0.0, 0};
+                    if (on[i] != kIdle && w >= 0) {
+                        v.dx = off_x(cand[on[i]], w & 0xFFFF, a.hx);
+                        v.dy = off_y(cand[on[i]], w >> 16, a.hy);
+                        v.g = (C)exp(-sum_sq(v.dx, v.dy) * a.inv_rc2);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < BT; ++i) {
+                    const Place& v = pl[i0 + i];
+                    if ((gm >> ((q[i] >> 4) * NG + (s[i] >> 2))) & 1)
+                        put_chi(s[i], q[i], add_sq(sum_sq(v.dx, v.dy), z[i][1]) <= a.rcut2, v.g, (C)v.dx, (C)v.dy, z[i][0],
+                                z[i][1]);
                 }
             }
-            C* r = chi + q * RS + 4 * s;
-            r[0] = v0;
-            r[1] = v1;
-            r[2] = v2;
-            r[3] = v3;
+        } else {
+            for (int e = t; e < NP * S; e += nt) {
+                const int s = e / NP, q = e - s * NP;
+                const int o = occ[zl * S + s], w = xy[q];
+                const bool live = o != kIdle && w >= 0;
+                double dx = 0, dy = 0, r2 = 0;
+                if (live) {
+                    dx = off_x(cand[o], w & 0xFFFF, a.hx);
+                    dy = off_y(cand[o], w >> 16, a.hy);
+                    r2 = sum_sq(dx, dy);
+                    if (zl == 0 || occ[(zl - 1) * S + s] != o) gxy[e] = (C)exp(-r2 * a.inv_rc2);
+                }
+                if (!((gm >> ((q >> 4) * NG + (s >> 2))) & 1)) continue;
+                C v0 = 0, v1 = 0, v2 = 0, v3 = 0;
+                if (live) {
+                    const double* z = ezdz + ((zl & 1) * S + s) * 2;
+                    if (add_sq(r2, z[1]) <= a.rcut2) {
+                        const C ex = gxy[e] * (C)z[0];
+                        const C e1 = (C)a.N1 * ex;
+                        v0 = (C)a.N0 * ex;
+                        v1 = e1 * (C)dx;
+                        v2 = e1 * (C)dy;
+                        v3 = e1 * (C)z[1];
+                    }
+                }
+                C* r = chi + q * RS + 4 * s;
+                r[0] = v0;
+                r[1] = v1;
+                r[2] = v2;
+                r[3] = v3;
+            }
         }
     };
 
     const int wv = t >> 6, lane = t & 63, li = lane & 15, g = lane >> 4;
     // waves without columns only help to build; lanes past the last column
     // repeat it (the same loads, results and stores)
-    const bool mine = wv < a.nwc && 16 * (chunk * a.nwc + wv) < a.ncol;
-    const int cl = 16 * (chunk * a.nwc + wv) + li, col = min(cl, a.ncol - 1);
+    const int part = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(wv), b0 = WB * part;   // the wave's blocks: b0 ..
+    const int tile = NW == 1 ? chunk * a.nwc + wv : chunk;                               // and 16 columns
+    const bool mine = (NW == 1 ? wv < a.nwc : wv < NW) && 16 * tile < a.ncol;
+    const int cl = 16 * tile + li, col = min(cl, a.ncol - 1);
     T* yc = a.y + (long)(col >> a.halves) * a.ldx + (long)(col & a.halves) * a.half;
-
-    double alpha = 1.0, csh, beta;
-    if (AP) filter_coefs(a.params, a.mode, a.step, alpha, csh, beta);
-    const C al = (C)alpha;
 
     GroupSum<C> sum[NG];
     C d[NG][4];
@@ -342,30 +416,32 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
             if (on == oc[G]) continue;
             if (PR) {
                 if (oc[G] != kIdle && cl < a.ncol) {
-                    double* q = a.part + ((long)(U.ebase + oc[G]) * a.ncol + col) * 4;
+                    double* q = a.part + (((long)(U.ebase + oc[G]) * NW + part) * a.ncol + col) * 4;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) q[r] = sum[G].get(r);
                 }
                 sum[G].zero();
             }
             if (AP) {
-                const C* Dc = a.D + (long)col * a.ldD;
-                if (on != kIdle) Dc += 4 * (a.by_pair ? cand[on].id : cand[on].atom);
+                // plain loads, nothing that would wait for them (and for those of the
+                // next plane's blocks, which are in flight) before the next plane
+                const C* Dc = a.zero;
+                if (on != kIdle) Dc = a.D + (long)col * a.ldD + 4 * (a.by_pair ? cand[on].id : cand[on].atom);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) d[G][j] = on == kIdle ? (C)0 : al * Dc[j];
+                for (int j = 0; j < 4; ++j) d[G][j] = Dc[j];
             }
             oc[G] = on;
         }
     };
     // first point of each block (in scalar registers); places past the
     // pencil's list load the plane's first points and meet no group
-    int pb0[NB];
+    int pb0[WB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) pb0[b] = __builtin_amdgcn_readfirstlane(max(0, blk[b]));
-    T q[RING][4];
+    for (int b = 0; b < WB; ++b) pb0[b] = __builtin_amdgcn_readfirstlane(mine ? max(0, blk[b0 + b]) : 0);
+    T q[WB][4];   // the blocks of a plane
     auto load = [&](T* v, int b, int z) { P::load(yc + (long)z * a.nxy, pb0[b], g, v); };
     // some coefficients of the wave's columns may not be finite
-    const bool odd = AP && mine && a.odd[chunk * a.nwc + wv] == a.epoch;
+    const bool odd = AP && mine && a.odd[tile] == a.epoch;
     // a plane of such columns: block by block as in the loop below, with the
     // coefficients that are not finite at the points that their pairs reach only
     auto plane_odd = [&](int z, uint64_t gm) {
@@ -378,7 +454,7 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) d[G][j] = 0;
 #pragma unroll 1
-        for (int b = 0; b < NB; ++b) {
+        for (int b = b0; b < b0 + WB; ++b) {
             const bool tail = TAIL && b == NB - 1 && part5;
             if (b >= nb && !tail) continue;
             const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
@@ -398,7 +474,7 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
                 const int o = occ[zl * S + s];
                 if (o == kIdle || !((gb >> (s >> 2)) & 1)) continue;
                 const C* e = Dc + 4 * (a.by_pair ? cand[o].id : cand[o].atom);
-                const C e0 = al * e[0], e1 = al * e[1], e2 = al * e[2], e3 = al * e[3];
+                const C e0 = e[0], e1 = e[1], e2 = e[2], e3 = e[3];
                 if (__builtin_isfinite(e0) && __builtin_isfinite(e1) && __builtin_isfinite(e2) && __builtin_isfinite(e3))
                     continue;
                 const double dz = ezdz[((zl & 1) * S + s) * 2 + 1];
@@ -430,7 +506,7 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     };
     if (mine) {
 #pragma unroll
-        for (int b = 0; b < RING; ++b) load(q[b], b, U.zb);
+        for (int b = 0; b < WB; ++b) load(q[b], b, U.zb);
         slots(0);
     }
     zfactor(0);
@@ -449,19 +525,19 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
         if (AP && __builtin_expect(odd, 0)) {
             plane_odd(z, gm);
 #pragma unroll
-            for (int b = 0; b < RING; ++b) load(q[b], b, min(z + 1, U.ze - 1));
+            for (int b = 0; b < WB; ++b) load(q[b], b, min(z + 1, U.ze - 1));
             slots(zl + 1);
             continue;
         }
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
-            T* v = q[b % RING];
+        for (int b = 0; b < WB; ++b) {
+            const uint32_t gb = (uint32_t)(gm >> ((b0 + b) * NG)) & ((1u << NG) - 1);
+            T* v = q[b];
             acc_t acc = {(C)v[0], (C)v[1], (C)v[2], (C)v[3]};
-            // the next block of this ring place; loads and stores take no
+            // the block's next plane; loads and stores take no
             // branch, so that those in flight can be counted
-            load(v, (b + RING) % NB, b + RING < NB ? z : min(z + 1, U.ze - 1));
-            const C* cb = chi + 16 * b * RS;
+            load(v, b, min(z + 1, U.ze - 1));
+            const C* cb = chi + 16 * (b0 + b) * RS;
             // with both products the operands of the second are read along with
             // the first's, so that only one wait on LDS is left per group
             // (72^3 x 260: FP32 590 -> 550 us a degree, FP64 within 1%)
@@ -483,12 +559,12 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
                     }
                 T* yp = yc + (long)z * a.nxy + pb0[b];
                 const T o[4] = {(T)acc[0], (T)acc[1], (T)acc[2], (T)acc[3]};
-                if (TAIL && b == NB - 1 && part5) {
+                if (TAIL && b == WB - 1 && b0 + b == NB - 1 && part5) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         if (P::of(g, r) >= 16 - a.tail) yp[P::of(g, r)] = o[r];
                 } else {
-                    P::store(b < nb ? yp : dummy, 0, g, o);
+                    P::store(b0 + b < nb ? yp : dummy, 0, g, o);
                 }
             }
             if (PR) {
@@ -520,13 +596,8 @@ struct NlSupport {
     const NlCand* cand;
     uint32_t* odd;
     uint32_t epoch;
+    const double* alpha;    // of the filter step that will apply the projections
 };
-
-// so large that alpha may make it infinite, or not finite
-template <typename T>
-__device__ inline bool beyond(T v) {
-    return !(fabs(v) < (sizeof(T) == 8 ? (T)1e250 : (T)1e25f));
-}
 
 // sum of chi_lm y over the points that a pair reaches, for a projection in which
 // a value that is not finite took part; ends at the first NaN.
@@ -552,35 +623,47 @@ __device__ double sum_support(const NlSupport<T>& a, const NlCand& c, const T* y
     return s;
 }
 
-// D(4a+lm, col) = gamma_lm dV sum of atom a's entries, in entry order.
+// D(4a+lm, col) = alpha gamma_lm dV sum of atom a's entries (nw partial ones each, 1 or kNlSplit), in
+// `parts` runs of them side by side, each in entry order, added in order.
 template <typename T>
-__global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ part, int ncol,
+__global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ part, int ncol, int nw, int parts,
                                                    const int* __restrict__ off, const int* __restrict__ ent,
                                                    const int* __restrict__ cand_off, NlSupport<T> sup,
                                                    const double* __restrict__ g4, double dV, T* __restrict__ D,
                                                    long ldD) {
-    const int a = blockIdx.x;
-    const long q = (long)blockIdx.y * blockDim.x + threadIdx.x;
-    if (q >= 4L * ncol) return;
+    __shared__ double sums[256];
+    const int a = blockIdx.x, per = 256 / parts, run = threadIdx.x / per;
+    const long q = (long)blockIdx.y * per + threadIdx.x % per;
+    const bool on = q < 4L * ncol;
     const int col = (int)(q / 4), lm = (int)(q % 4);
     // eight loads in flight, added in order
     double s = 0.0;
-    const int e1 = off[a + 1];
-    for (int e = off[a]; e < e1; e += 8) {
+    const int e0 = off[a], n = (off[a + 1] - e0) * nw, len = (n + parts - 1) / parts, k1 = min(n, (run + 1) * len);
+    for (int k = run * len; k < k1 && on; k += 8) {
         double v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = part[(long)ent[min(e + k, e1 - 1)] * ncol * 4 + q];
+        for (int u = 0; u < 8; ++u) {
+            const int i = min(k + u, k1 - 1), e = nw == 1 ? i : i / kNlSplit;
+            v[u] = part[((long)ent[e0 + e] * nw + (i - e * nw)) * ncol * 4 + q];
+        }
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (e + k < e1) s += v[k];
+        for (int u = 0; u < 8; ++u)
+            if (k + u < k1) s += v[u];
     }
+    if (parts > 1) {
+        sums[threadIdx.x] = s;
+        __syncthreads();
+        if (run == 0)
+            for (int r = 1; r < parts; ++r) s += sums[r * per + threadIdx.x];
+    }
+    if (run || !on) return;
     if (__builtin_expect(!__builtin_isfinite(s), 0)) {
         s = 0.0;
         for (int q = cand_off[a]; q < cand_off[a + 1]; ++q)
             s += sum_support(sup, sup.cand[q], sup.y + (long)col * sup.ldx, lm);
     }
-    const T v = (T)(g4[4 * a + lm] * dV * s);
-    if (__builtin_expect(beyond(v), 0)) sup.odd[col / 16] = sup.epoch;
+    const T v = (T)(*sup.alpha * g4[4 * a + lm] * dV * s);
+    if (__builtin_expect(!__builtin_isfinite(v), 0)) sup.odd[col / 16] = sup.epoch;
     D[(long)col * ldD + 4 * a + lm] = v;
 }
 
@@ -595,40 +678,52 @@ __global__ void k_nl_phase(const NlCand* __restrict__ cand, int n, int nx, int n
 
 // Bloch form, per atom and complex column c: with the real projections p_s of
 // the two halves on the atom's images s,
-//   D_a = gamma dV sum_s exp(i k.sL) (p_s[u] + i p_s[v])   (entries in order),
+//   D_a = alpha gamma dV sum_s exp(i k.sL) (p_s[u] + i p_s[v])   (entries as above),
 // and the coefficients exp(-i k.sL) D_a of every image, real part at the
 // column of u, imaginary part at that of v.
 template <typename T>
-__global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ part, int ncol,
+__global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ part, int ncol, int nw, int parts,
                                                      const int* __restrict__ off, const int* __restrict__ ent,
                                                      const int* __restrict__ ent_cand,
                                                      const int* __restrict__ cand_off, NlSupport<T> sup, long half,
                                                      const double* __restrict__ phase, const double* __restrict__ g4,
                                                      double dV, double* __restrict__ D, long ldD) {
-    const int a = blockIdx.x;
-    const long q = (long)blockIdx.y * blockDim.x + threadIdx.x;
-    if (q >= 4L * ncol) return;
+    __shared__ double sums[2][256];
+    const int a = blockIdx.x, per = 256 / parts, run = threadIdx.x / per;
+    const long q = (long)blockIdx.y * per + threadIdx.x % per;
+    const bool on = q < 4L * ncol;
     const int c = (int)(q / 4), lm = (int)(q % 4);
     double zr = 0.0, zi = 0.0;
-    const int e1 = off[a + 1];
-    for (int e = off[a]; e < e1; e += 4) {
+    const int e0 = off[a], n = (off[a + 1] - e0) * nw, len = (n + parts - 1) / parts, k1 = min(n, (run + 1) * len);
+    for (int k = run * len; k < k1 && on; k += 4) {
         double u[4], v[4], cs[4], sn[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int en = ent[min(e + k, e1 - 1)];
-            const double* p = part + ((long)en * 2 * ncol + 2 * c) * 4 + lm;
-            u[k] = p[0];
-            v[k] = p[4];
-            cs[k] = phase[2 * ent_cand[en]];
-            sn[k] = phase[2 * ent_cand[en] + 1];
+        for (int r = 0; r < 4; ++r) {
+            const int i = min(k + r, k1 - 1), e = nw == 1 ? i : i / kNlSplit, en = ent[e0 + e];
+            const double* p = part + (((long)en * nw + (i - e * nw)) * 2 * ncol + 2 * c) * 4 + lm;
+            u[r] = p[0];
+            v[r] = p[4];
+            cs[r] = phase[2 * ent_cand[en]];
+            sn[r] = phase[2 * ent_cand[en] + 1];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (e + k < e1) {
-                zr += cs[k] * u[k] - sn[k] * v[k];
-                zi += sn[k] * u[k] + cs[k] * v[k];
+        for (int r = 0; r < 4; ++r)
+            if (k + r < k1) {
+                zr += cs[r] * u[r] - sn[r] * v[r];
+                zi += sn[r] * u[r] + cs[r] * v[r];
             }
     }
+    if (parts > 1) {
+        sums[0][threadIdx.x] = zr;
+        sums[1][threadIdx.x] = zi;
+        __syncthreads();
+        if (run == 0)
+            for (int r = 1; r < parts; ++r) {
+                zr += sums[0][r * per + threadIdx.x];
+                zi += sums[1][r * per + threadIdx.x];
+            }
+    }
+    if (run || !on) return;
     if (__builtin_expect(!(__builtin_isfinite(zr) && __builtin_isfinite(zi)), 0)) {
         zr = zi = 0.0;
         const T* y = sup.y + (long)c * sup.ldx;
@@ -638,10 +733,10 @@ __global__ __launch_bounds__(256) void k_nl_reduce_k(const double* __restrict__ 
             zi += phase[2 * s + 1] * u + phase[2 * s] * v;
         }
     }
-    const double g = dV * g4[4 * a + lm];
+    const double g = *sup.alpha * dV * g4[4 * a + lm];
     zr *= g;
     zi *= g;
-    if (__builtin_expect(beyond(zr) || beyond(zi), 0)) sup.odd[c / 8] = sup.epoch;
+    if (__builtin_expect(!(fabs(zr) < 1e300 && fabs(zi) < 1e300), 0)) sup.odd[c / 8] = sup.epoch;
     for (int s = cand_off[a]; s < cand_off[a + 1]; ++s) {
         const double cs = phase[2 * s], sn = phase[2 * s + 1];
         D[(2L * c) * ldD + 4 * s + lm] = zr * cs + zi * sn;
@@ -670,13 +765,164 @@ float* D_of<float>(sparc_gpu_ctx c) {
 }  // namespace
 
 void free_nl_pass(NlPass& T) {
-    for (void* p : {(void*)T.units, (void*)T.blk, (void*)T.occ, (void*)T.gm, (void*)T.ent_cand, (void*)T.cand,
-                    (void*)T.red_off, (void*)T.red_ent, (void*)T.cand_off, (void*)T.odd, T.dummy})
+    for (void* p : {(void*)T.blk, (void*)T.cand, (void*)T.cand_off, (void*)T.odd, (void*)T.zero, T.dummy})
         if (p) hipFree(p);
+    for (NlRanges& R : T.ranges)
+        for (void* p : {(void*)R.units, (void*)R.occ, (void*)R.gm, (void*)R.ent_cand, (void*)R.red_off, (void*)R.red_ent})
+            if (p) hipFree(p);
     T = NlPass{};
 }
 
-// The units, slots and block masks of the pass.  segs: every (atom, image)
+namespace {
+
+// Time of a pass over `tiles` column tiles of 16 in k z ranges, `split`: one tile
+// per workgroup, whose waves share the blocks.  (Time of a plane) x (planes one
+// after another) on a chip that holds 512 workgroups, two per compute unit (768
+// that share blocks in FP32, whose tables take half the LDS); where half of a round
+// is enough, each runs alone and takes 0.65 of the time (8.3 and 13 us a plane at
+// 72^3).  A range costs about 3 planes more than its own (set-up, ends of pairs).
+double nl_cost(int npen, int nz, int tiles, int k, bool split, bool fp32) {
+    const long slots = split && fp32 ? 768 : 512, n = (long)npen * (split ? tiles : div_up(tiles, kNlWaves)) * k;
+    const long last = n % slots;
+    const double rounds = n / slots + (last == 0 ? 0.0 : (2 * last <= slots ? 0.65 : 1.0));
+    return rounds * (div_up(nz, k) + 3) * (split ? kNlSplitPlane : 1.0);
+}
+
+// A pair's support in a pencil's plane: the blocks it meets
+struct Hit {
+    int pencil, cand, z;
+    uint32_t mask;
+};
+
+// The hits of a pair in a pencil
+struct PairHits {
+    int cand;
+    size_t h0, h1;
+};
+
+}  // namespace
+
+// The units, slots and block masks for zs ranges of z.  hits: sorted by pencil,
+// pair and plane; pairs, first: where each pencil's pairs begin.
+static sparc_status build_ranges(sparc_gpu_ctx c, const std::vector<NlCand>& cands, const std::vector<Hit>& hits,
+                                 const std::vector<PairHits>& pairs, const std::vector<size_t>& first,
+                                 const std::vector<int>& nblk, int zs, NlRanges& R) {
+    const int nz = c->nz, S = c->nlp.slots, NG = S / 4, zlen = (nz + zs - 1) / zs;
+    zs = (nz + zlen - 1) / zlen;
+    struct Span {
+        int z0, z1, cand;
+        size_t h0, h1;
+    };
+    // slots: each pair takes, for its span of planes in the unit, a free one of the
+    // group that meets the fewest further blocks for it; pairs beyond the slots or
+    // the local indices go to a further layer (a further pass), which supports this
+    // dense do not reach in practice
+    struct Placed {
+        int slot, local;
+        Span s;
+    };
+    struct Unit {
+        NlUnit u;
+        std::vector<Placed> p;
+    };
+    std::vector<std::vector<Unit>> layers;
+    std::vector<Span> sp, rest;
+    std::vector<uint32_t> met;
+    int ncl = 1;
+    for (int pencil = 0; pencil + 1 < (int)first.size(); ++pencil)
+        for (int zr = 0; zr < zs; ++zr) {
+            const int zb = zr * zlen, ze = std::min(nz, zb + zlen);
+            auto before = [](const Hit& h, int z) { return h.z < z; };
+            sp.clear();
+            for (size_t q = first[pencil]; q < first[pencil + 1]; ++q) {
+                const auto b = hits.begin() + pairs[q].h0, e = hits.begin() + pairs[q].h1;
+                const auto lo = std::lower_bound(b, e, zb, before), hi = std::lower_bound(lo, e, ze, before);
+                if (lo != hi)
+                    sp.push_back({lo->z, (hi - 1)->z, pairs[q].cand, (size_t)(lo - hits.begin()), (size_t)(hi - hits.begin())});
+            }
+            std::sort(sp.begin(), sp.end(),
+                      [](const Span& A, const Span& B) { return A.z0 != B.z0 ? A.z0 < B.z0 : A.cand < B.cand; });
+            for (int layer = 0; !sp.empty(); ++layer) {
+                std::vector<int> end(S, -1);   // last plane of each slot's pair
+                met.assign((size_t)NG * zlen, 0);
+                rest.clear();
+                Unit un;
+                un.u = NlUnit{zb, ze, pencil, nblk[pencil], 0, 0};
+                for (const Span& s : sp) {
+                    int slot = -1, fewest = 1 << 30;
+                    for (int G = 0; G < NG; ++G) {
+                        int q = 4 * G;
+                        while (q < 4 * G + 4 && end[q] >= s.z0) ++q;
+                        if (q == 4 * G + 4) continue;
+                        int n = 0;   // blocks that group G would meet for this pair alone
+                        for (size_t h = s.h0; h < s.h1; ++h)
+                            n += __builtin_popcount(hits[h].mask & ~met[(size_t)G * zlen + hits[h].z - zb]);
+                        if (n < fewest) {
+                            fewest = n;
+                            slot = q;
+                        }
+                    }
+                    if (slot < 0 || un.p.size() >= (size_t)kMaxLocal) {
+                        rest.push_back(s);
+                        continue;
+                    }
+                    end[slot] = s.z1;
+                    for (size_t h = s.h0; h < s.h1; ++h) met[(size_t)(slot / 4) * zlen + hits[h].z - zb] |= hits[h].mask;
+                    un.p.push_back({slot, (int)un.p.size(), s});
+                }
+                un.u.ncl = (int)un.p.size();
+                ncl = std::max(ncl, un.u.ncl);
+                if ((int)layers.size() <= layer) layers.emplace_back();
+                layers[layer].push_back(std::move(un));
+                sp.swap(rest);
+            }
+        }
+    std::vector<NlUnit> units;
+    std::vector<uint8_t> occ;
+    std::vector<uint64_t> gm;
+    std::vector<int> ent_cand;
+    std::vector<std::vector<int>> per_atom(c->n_atoms);
+    R.layer_off.assign(1, 0);
+    for (auto& ly : layers) {
+        // units of one z range and neighbouring pencils side by side
+        std::stable_sort(ly.begin(), ly.end(), [](const Unit& A, const Unit& B) { return A.u.zb < B.u.zb; });
+        for (Unit& un : ly) {
+            un.u.ebase = (int)ent_cand.size();
+            const size_t o0 = occ.size(), g0 = gm.size();
+            occ.insert(occ.end(), (size_t)zlen * S, (uint8_t)kIdle);
+            gm.insert(gm.end(), zlen, 0);
+            for (const Placed& p : un.p) {
+                per_atom[cands[p.s.cand].atom].push_back((int)ent_cand.size());
+                ent_cand.push_back(p.s.cand);
+                for (int z = p.s.z0; z <= p.s.z1; ++z) occ[o0 + (size_t)(z - un.u.zb) * S + p.slot] = (uint8_t)p.local;
+                for (size_t h = p.s.h0; h < p.s.h1; ++h) {
+                    uint64_t& w = gm[g0 + hits[h].z - un.u.zb];
+                    for (int b = 0; b < kNlBlocks; ++b)
+                        if ((hits[h].mask >> b) & 1) w |= 1ull << (b * NG + p.slot / 4);
+                }
+            }
+            units.push_back(un.u);
+        }
+        R.layer_off.push_back((int)units.size());
+    }
+    std::vector<int> roff(c->n_atoms + 1, 0), rent;
+    for (int a = 0; a < c->n_atoms; ++a) {
+        rent.insert(rent.end(), per_atom[a].begin(), per_atom[a].end());
+        roff[a + 1] = (int)rent.size();
+    }
+    R.zlen = zlen;
+    R.ncl = ncl;
+    R.n_entries = (long)ent_cand.size();
+    sparc_status st;
+    if ((st = put(c, &R.units, units)) != SPARC_OK) return st;
+    if ((st = put(c, &R.occ, occ)) != SPARC_OK) return st;
+    if ((st = put(c, &R.gm, gm)) != SPARC_OK) return st;
+    if ((st = put(c, &R.ent_cand, ent_cand)) != SPARC_OK) return st;
+    if ((st = put(c, &R.red_off, roff)) != SPARC_OK) return st;
+    return put(c, &R.red_ent, rent);
+}
+
+// The pencils of the pass and its tables.  segs: every (atom, image)
 // pair's support as line segments of the wrapped grid.
 sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, const std::vector<NlSeg>& segs) {
     const int nx = c->nx, ny = c->ny, nz = c->nz, nxy = nx * ny;
@@ -731,22 +977,15 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
         }
         return sum / *npen;
     };
-    // z ranges: the count with the least (time of a plane) x (planes one after
-    // another) on a chip that holds 512 workgroups, two per compute unit (alone
-    // on it one takes 0.65 of its time: 8.3 and 13 us a plane at 72^3), a range
-    // costing about 3 planes more than its own (set-up, ends of pairs).  Fixed
-    // here, for the context's full block, so that a column's sums do not depend
-    // on the block it comes in.
-    const int chunks = div_up(div_up(c->n_states, 16), kNlWaves);
+    // pencils and z ranges for the context's full block
+    const int tiles = div_up(c->n_states, 16), least_zs = (nz + kMaxPlanes - 1) / kMaxPlanes;
     int zs = 0;
     double best = 0;
     auto consider = [&]() {
         int npen;
         const double plane = plane_time(&npen);
-        for (int k = (nz + kMaxPlanes - 1) / kMaxPlanes; k <= std::max(1, nz / 4); ++k) {
-            const long n = (long)npen * chunks * k, last = n % 512;
-            const double rounds = n / 512 + (last == 0 ? 0.0 : (last <= 256 ? 0.65 : 1.0));
-            const double cost = plane * rounds * (div_up(nz, k) + 3);
+        for (int k = least_zs; k <= std::max(1, nz / 4); ++k) {
+            const double cost = plane * nl_cost(npen, nz, tiles, k, false, false);
             if (zs == 0 || cost < best) {
                 best = cost;
                 zs = k;
@@ -783,13 +1022,7 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
             }
         }
     }
-    const int zlen = (nz + zs - 1) / zs;
-    zs = (nz + zlen - 1) / zlen;
     // (pencil, pair, plane) -> blocks met
-    struct Hit {
-        int pencil, cand, z;
-        uint32_t mask;
-    };
     std::vector<Hit> hits;
     hits.reserve(2 * segs.size());
     for (const NlSeg& s : segs) {
@@ -806,172 +1039,116 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
         if (A.cand != B.cand) return A.cand < B.cand;
         return A.z < B.z;
     });
-    struct Span {
-        int z0, z1, cand;
-        size_t h0, h1;
-    };
-    // slots: each pair takes, for its span of planes in the unit, a free one of the
-    // group that meets the fewest further blocks for it (see the layout above); pairs beyond the slots or the local indices go to a further layer
-    // (a further pass), which supports this dense do not reach in practice
-    struct Placed {
-        int slot, local;
-        Span s;
-    };
-    struct Unit {
-        NlUnit u;
-        std::vector<Placed> p;
-    };
-    std::vector<std::vector<Unit>> layers;
-    int most = 1, ncl = 1;
-    for (int pass = 0; pass < 2; ++pass) {
-        // the first pass only counts the slots an unlimited table would take
-        const int limit = pass == 0 ? 1 << 20 : T.slots;
-        layers.clear();
-        for (size_t i = 0; i < hits.size();) {
-            size_t e = i;
-            while (e < hits.size() && hits[e].pencil == hits[i].pencil) ++e;
-            for (int zr = 0; zr < zs; ++zr) {
-                const int zb = zr * zlen, ze = std::min(nz, zb + zlen);
-                std::vector<Span> sp;
-                for (size_t h = i; h < e;) {
-                    size_t k = h;
-                    Span s{1 << 30, -1, hits[h].cand, 0, 0};
-                    for (; k < e && hits[k].cand == hits[h].cand; ++k)
-                        if (hits[k].z >= zb && hits[k].z < ze) {
-                            if (s.z1 < 0) s.h0 = k;
-                            s.z0 = std::min(s.z0, hits[k].z);
-                            s.z1 = hits[k].z;
-                            s.h1 = k + 1;
-                        }
-                    if (s.z1 >= 0) sp.push_back(s);
-                    h = k;
-                }
-                std::sort(sp.begin(), sp.end(),
-                          [](const Span& A, const Span& B) { return A.z0 != B.z0 ? A.z0 < B.z0 : A.cand < B.cand; });
-                for (int layer = 0; !sp.empty(); ++layer) {
-                    std::vector<int> end(pass == 0 ? 0 : limit, -1);   // last plane of each slot's pair
-                    std::vector<uint32_t> met((size_t)(limit / 4) * (pass == 0 ? 0 : zlen), 0);
-                    std::vector<Span> rest;
-                    Unit un;
-                    un.u = NlUnit{zb, ze, hits[i].pencil, nblk[hits[i].pencil], 0, 0};
-                    for (const Span& s : sp) {
-                        if (pass == 0) {
-                            size_t q = 0;
-                            while (q < end.size() && end[q] >= s.z0) ++q;
-                            if (q == end.size()) end.push_back(0);
-                            end[q] = s.z1;
-                            continue;
-                        }
-                        int slot = -1, fewest = 1 << 30;
-                        for (int G = 0; G < limit / 4; ++G) {
-                            int q = 4 * G;
-                            while (q < 4 * G + 4 && end[q] >= s.z0) ++q;
-                            if (q == 4 * G + 4) continue;
-                            int n = 0;   // blocks that group G would meet for this pair alone
-                            for (size_t h = s.h0; h < s.h1; ++h)
-                                n += __builtin_popcount(hits[h].mask & ~met[(size_t)G * zlen + hits[h].z - zb]);
-                            if (n < fewest) {
-                                fewest = n;
-                                slot = q;
-                            }
-                        }
-                        if (slot < 0 || un.p.size() >= (size_t)kMaxLocal) {
-                            rest.push_back(s);
-                            continue;
-                        }
-                        end[slot] = s.z1;
-                        for (size_t h = s.h0; h < s.h1; ++h) met[(size_t)(slot / 4) * zlen + hits[h].z - zb] |= hits[h].mask;
-                        un.p.push_back({slot, (int)un.p.size(), s});
-                    }
-                    un.u.ncl = (int)un.p.size();
-                    if (pass == 0) most = std::max(most, (int)end.size());
-                    else {
-                        ncl = std::max(ncl, un.u.ncl);
-                        if ((int)layers.size() <= layer) layers.emplace_back();
-                        layers[layer].push_back(std::move(un));
-                    }
-                    sp.swap(rest);
-                }
-            }
-            i = e;
+    // per pencil the pairs' hits, and the most pairs at one plane
+    std::vector<PairHits> pairs;
+    std::vector<size_t> first(npen + 1, 0);
+    int most = 1;
+    {
+        std::vector<int> live;
+        for (size_t h = 0; h < hits.size();) {
+            size_t k = h;
+            while (k < hits.size() && hits[k].pencil == hits[h].pencil && hits[k].cand == hits[h].cand) ++k;
+            if (h == 0 || hits[h].pencil != hits[h - 1].pencil) live.assign(nz, 0);
+            for (int z = hits[h].z; z <= hits[k - 1].z; ++z) most = std::max(most, ++live[z]);
+            pairs.push_back({hits[h].cand, h, k});
+            first[hits[h].pencil + 1] = pairs.size();
+            h = k;
         }
-        if (pass == 0) T.slots = most <= 8 ? 8 : (most <= 16 ? 16 : kMaxSlots);
+        for (int q = 0; q < npen; ++q) first[q + 1] = std::max(first[q + 1], first[q]);
     }
-    const int S = T.slots, NG = S / 4;
-    std::vector<NlUnit> units;
-    std::vector<uint8_t> occ;
-    std::vector<uint64_t> gm;
-    std::vector<int> ent_cand;
-    std::vector<std::vector<int>> per_atom(c->n_atoms);
-    T.layer_off.assign(1, 0);
-    for (auto& ly : layers) {
-        // units of one z range and neighbouring pencils side by side
-        std::stable_sort(ly.begin(), ly.end(), [](const Unit& A, const Unit& B) { return A.u.zb < B.u.zb; });
-        for (Unit& un : ly) {
-            un.u.ebase = (int)ent_cand.size();
-            const size_t o0 = occ.size(), g0 = gm.size();
-            occ.insert(occ.end(), (size_t)zlen * S, (uint8_t)kIdle);
-            gm.insert(gm.end(), zlen, 0);
-            for (const Placed& p : un.p) {
-                per_atom[cands[p.s.cand].atom].push_back((int)ent_cand.size());
-                ent_cand.push_back(p.s.cand);
-                for (int z = p.s.z0; z <= p.s.z1; ++z) occ[o0 + (size_t)(z - un.u.zb) * S + p.slot] = (uint8_t)p.local;
-                for (size_t h = p.s.h0; h < p.s.h1; ++h) {
-                    if (hits[h].z < un.u.zb || hits[h].z >= un.u.ze) continue;
-                    uint64_t& w = gm[g0 + hits[h].z - un.u.zb];
-                    for (int b = 0; b < kNlBlocks; ++b)
-                        if ((hits[h].mask >> b) & 1) w |= 1ull << (b * NG + p.slot / 4);
-                }
-            }
-            units.push_back(un.u);
-        }
-        T.layer_off.push_back((int)units.size());
-    }
-    std::vector<int> roff(c->n_atoms + 1, 0), rent, coff(c->n_atoms + 1, 0);
+    T.npen = npen;
+    T.slots = most <= 8 ? 8 : (most <= 16 ? 16 : kMaxSlots);
+    std::vector<int> coff(c->n_atoms + 1, 0);
     for (const NlCand& q : cands) coff[q.atom + 1]++;
     for (int a = 0; a < c->n_atoms; ++a) coff[a + 1] += coff[a];
     T.n_cand = (int)cands.size();
-    for (int a = 0; a < c->n_atoms; ++a) {
-        rent.insert(rent.end(), per_atom[a].begin(), per_atom[a].end());
-        roff[a + 1] = (int)rent.size();
-    }
-    T.zlen = zlen;
-    T.ncl = ncl;
     sparc_status st;
     SG_HIP(c, hipMalloc(&T.dummy, 256 * sizeof(double)));
     // one per column of a block at most (column groups of less than 16), two
     // blocks' worth of halves in tiles of 16 for Bloch columns
     if ((st = put(c, &T.odd, std::vector<uint32_t>(c->n_states + 1, 0))) != SPARC_OK) return st;
-    T.n_entries = (long)ent_cand.size();
-    if ((st = put(c, &T.units, units)) != SPARC_OK) return st;
+    if ((st = put(c, &T.zero, std::vector<double>(5, 0.0))) != SPARC_OK) return st;
     if ((st = put(c, &T.blk, blk)) != SPARC_OK) return st;
-    if ((st = put(c, &T.occ, occ)) != SPARC_OK) return st;
-    if ((st = put(c, &T.gm, gm)) != SPARC_OK) return st;
-    if ((st = put(c, &T.ent_cand, ent_cand)) != SPARC_OK) return st;
     if ((st = put(c, &T.cand, cands)) != SPARC_OK) return st;
-    if ((st = put(c, &T.red_off, roff)) != SPARC_OK) return st;
-    if ((st = put(c, &T.red_ent, rent)) != SPARC_OK) return st;
     if ((st = put(c, &T.cand_off, coff)) != SPARC_OK) return st;
-    double groups = 0;
-    for (uint64_t w : gm) groups += __builtin_popcountll(w);
-    if (c->debug)
-        fprintf(stderr,
-                "[sparc_gpu] nonlocal pass: %d pencils, %zu units of %d planes, %d slots (%d used), %zu layers, %ld "
-                "entries, at most %d pairs per unit, %.2f groups per block\n",
-                npen, units.size(), zlen, S, most, layers.size(), T.n_entries, ncl, groups / ((double)nb * nz));
+    // the ranges of the full block, then those that suit 1, 2, 4, ... column tiles
+    std::vector<int> cuts{zs};
+    for (int t = 1; t < tiles; t *= 2)
+        for (bool fp32 : {false, true}) {
+            int best_k = zs;
+            double least = 0;
+            for (int k = least_zs; k <= std::max(1, nz / 4); ++k) {
+                const double cost = std::min(nl_cost(npen, nz, t, k, false, fp32), nl_cost(npen, nz, t, k, true, fp32));
+                if (k == least_zs || cost < least) {
+                    least = cost;
+                    best_k = k;
+                }
+            }
+            if (std::find(cuts.begin(), cuts.end(), best_k) == cuts.end()) cuts.push_back(best_k);
+        }
+    for (int k : cuts) {
+        T.ranges.emplace_back();
+        if ((st = build_ranges(c, cands, hits, pairs, first, nblk, k, T.ranges.back())) != SPARC_OK) return st;
+        const NlRanges& R = T.ranges.back();
+        if (c->debug)
+            fprintf(stderr,
+                    "[sparc_gpu] nonlocal pass: %d pencils, %d units of %d planes, %d slots (%d used), %zu layers, %ld "
+                    "entries, at most %d pairs per unit\n",
+                    npen, R.layer_off.back(), R.zlen, T.slots, most, R.layer_off.size() - 1, R.n_entries, R.ncl);
+    }
     return SPARC_OK;
 }
 
+// Runs of entries that k_nl_reduce sums side by side: as many as the threads of a
+// workgroup allow for ncol columns.
+static int reduce_runs(int ncol) {
+    int parts = 1;
+    while (parts < 16 && 8 * parts * ncol <= 256) parts *= 2;
+    return parts;
+}
+
+// Ranges and waves of a pass over ncol columns: the cheapest by nl_cost of the
+// ranges that were built; other than those of the full block only where their
+// partial sums fit the fixed scratch array, so that the allocation-free filter
+// takes the same.
+struct NlShape {
+    const NlRanges* R;
+    int nw;   // partial entries of a unit and pair (waves that share the blocks)
+};
+static NlShape nl_shape(sparc_gpu_ctx c, int ncol, bool fp32) {
+    const NlPass& N = c->nlp;
+    NlShape best{&N.ranges[0], 1};
+    double least = 0;
+    for (const NlRanges& R : N.ranges)
+        for (int nw : {1, kNlSplit}) {
+            const bool full = &R == &N.ranges[0] && nw == 1;
+            if (!full && (size_t)R.n_entries * nw * 4 * ncol > c->scratch_elems) continue;
+            // the sum over an atom's entries takes 0.023 planes per entry and run
+            const double cost = nl_cost(N.npen, c->nz, div_up(ncol, 16), div_up(c->nz, R.zlen), nw > 1, fp32) +
+                                0.023 * R.n_entries * nw / c->n_atoms / reduce_runs(ncol);
+            if (full || cost < least) {
+                least = cost;
+                best = NlShape{&R, nw};
+            }
+        }
+    return best;
+}
+
 template <typename T, typename C, int S>
-static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, bool ap, bool pr, size_t shmem) {
+static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, int nw, bool ap, bool pr, size_t shmem) {
+    constexpr int NB = kNlBlocks, WB = kNlBlocks / kNlSplit;
     const long nblocks = 8L * div_up(a.nunit, 8) * a.nchunk;
     if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "nonlocal pass: too many blocks");
-    const dim3 g((unsigned)nblocks), b(64 * std::max(4, a.nwc));
-    if (!ap) k_nl_pass<T, C, S, false, true, false><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail && pr) k_nl_pass<T, C, S, true, true, true><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail) k_nl_pass<T, C, S, true, false, true><<<g, b, shmem, c->stream>>>(a);
-    else if (pr) k_nl_pass<T, C, S, true, true, false><<<g, b, shmem, c->stream>>>(a);
-    else k_nl_pass<T, C, S, true, false, false><<<g, b, shmem, c->stream>>>(a);
+    const dim3 g((unsigned)nblocks), b(64 * kNlWaves);
+    if (nw > 1) {
+        if (!ap) k_nl_pass<T, C, S, WB, false, true, false><<<g, b, shmem, c->stream>>>(a);
+        else if (pr) k_nl_pass<T, C, S, WB, true, true, true><<<g, b, shmem, c->stream>>>(a);
+        else k_nl_pass<T, C, S, WB, true, false, true><<<g, b, shmem, c->stream>>>(a);
+    } else if (!ap) k_nl_pass<T, C, S, NB, false, true, false><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail && pr) k_nl_pass<T, C, S, NB, true, true, true><<<g, b, shmem, c->stream>>>(a);
+    else if (a.tail) k_nl_pass<T, C, S, NB, true, false, true><<<g, b, shmem, c->stream>>>(a);
+    else if (pr) k_nl_pass<T, C, S, NB, true, true, false><<<g, b, shmem, c->stream>>>(a);
+    else k_nl_pass<T, C, S, NB, true, false, false><<<g, b, shmem, c->stream>>>(a);
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;
 }
@@ -993,7 +1170,7 @@ static sparc_status partials(sparc_gpu_ctx c, size_t need, double** part) {
 }
 
 template <typename T, typename C>
-static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
+static NlArgs<T, C> pass_args(sparc_gpu_ctx c, const NlRanges& R, long ldx, int mode, int step) {
     const NlPass& N = c->nlp;
     NlArgs<T, C> a;
     a.y = nullptr;
@@ -1006,12 +1183,12 @@ static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
     a.nz = c->nz;
     a.nxy = c->nx * c->ny;
     a.ncol = 0;
-    a.zlen = N.zlen;
-    a.ncl = N.ncl;
+    a.zlen = R.zlen;
+    a.ncl = R.ncl;
     a.blk = N.blk;
     a.tail = a.nxy % 16;
     a.dummy = reinterpret_cast<T*>(N.dummy);
-    a.ent_cand = N.ent_cand;
+    a.ent_cand = R.ent_cand;
     a.cand = N.cand;
     a.hx = c->hx;
     a.hy = c->hy;
@@ -1025,6 +1202,8 @@ static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
     a.odd = N.odd;
     a.epoch = N.epoch;
     a.part = nullptr;
+    a.zero = reinterpret_cast<const C*>(N.zero);
+    a.alpha = N.zero + 4;
     a.params = c->scal + S_A;
     a.mode = mode;
     a.step = step;
@@ -1032,49 +1211,53 @@ static NlArgs<T, C> pass_args(sparc_gpu_ctx c, long ldx, int mode, int step) {
 }
 
 template <typename T, typename C>
-static NlSupport<T> support(sparc_gpu_ctx c, const NlArgs<T, C>& a, uint32_t epoch) {
-    return NlSupport<T>{a.y,  a.ldx, a.nx,       a.ny,    a.nz,   a.hx,  a.hy, a.hz, a.inv_rc2,
-                        a.N0, a.N1,  c->rcut_nl, a.rcut2, a.cand, a.odd, epoch};
+static NlSupport<T> support(sparc_gpu_ctx c, const NlArgs<T, C>& a) {
+    return NlSupport<T>{a.y,  a.ldx,      a.nx,    a.ny,   a.nz,  a.hx,        a.hy,          a.hz, a.inv_rc2, a.N0,
+                        a.N1, c->rcut_nl, a.rcut2, a.cand, a.odd, a.epoch + 1, a.alpha};
 }
 
 // The pass over the columns set in a; with further layers every apply comes
 // before the first projection.
 template <typename T, typename C>
-static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, bool ap, bool pr) {
-    const NlPass& N = c->nlp;
-    const size_t shmem = nl_lds_layout(sizeof(C), N.slots, N.zlen, N.ncl).total;
+static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, bool ap, bool pr) {
+    const NlRanges& R = *sh.R;
+    const int S = c->nlp.slots;
+    const size_t shmem = nl_lds_layout(sizeof(C), S, R.zlen, R.ncl).total;
     if (shmem > 160 * 1024) return set_err(c, SPARC_ERR_ARG, "nonlocal pass needs more than 160 KB of LDS");
     const int tiles = div_up(a.ncol, 16);
-    a.nchunk = div_up(tiles, kNlWaves);
+    a.nchunk = sh.nw > 1 ? tiles : div_up(tiles, kNlWaves);
     a.nwc = div_up(tiles, a.nchunk);
-    const int nl = (int)N.layer_off.size() - 1;
+    const int nl = (int)R.layer_off.size() - 1;
     for (int half = 0; half < (nl > 1 ? 2 : 1); ++half) {
         const bool ap1 = ap && half == 0, pr1 = pr && (nl == 1 || half == 1);
         if (!ap1 && !pr1) continue;
         for (int l = 0; l < nl; ++l) {
-            const long u0 = N.layer_off[l];
-            a.nunit = N.layer_off[l + 1] - (int)u0;
-            a.units = N.units + u0;
-            a.occ = N.occ + u0 * N.zlen * N.slots;
-            a.gm = N.gm + u0 * N.zlen;
-            sparc_status st = N.slots == 8    ? launch_pass<T, C, 8>(c, a, ap1, pr1, shmem)
-                              : N.slots == 16 ? launch_pass<T, C, 16>(c, a, ap1, pr1, shmem)
-                                              : launch_pass<T, C, kMaxSlots>(c, a, ap1, pr1, shmem);
+            const long u0 = R.layer_off[l];
+            a.nunit = R.layer_off[l + 1] - (int)u0;
+            a.units = R.units + u0;
+            a.occ = R.occ + u0 * R.zlen * S;
+            a.gm = R.gm + u0 * R.zlen;
+            sparc_status st = S == 8    ? launch_pass<T, C, 8>(c, a, sh.nw, ap1, pr1, shmem)
+                              : S == 16 ? launch_pass<T, C, 16>(c, a, sh.nw, ap1, pr1, shmem)
+                                        : launch_pass<T, C, kMaxSlots>(c, a, sh.nw, ap1, pr1, shmem);
             if (st != SPARC_OK) return st;
         }
     }
     return SPARC_OK;
 }
 
-// One pass over a block: apply (y += alpha chi D, alpha that of filter step
-// `step` of mode `mode`) and / or project (D = gamma dV chi^T y).
+// One pass over a block: apply (y += chi D) and / or project (D = alpha gamma dV
+// chi^T y, alpha that of filter step `step` of mode `mode`, which will apply it).
 template <typename T>
 sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step, double* part,
                      size_t part_elems) {
     const NlPass& N = c->nlp;
-    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
+    if (N.ranges.empty() || N.ranges[0].n_entries == 0 || ncol == 0) return SPARC_OK;
     sparc_status st;
-    const size_t per_col = (size_t)N.n_entries * 4;
+    const NlShape sh = nl_shape(c, ncol, sizeof(T) == 4);
+    const NlRanges& R = *sh.R;
+    const int runs = reduce_runs(ncol);
+    const size_t per_col = (size_t)R.n_entries * sh.nw * 4;
     int group = ncol;
     if (pr && part) {
         // caller memory: as many columns at a time as it holds, whole
@@ -1086,7 +1269,7 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
     } else if (pr) {
         if ((st = partials(c, per_col * ncol, &part)) != SPARC_OK) return st;
     }
-    NlArgs<T, T> a = pass_args<T, T>(c, ldx, mode, step);
+    NlArgs<T, T> a = pass_args<T, T>(c, R, ldx, mode, step);
     a.ldD = 4L * c->n_atoms;
     a.part = part;
     const int slot = prof_begin(c, PK_PROJ);
@@ -1096,11 +1279,11 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
         a.odd = N.odd + (group < 16 ? c0 : c0 / 16);
         T* D = D_of<T>(c) + (long)c0 * a.ldD;
         a.D = D;
-        if ((st = run_layers<T, T>(c, a, ap, pr)) != SPARC_OK) return st;
+        if ((st = run_layers<T, T>(c, a, sh, ap, pr)) != SPARC_OK) return st;
         if (pr) {
-            k_nl_reduce<T><<<dim3(c->n_atoms, div_up(4L * a.ncol, 256)), 256, 0, c->stream>>>(
-                part, a.ncol, N.red_off, N.red_ent, N.cand_off, support(c, a, a.epoch + 1), c->nl.gamma4, c->dV, D,
-                a.ldD);
+            k_nl_reduce<T><<<dim3(c->n_atoms, div_up(4L * a.ncol, 256 / runs)), 256, 0, c->stream>>>(
+                part, a.ncol, sh.nw, runs, R.red_off, R.red_ent, N.cand_off, support(c, a), c->nl.gamma4,
+                c->dV, D, a.ldD);
             SG_CHECK_LAUNCH(c);
         }
     }
@@ -1117,10 +1300,13 @@ template sparc_status nl_pass<float>(sparc_gpu_ctx, float*, int, long, bool, boo
 template <typename T>
 sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step) {
     const NlPass& N = c->nlp;
-    if (N.n_entries == 0 || ncol == 0) return SPARC_OK;
+    if (N.ranges.empty() || N.ranges[0].n_entries == 0 || ncol == 0) return SPARC_OK;
     sparc_status st;
+    const NlShape sh = nl_shape(c, 2 * ncol, false);
+    const NlRanges& R = *sh.R;
+    const int runs = reduce_runs(ncol);
     double* part = nullptr;
-    if (pr && (st = partials(c, (size_t)N.n_entries * 4 * 2 * ncol, &part)) != SPARC_OK) return st;
+    if (pr && (st = partials(c, (size_t)R.n_entries * sh.nw * 4 * 2 * ncol, &part)) != SPARC_OK) return st;
     const long ldD = 4L * N.n_cand;
     if (c->kp_D_elems < (size_t)ldD * 2 * ncol) {
         if (c->kp_D) {
@@ -1142,7 +1328,7 @@ sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool 
         for (int d = 0; d < 3; ++d) c->kp_phase_k[d] = k[d];
         c->kp_phase_valid = 1;
     }
-    NlArgs<T, double> a = pass_args<T, double>(c, ldx, mode, step);
+    NlArgs<T, double> a = pass_args<T, double>(c, R, ldx, mode, step);
     a.halves = 1;
     a.by_pair = 1;
     a.ldD = ldD;
@@ -1150,11 +1336,11 @@ sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool 
     a.ncol = 2 * ncol;
     a.y = y;
     a.D = c->kp_D;
-    if ((st = run_layers<T, double>(c, a, ap, pr)) != SPARC_OK) return st;
+    if ((st = run_layers<T, double>(c, a, sh, ap, pr)) != SPARC_OK) return st;
     if (pr) {
-        k_nl_reduce_k<T><<<dim3(c->n_atoms, div_up(4L * ncol, 256)), 256, 0, c->stream>>>(
-            part, ncol, N.red_off, N.red_ent, N.ent_cand, N.cand_off, support(c, a, a.epoch + 1), a.half, c->kp_phase,
-            c->nl.gamma4, c->dV, c->kp_D, ldD);
+        k_nl_reduce_k<T><<<dim3(c->n_atoms, div_up(4L * ncol, 256 / runs)), 256, 0, c->stream>>>(
+            part, ncol, sh.nw, runs, R.red_off, R.red_ent, R.ent_cand, N.cand_off, support(c, a), a.half,
+            c->kp_phase, c->nl.gamma4, c->dV, c->kp_D, ldD);
         SG_CHECK_LAUNCH(c);
         ++c->nlp.epoch;
     }

@@ -530,13 +530,13 @@ __global__ void k_copy_block(const T* __restrict__ src, T* __restrict__ dst, lon
 template <typename T>
 sparc_status filter_impl(sparc_gpu_ctx c, T* X, T* Wk, int ncol, long ldx, int m, double* part, size_t part_elems) {
     sparc_status st;
-    if ((st = nl_pass<T>(c, X, ncol, ldx, false, true, 0, 0, part, part_elems)) != SPARC_OK) return st;
+    if ((st = nl_pass<T>(c, X, ncol, ldx, false, true, 1, 1, part, part_elems)) != SPARC_OK) return st;
     for (int k = 1; k <= m; ++k) {
         T* cur = (k % 2 == 0) ? Wk : X;   // Y_{k-1}
         T* dst = (k % 2 == 0) ? X : Wk;   // Y_{k-2}, overwritten with Y_k
         const int mode = k == 1 ? 1 : 2;
         if ((st = launch_hsweep<T>(c, cur, dst, k == 1 ? nullptr : dst, ncol, ldx, mode, k)) != SPARC_OK) return st;
-        if ((st = nl_pass<T>(c, dst, ncol, ldx, true, k < m, mode, k, part, part_elems)) != SPARC_OK) return st;
+        if ((st = nl_pass<T>(c, dst, ncol, ldx, true, k < m, 2, k + 1, part, part_elems)) != SPARC_OK) return st;
     }
     if (m % 2 == 1) {
         dim3 grid(div_up(c->nd, 256), ncol);

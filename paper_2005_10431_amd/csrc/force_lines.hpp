@@ -58,8 +58,9 @@ __host__ __device__ inline bool force_advance(const ForceBox& b, ForceStep& s, i
         }
         if (s.k >= b.nzb) return false;
         const float dy = (float)((b.ly + s.j) * b.hy - b.cy), dz = (float)((b.lz + s.k) * b.hz - b.cz);
-        const float in2 = b.r2 - dy * dy - dz * dz;
-        const float half = sqrtf((in2 > 0.0f ? in2 : 0.0f) + 1e-6f * b.r2) * b.per_h + 0.02f;
+        const float in2 = b.r2 - dy * dy - dz * dz + 1e-6f * b.r2;
+        if (in2 < 0.0f) continue;
+        const float half = sqrtf(in2) * b.per_h + 0.02f;
         const int lo = (int)ceilf(b.fx - half), hi = (int)floorf(b.fx + half);
         s.next = uniform(lo > 0 ? lo : 0);
         s.last = uniform(hi < b.nxb - 1 ? hi : b.nxb - 1);

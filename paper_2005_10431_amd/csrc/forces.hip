@@ -10,6 +10,8 @@
 // around the atom, wrapped to the periodic grid for field values.
 // Reductions are in fixed order (no value atomics), so results are
 // bitwise reproducible.
+#include <type_traits>
+
 #include "force_lines.hpp"
 #include "internal.hpp"
 #include "mfma.hpp"
@@ -143,12 +145,12 @@ __global__ __launch_bounds__(256) void k_force_overlap(ForceTab tab, int n_atoms
 constexpr int kForceTiles = 5;   // 16-column tiles of a workgroup at most
 
 // Projections of the columns on the atom's projectors and their gradients:
-// pd[(a ncol + col) 16 + q] with q = k (chi_k^T psi, k = s, px, py, pz) and
-// q = 4 + 3 k + d ((d/dx_d chi_k)^T psi), each times dV.
+// pd[((part n_atoms + a) ncol + col) 16 + q] with q = k (chi_k^T psi, k = s, px, py, pz) and
+// q = 4 + 3 k + d ((d/dx_d chi_k)^T psi), each times dV; parts are added later.
 //
 // The 16 functions of an atom are the rows of one FP64 MFMA tile.  A workgroup
-// takes an atom and up to 80 columns; its waves take every fourth x-line of the
-// atom's sphere, 24 points at a time with the next ones' loads in flight, and for
+// takes an atom, up to 80 columns (TL tiles of 16) and one of `parts` shares of the
+// x-lines of the atom's sphere, its waves every (4 parts)-th of them, 24 points at a time with the next ones' loads in flight, and for
 // each point every lane forms the one function of its row,
 //   f_q = exp(-r^2 / rc^2) (c0 + c1 u v),   u, v each 1, dx, dy or dz,
 // which all columns then share.  Reading is what bounds it: the lanes
@@ -158,15 +160,15 @@ constexpr int kForceTiles = 5;   // 16-column tiles of a workgroup at most
 // four columns per thread; 1.27 on the matrix cores with loads of single points,
 // 1.11 with pairs (the products alone would take 0.13).  Neighbouring atoms on one
 // XCD made no difference.
-template <typename T>
+template <typename T, int TL>
 __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ X, long ldx, int ncol, ForceTab tab,
                                                           int nx, int ny, int nz, double hx, double hy, double hz,
                                                           double rc, double rcut, double N0, double N1, double dV,
-                                                          double* __restrict__ pd, int tiles) {
-    constexpr int CH = kForcePoints / 8, TL = kForceTiles;   // 8-point chunks of a step, 16-column tiles
+                                                          double* __restrict__ pd) {
+    constexpr int CH = kForcePoints / 8;   // 8-point chunks of a step
     __shared__ double ex[3][256];   // Gaussian factors along the box's axes (at most 255 points)
     __shared__ double red[4][16][16 * TL];
-    const int a = blockIdx.x, col0 = 16 * tiles * blockIdx.y;
+    const int a = blockIdx.x, col0 = 16 * TL * blockIdx.y, parts = gridDim.z, part = blockIdx.z;
     const double cx = tab.pos[3 * a], cy = tab.pos[3 * a + 1], cz = tab.pos[3 * a + 2];
     const ForceBox B = force_box(cx, cy, cz, hx, hy, hz, rcut);
     const int lx = B.lx, ly = B.ly, lz = B.lz;
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
     const double u1 = ku < 0 ? 1.0 : 0.0, uX = ku == 0 ? 1.0 : 0.0, uY = ku == 1 ? 1.0 : 0.0, uZ = ku == 2 ? 1.0 : 0.0;
     const double v1 = kv < 0 ? 1.0 : 0.0, vX = kv == 0 ? 1.0 : 0.0, vY = kv == 1 ? 1.0 : 0.0, vZ = kv == 2 ? 1.0 : 0.0;
     // columns past the last repeat it and are not stored
-    const int nt = min(tiles, (ncol - col0 + 15) / 16);
+    const int nt = min(TL, (ncol - col0 + 15) / 16);
     const T* xc[TL];
 #pragma unroll
     for (int k = 0; k < TL; ++k) xc[k] = X + (long)min(ncol - 1, col0 + 16 * min(k, nt - 1) + li) * ldx;
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
         int x0;
     };
     auto advance = [&](Step& s) -> bool {
-        if (!force_advance(B, s, 4, [](int v) { return __builtin_amdgcn_readfirstlane(v); })) return false;
+        if (!force_advance(B, s, 4 * parts, [](int v) { return __builtin_amdgcn_readfirstlane(v); })) return false;
         s.x0 = wrap(lx + s.i0, nx);
         return true;
     };
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
             }
         }
     };
-    Step s{{__builtin_amdgcn_readfirstlane((t >> 6) - 4), 0, 0, 0, 1, 0}, 0};
+    Step s{{__builtin_amdgcn_readfirstlane(4 * part + (t >> 6) - 4 * parts), 0, 0, 0, 1, 0}, 0};
     vec xa[CH][TL], xb[CH][TL];
     bool more = advance(s);
     if (more) load(s, xa);
@@ -272,22 +274,30 @@ __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ 
     for (int e = t; e < 256 * nt; e += blockDim.x) {
         const int q = e & 15, c = e >> 4;
         if (col0 + c < ncol)
-            pd[((long)a * ncol + col0 + c) * 16 + q] =
+            pd[(((long)part * gridDim.x + a) * ncol + col0 + c) * 16 + q] =
                 dV * (red[0][q][c] + red[1][q][c] + red[2][q][c] + red[3][q][c]);
     }
 }
 
-// out[3 a + d] += 2 sum_n w_n sum_k gamma_k P_k D_kd (one block per atom;
-// columns in fixed order per thread, then the fixed-order block reduction)
-__global__ __launch_bounds__(256) void k_force_nl_reduce(const double* __restrict__ pd, int ncol,
+// out[3 a + d] += 2 sum_n w_n sum_k gamma_k P_k D_kd (one block per atom; the parts
+// of P and D in order, columns in fixed order per thread, then the fixed-order
+// block reduction)
+__global__ __launch_bounds__(256) void k_force_nl_reduce(const double* __restrict__ pd, int ncol, int parts,
                                                         const double* __restrict__ w, ForceTab tab,
                                                         double* __restrict__ out) {
     const int a = blockIdx.x;
     double acc[3] = {0.0, 0.0, 0.0};
     for (int n = threadIdx.x; n < ncol; n += blockDim.x) {
-        const double* v = pd + ((long)a * ncol + n) * 16;
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = pd[((long)a * ncol + n) * 16 + q];
+        for (int p = 1; p < parts; ++p)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] += pd[(((long)p * gridDim.x + a) * ncol + n) * 16 + q];
+#pragma unroll
         for (int k = 0; k < 4; ++k) {
             const double cpk = 2.0 * tab.gamma4[4 * a + k] * w[n] * v[k];
+#pragma unroll
             for (int d = 0; d < 3; ++d) acc[d] += cpk * v[4 + 3 * k + d];
         }
     }
@@ -321,17 +331,51 @@ sparc_status ensure_force_tables(sparc_gpu_ctx c) {
 
 namespace {
 
+// Tiles of a workgroup, chunks of columns and parts of a sphere.  A chip holds 512
+// workgroups, and the last ones run on after the others for about 0.6 of their
+// time; a part costs 0.03 spheres more than its lines (set-up, the sum over the
+// waves).  In one part few atoms or columns leave the chip idle: 4 atoms x 12
+// columns 521 and now 209 us with the local part, 46 x 77 600 and 288, 108 x 16 723
+// and 340; 108 x 260 fills it unevenly (1302 us in one part, 1124 in 3, 1146 in 4).
+struct ForceGrid {
+    int tiles, chunks, parts;
+};
+ForceGrid force_grid(int n_atoms, int ncol) {
+    const int tiles = div_up(ncol, 16);
+    ForceGrid g;
+    g.chunks = div_up(tiles, kForceTiles);
+    g.tiles = div_up(tiles, g.chunks);
+    g.parts = 1;
+    double least = 0;
+    for (int p = 1; p <= 16; ++p) {
+        const double rounds = (double)n_atoms * g.chunks * p / 512, cost = (rounds + 0.6) / p + 0.03 * rounds;
+        if (p == 1 || cost < least) {
+            least = cost;
+            g.parts = p;
+        }
+    }
+    return g;
+}
+
 template <typename T>
 sparc_status nl_force(sparc_gpu_ctx c, const T* X, int ncol, long ldx, const double* w, double* pd, double* out) {
     const ForceTab tab = force_tab(c);
     const double rc = c->rc_nl;
     const double N0 = std::pow(2.0 / (kPi * rc * rc), 0.75);
     const double N1 = (2.0 / rc) * N0;
-    const int tiles = div_up(ncol, 16), chunks = div_up(tiles, kForceTiles);
-    k_force_nl_proj<T><<<dim3(c->n_atoms, chunks), 256, 0, c->stream>>>(
-        X, ldx, ncol, tab, c->nx, c->ny, c->nz, c->hx, c->hy, c->hz, rc, c->rcut_nl, N0, N1, c->dV, pd,
-        div_up(tiles, chunks));
-    k_force_nl_reduce<<<c->n_atoms, 256, 0, c->stream>>>(pd, ncol, w, tab, out);
+    const ForceGrid G = force_grid(c->n_atoms, ncol);
+    auto go = [&](auto tl) {
+        k_force_nl_proj<T, tl()><<<dim3(c->n_atoms, G.chunks, G.parts), 256, 0, c->stream>>>(
+            X, ldx, ncol, tab, c->nx, c->ny, c->nz, c->hx, c->hy, c->hz, rc, c->rcut_nl, N0, N1, c->dV, pd);
+    };
+    switch (G.tiles) {
+        case 1: go(std::integral_constant<int, 1>()); break;
+        case 2: go(std::integral_constant<int, 2>()); break;
+        case 3: go(std::integral_constant<int, 3>()); break;
+        case 4: go(std::integral_constant<int, 4>()); break;
+        default: go(std::integral_constant<int, kForceTiles>()); break;
+    }
+    k_force_nl_reduce<<<c->n_atoms, 256, 0, c->stream>>>(pd, ncol, G.parts, w, tab, out);
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;
 }
@@ -362,7 +406,7 @@ sparc_status sparc_gpu_forces(sparc_gpu_ctx c, const double* d_phi, sparc_prec p
     sparc_status st;
     if ((st = ensure_force_tables(c)) != SPARC_OK) return st;
     const int na = c->n_atoms;
-    const size_t need = std::max((size_t)na * kLocalChunks * 3, nl ? (size_t)na * ncol * 16 : 0);
+    const size_t need = std::max((size_t)na * kLocalChunks * 3, nl ? (size_t)na * ncol * 16 * force_grid(na, ncol).parts : 0);
     if ((st = ensure_red(c, need)) != SPARC_OK) return st;
     const ForceTab tab = force_tab(c);
     int slot = prof_begin(c, PK_FORCE_LOCAL);

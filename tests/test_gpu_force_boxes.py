@@ -33,3 +33,16 @@ def test_force_boxes_below_the_spacing(rcut, dtype):
     got = _gpu_forces(torch, s, phi, blocks, w, dtype=getattr(torch, dtype))
     ref = forces.forces(s, phi, blocks, w)
     assert np.max(np.abs(got - ref)) <= 1e-11 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("ncol", [33, 49, 65, 97])
+def test_force_tiles_and_parts(ncol):
+    """Three, four and five 16-column tiles in a workgroup and two chunks of
+    four, on spheres that few atoms leave to many workgroups."""
+    torch = require_gpu()
+    s = ragged_system(n_states=97)
+    phi, blocks, w = _inputs(s, ncol, 6)
+    log(f"force tiles: {ncol} columns")
+    got = _gpu_forces(torch, s, phi, blocks, w)
+    ref = forces.forces(s, phi, blocks, w)
+    assert np.max(np.abs(got - ref)) <= 1e-11 * np.max(np.abs(ref))

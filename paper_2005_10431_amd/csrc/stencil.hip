@@ -102,7 +102,9 @@ __device__ __forceinline__ void each_phase(F& f, int z0, int ze, std::integer_se
 
 // The sweep.  MODE: 0 out = H_loc x; 1 first filter step; 2 filter step `step`
 // (>= 2) with xprev = X_{k-1} (may alias out).  VX: points per thread, a
-// divisor of n_x.  HM: halo vectors per thread and plane.
+// divisor of n_x.  HM: halo vectors per thread and plane.  Where PQ planes of them
+// would spill (PH) they are loaded one plane ahead (256 x 40 x 40 x 100 in FP64, a
+// filter step: 489 us with two planes, now 383; 200 x 64 x 64 x 120: 883 and 687).
 //
 // One z-plane step at ring phase U (z = z0 + U).  On entry the LDS buffer of
 // parity U holds plane z (own rows with x-wrap padding and halo rows), written
@@ -127,6 +129,8 @@ __global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_
     constexpr int NO = kMaxHalfOrder;
     constexpr int RING = kRing, PR = kRingAhead, PQ = kQueue;
     constexpr int PAD = sweep_pad(VX);
+    constexpr bool tight = !BL && VX * sizeof(T) == 16 && (HM == 3 || (HM == 2 && MODE == 2 && sizeof(T) == 8));
+    constexpr int PH = tight ? 1 : PQ;   // planes that halo rows are loaded ahead
     using gv = typename VecOf<T, VX, sizeof(T)>::type;        // in global memory
     using rv = typename VecOf<T, VX, VX * sizeof(T)>::type;   // in registers and LDS
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -239,7 +243,7 @@ __global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_
     auto wz = [nz](int z) { return z >= nz ? z - nz : (z < 0 ? z + nz : z); };
 
     rv q[RING];
-    rv hq[PQ][HM];
+    rv hq[PH][HM];
     rv xp[PQ], ve[PQ];
     // Bloch: other half of the ring plane loaded last, of the x edges and of the halo rows
     rv oz, ox[PQ], oh[PQ][HM];
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_
         ve[j] = ld(a.veff + pxy + zo);
     }
 #pragma unroll
-    for (int j = 1; j < PQ; ++j)
+    for (int j = 1; j < PH; ++j)
 #pragma unroll
         for (int i = 0; i < HM; ++i) hq[j][i] = ld(xc + goff[i] + (long)wz(zb + j) * plane);
     auto edge_at = [&](int z) { return wedge ? xo + pxy + (long)wz(z) * plane : xo; };

@@ -56,6 +56,7 @@ struct NlRanges {
     int* red_ent = nullptr;
     int zlen = 1, ncl = 1;
     long n_entries = 0;
+    bool whole = false;          // one layer, whose units hold every point of the grid
     std::vector<int> layer_off;  // unit ranges of the layers
 };
 struct NlPass {
@@ -239,24 +240,31 @@ enum Flag {
 
 // ---- kernels (launchers) -------------------------------------------------
 // Local part of H / Chebyshev sweeps. mode: 0 out = H_loc x; 1 first filter
-// step; 2 filter step `step` (>= 2) with xprev = X_{k-1} (may alias out).
+// step; 2 filter step `step` (>= 2) with xprev = X_{k-1} (may alias out), and with
+// step 0 out = H_loc x + xprev.
 // halves: column j is half j % 2 (N_d rows) of Bloch column j / 2, at the
 // context's k.
 template <typename T>
 sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, int ncol, long ldx,
                            int mode, int step, bool halves = false);
-// The nonlocal term of a block in one pass: apply (y += chi D) and / or project (D =
-// alpha gamma dV chi^T y of the completed y, alpha that of the filter step (mode,
-// step) that will apply it, 1 for mode 0).  The partial sums go to `part`
+// The nonlocal term of a block in one pass: apply (add: y += chi D; write: y = chi D,
+// only where nl_writes says so) and / or project (D = alpha gamma dV chi^T y of the
+// completed y, alpha that of the filter step (mode, step) that will apply it, 1
+// for mode 0).  The partial sums go to `part`
 // (part_elems doubles, as many columns at a time as fit) when given, else to
 // context memory sized for the whole block.  Does nothing without projectors.
+enum class NlApply { no, add, write };
 template <typename T>
-sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool apply, bool project, int mode, int step,
+sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply apply, bool project, int mode, int step,
                      double* part = nullptr, size_t part_elems = 0);
-// The same for ncol Bloch columns [u; v] at the context's k, in FP64 arithmetic
+// Whether H X had better let the pass over ncol real columns (halves of Bloch
+// columns) write y before the sweep adds to it: it has projectors, whose units
+// hold every point, and the shape is right.
+bool nl_writes(sparc_gpu_ctx c, int ncol, bool fp32, bool bloch);
+// The pass for ncol Bloch columns [u; v] at the context's k, in FP64 arithmetic
 // for both block precisions.
 template <typename T>
-sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool apply, bool project, int mode, int step);
+sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply apply, bool project, int mode, int step);
 // Y = H X
 template <typename T>
 sparc_status apply_impl(sparc_gpu_ctx c, const T* X, T* Y, int ncol, long ldx);
@@ -270,12 +278,14 @@ sparc_status filter_impl(sparc_gpu_ctx c, T* X, T* Wk, int ncol, long ldx, int m
 //   sigma_k = 1/(tau - sigma_{k-1});
 //   step 1: out = (sigma_1/e)(Hx - c x)
 //   step k: out = (2 sigma_k/e)(Hx - c x) - sigma_{k-1} sigma_k xprev
+// and of mode 2, step 0: out = Hx + xprev.
 __device__ inline void filter_coefs(const double* params, int mode, int step, double& alpha, double& cshift,
                                     double& beta) {
     alpha = 1.0;
     cshift = 0.0;
     beta = 0.0;
-    if (mode == 0) return;
+    if (mode == 2 && step == 0) beta = 1.0;
+    if (mode == 0 || step == 0) return;
     double A = params[0], B = params[1], A0 = params[2];
     double e = 0.5 * (B - A), c = 0.5 * (B + A);
     double s1 = e / (A0 - c);

@@ -106,11 +106,15 @@ sparc_status kp_nl_bounds(sparc_gpu_ctx c, const double* k, double* nl_lo, doubl
 
 template <typename T>
 sparc_status bloch_apply_impl(sparc_gpu_ctx c, const T* X, T* Y, int ncol, long ldx) {
-    // the projecting pass only reads X
-    sparc_status st = nl_pass_k<T>(c, const_cast<T*>(X), ncol, ldx, false, true, 0, 0);
+    // the projecting pass only reads X; then as at the Gamma point
+    sparc_status st = nl_pass_k<T>(c, const_cast<T*>(X), ncol, ldx, NlApply::no, true, 0, 0);
     if (st != SPARC_OK) return st;
+    if (nl_writes(c, 2 * ncol, sizeof(T) == 4, true)) {
+        if ((st = nl_pass_k<T>(c, Y, ncol, ldx, NlApply::write, false, 0, 0)) != SPARC_OK) return st;
+        return launch_hsweep<T>(c, X, Y, Y, 2 * ncol, ldx, 2, 0, true);
+    }
     if ((st = launch_hsweep<T>(c, X, Y, nullptr, 2 * ncol, ldx, 0, 0, true)) != SPARC_OK) return st;
-    return nl_pass_k<T>(c, Y, ncol, ldx, true, false, 0, 0);
+    return nl_pass_k<T>(c, Y, ncol, ldx, NlApply::add, false, 0, 0);
 }
 template sparc_status bloch_apply_impl<double>(sparc_gpu_ctx, const double*, double*, int, long);
 template sparc_status bloch_apply_impl<float>(sparc_gpu_ctx, const float*, float*, int, long);
@@ -120,14 +124,14 @@ template sparc_status bloch_apply_impl<float>(sparc_gpu_ctx, const float*, float
 template <typename T>
 sparc_status bloch_filter_impl(sparc_gpu_ctx c, T* X, T* W, int ncol, long ldx, int m) {
     sparc_status st;
-    if ((st = nl_pass_k<T>(c, X, ncol, ldx, false, true, 1, 1)) != SPARC_OK) return st;
+    if ((st = nl_pass_k<T>(c, X, ncol, ldx, NlApply::no, true, 1, 1)) != SPARC_OK) return st;
     for (int k = 1; k <= m; ++k) {
         T* cur = (k % 2 == 0) ? W : X;
         T* dst = (k % 2 == 0) ? X : W;
         const int mode = k == 1 ? 1 : 2;
         if ((st = launch_hsweep<T>(c, cur, dst, k == 1 ? nullptr : dst, 2 * ncol, ldx, mode, k, true)) != SPARC_OK)
             return st;
-        if ((st = nl_pass_k<T>(c, dst, ncol, ldx, true, k < m, 2, k + 1)) != SPARC_OK) return st;
+        if ((st = nl_pass_k<T>(c, dst, ncol, ldx, NlApply::add, k < m, 2, k + 1)) != SPARC_OK) return st;
     }
     if (m % 2 == 1) {
         k_copy_block_k<T><<<dim3(div_up(2 * c->nd, 256), ncol), 256, 0, c->stream>>>(W, X, 2 * c->nd, ncol, ldx);

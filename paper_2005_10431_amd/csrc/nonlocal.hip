@@ -43,6 +43,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "mfma.hpp"
@@ -217,7 +218,7 @@ __device__ inline double add_sq(double r2, double d) {
     return r2 + d * d;
 }
 
-// AP: y += chi D.  PR: partial projections of (the completed) y.  WB: blocks
+// AP: y += chi D (1) or y = chi D (2).  PR: partial projections of (the completed) y.  WB: blocks
 // of a wave: all of the pencil's, or a third of them, when the waves of a workgroup
 // share 16 columns and leave a partial entry each (see nl_shape).
 // Per plane: barrier; chi of the plane into LDS; barrier; the products.  Two
@@ -225,7 +226,7 @@ __device__ inline double add_sq(double r2, double d) {
 // table overlaps the other's products.  A wave has the loads of a whole plane
 // (12 KB in FP64) in flight: with half of that and six waves per workgroup
 // the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.
-template <typename T, typename C, int S, int WB, bool AP, bool PR, bool TAIL>
+template <typename T, typename C, int S, int WB, int AP, bool PR, bool TAIL>
 __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
     using P = Pts<C>;
     using acc_t = typename Mfma<C>::acc_t;
@@ -439,7 +440,10 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
 #pragma unroll
     for (int b = 0; b < WB; ++b) pb0[b] = __builtin_amdgcn_readfirstlane(mine ? max(0, blk[b0 + b]) : 0);
     T q[WB][4];   // the blocks of a plane
-    auto load = [&](T* v, int b, int z) { P::load(yc + (long)z * a.nxy, pb0[b], g, v); };
+    auto load = [&](T* v, int b, int z) {
+        if constexpr (AP == 2) v[0] = v[1] = v[2] = v[3] = 0;
+        else P::load(yc + (long)z * a.nxy, pb0[b], g, v);
+    };
     // some coefficients of the wave's columns may not be finite
     const bool odd = AP && mine && a.odd[tile] == a.epoch;
     // a plane of such columns: block by block as in the loop below, with the
@@ -459,8 +463,8 @@ __global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
             if (b >= nb && !tail) continue;
             const uint32_t gb = (uint32_t)(gm >> (b * NG)) & ((1u << NG) - 1);
             T* yp = yc + (long)z * a.nxy + blk[b];
-            T v[4];
-            P::load(yp, 0, g, v);
+            T v[4] = {0, 0, 0, 0};
+            if (AP != 2) P::load(yp, 0, g, v);
             acc_t acc = {(C)v[0], (C)v[1], (C)v[2], (C)v[3]};
             const C* cb = chi + 16 * b * RS;
 #pragma unroll
@@ -912,6 +916,7 @@ static sparc_status build_ranges(sparc_gpu_ctx c, const std::vector<NlCand>& can
     }
     R.zlen = zlen;
     R.ncl = ncl;
+    R.whole = R.layer_off.size() == 2 && (int)units.size() == c->nlp.npen * zs;
     R.n_entries = (long)ent_cand.size();
     sparc_status st;
     if ((st = put(c, &R.units, units)) != SPARC_OK) return st;
@@ -1135,20 +1140,29 @@ static NlShape nl_shape(sparc_gpu_ctx c, int ncol, bool fp32) {
 }
 
 template <typename T, typename C, int S>
-static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, int nw, bool ap, bool pr, size_t shmem) {
+static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, int nw, NlApply ap, bool pr, size_t shmem) {
     constexpr int NB = kNlBlocks, WB = kNlBlocks / kNlSplit;
     const long nblocks = 8L * div_up(a.nunit, 8) * a.nchunk;
     if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "nonlocal pass: too many blocks");
     const dim3 g((unsigned)nblocks), b(64 * kNlWaves);
-    if (nw > 1) {
-        if (!ap) k_nl_pass<T, C, S, WB, false, true, false><<<g, b, shmem, c->stream>>>(a);
-        else if (pr) k_nl_pass<T, C, S, WB, true, true, true><<<g, b, shmem, c->stream>>>(a);
-        else k_nl_pass<T, C, S, WB, true, false, true><<<g, b, shmem, c->stream>>>(a);
-    } else if (!ap) k_nl_pass<T, C, S, NB, false, true, false><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail && pr) k_nl_pass<T, C, S, NB, true, true, true><<<g, b, shmem, c->stream>>>(a);
-    else if (a.tail) k_nl_pass<T, C, S, NB, true, false, true><<<g, b, shmem, c->stream>>>(a);
-    else if (pr) k_nl_pass<T, C, S, NB, true, true, false><<<g, b, shmem, c->stream>>>(a);
-    else k_nl_pass<T, C, S, NB, true, false, false><<<g, b, shmem, c->stream>>>(a);
+    auto go = [&](auto wb, auto av, auto pv, auto tv) {
+        k_nl_pass<T, C, S, wb(), av(), pv(), tv()><<<g, b, shmem, c->stream>>>(a);
+    };
+    auto go_form = [&](auto wb, auto tv) {
+        constexpr std::integral_constant<int, 1> add;
+        constexpr std::integral_constant<int, 2> write;
+        if (ap == NlApply::write) go(wb, write, std::false_type(), tv);
+        else if (pr) go(wb, add, std::true_type(), tv);
+        else go(wb, add, std::false_type(), tv);
+    };
+    constexpr std::integral_constant<int, NB> whole;
+    constexpr std::integral_constant<int, WB> shared;
+    constexpr std::integral_constant<int, 0> none;
+    if (ap == NlApply::no && nw > 1) go(shared, none, std::true_type(), std::false_type());
+    else if (ap == NlApply::no) go(whole, none, std::true_type(), std::false_type());
+    else if (nw > 1) go_form(shared, std::true_type());
+    else if (a.tail) go_form(whole, std::true_type());
+    else go_form(whole, std::false_type());
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;
 }
@@ -1219,7 +1233,7 @@ static NlSupport<T> support(sparc_gpu_ctx c, const NlArgs<T, C>& a) {
 // The pass over the columns set in a; with further layers every apply comes
 // before the first projection.
 template <typename T, typename C>
-static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, bool ap, bool pr) {
+static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, NlApply ap, bool pr) {
     const NlRanges& R = *sh.R;
     const int S = c->nlp.slots;
     const size_t shmem = nl_lds_layout(sizeof(C), S, R.zlen, R.ncl).total;
@@ -1229,8 +1243,9 @@ static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, bool
     a.nwc = div_up(tiles, a.nchunk);
     const int nl = (int)R.layer_off.size() - 1;
     for (int half = 0; half < (nl > 1 ? 2 : 1); ++half) {
-        const bool ap1 = ap && half == 0, pr1 = pr && (nl == 1 || half == 1);
-        if (!ap1 && !pr1) continue;
+        const NlApply ap1 = half == 0 ? ap : NlApply::no;
+        const bool pr1 = pr && (nl == 1 || half == 1);
+        if (ap1 == NlApply::no && !pr1) continue;
         for (int l = 0; l < nl; ++l) {
             const long u0 = R.layer_off[l];
             a.nunit = R.layer_off[l + 1] - (int)u0;
@@ -1246,10 +1261,26 @@ static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, bool
     return SPARC_OK;
 }
 
-// One pass over a block: apply (y += chi D) and / or project (D = alpha gamma dV
+// Writing pays where reading y would bound the pass: all four waves of its
+// workgroups have columns (three where planes share 128-byte lines), and Bloch
+// columns in FP32, whose products take twice their reading, are more than the
+// last-level cache holds along.  H X with the pass last and first, us: 72^3 x 64
+// FP64 278, 250; 120^3 x 32 728, 789; 120^3 x 130 2543, 2690; 51 x 68 x 93 x 77 357, 338;
+// Bloch FP32 71 x 61 x 45 x 30 154, 176 and 72^3 x 260 1831, 1707.
+bool nl_writes(sparc_gpu_ctx c, int ncol, bool fp32, bool bloch) {
+    const NlPass& N = c->nlp;
+    if (N.ranges.empty() || N.ranges[0].n_entries == 0) return false;
+    const NlShape sh = nl_shape(c, ncol, fp32 && !bloch);
+    if (!sh.R->whole || sh.nw > 1) return false;
+    const int tiles = div_up(ncol, 16), waves = div_up(tiles, div_up(tiles, kNlWaves));
+    if (bloch) return waves == 4 && (!fp32 || (double)c->nd * ncol * sizeof(float) > 128e6);
+    return waves == 4 || (waves == 3 && (long)c->nx * c->ny % 16 != 0);
+}
+
+// One pass over a block: apply (y += chi D, or y = chi D) and / or project (D = alpha gamma dV
 // chi^T y, alpha that of filter step `step` of mode `mode`, which will apply it).
 template <typename T>
-sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step, double* part,
+sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bool pr, int mode, int step, double* part,
                      size_t part_elems) {
     const NlPass& N = c->nlp;
     if (N.ranges.empty() || N.ranges[0].n_entries == 0 || ncol == 0) return SPARC_OK;
@@ -1292,13 +1323,13 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr
     return SPARC_OK;
 }
 
-template sparc_status nl_pass<double>(sparc_gpu_ctx, double*, int, long, bool, bool, int, int, double*, size_t);
-template sparc_status nl_pass<float>(sparc_gpu_ctx, float*, int, long, bool, bool, int, int, double*, size_t);
+template sparc_status nl_pass<double>(sparc_gpu_ctx, double*, int, long, NlApply, bool, int, int, double*, size_t);
+template sparc_status nl_pass<float>(sparc_gpu_ctx, float*, int, long, NlApply, bool, int, int, double*, size_t);
 
 // The pass over Bloch columns: the halves u, v are real columns, the images'
 // phases enter in the sum over an atom's entries.
 template <typename T>
-sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool pr, int mode, int step) {
+sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bool pr, int mode, int step) {
     const NlPass& N = c->nlp;
     if (N.ranges.empty() || N.ranges[0].n_entries == 0 || ncol == 0) return SPARC_OK;
     sparc_status st;
@@ -1348,7 +1379,7 @@ sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, bool ap, bool 
     return SPARC_OK;
 }
 
-template sparc_status nl_pass_k<double>(sparc_gpu_ctx, double*, int, long, bool, bool, int, int);
-template sparc_status nl_pass_k<float>(sparc_gpu_ctx, float*, int, long, bool, bool, int, int);
+template sparc_status nl_pass_k<double>(sparc_gpu_ctx, double*, int, long, NlApply, bool, int, int);
+template sparc_status nl_pass_k<float>(sparc_gpu_ctx, float*, int, long, NlApply, bool, int, int);
 
 }  // namespace sg

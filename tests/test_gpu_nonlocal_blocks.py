@@ -103,3 +103,64 @@ def test_dense_systems_reach_all_slots_and_a_second_layer(capfd, monkeypatch):
         assert all(s == 24 for s, _ in seen["dense", ns])
         assert any(n > 1 for _, n in seen["layers", ns])
         assert all(s <= 16 and n == 1 for s, n in seen["odd_plane", ns])
+
+
+@pytest.mark.parametrize("system", ["deep", "whole_blocks", "wide", "sparse", "layers"])
+@pytest.mark.parametrize("ncol", [48, 64])
+def test_h_written_by_the_pass(system, ncol):
+    """Blocks that fill the pass's workgroups: the projector term is written
+    before the local part is added, where the units hold every point (not in
+    the sparse system and not with a second layer).  What Y held before must
+    not matter, padding stays, and a NaN reaches what it reaches in a narrow
+    block."""
+    torch = require_gpu()
+    from paper_2005_10431_amd import Context
+    s = _system(system)
+    v = np.random.default_rng(3).uniform(-1.0, 0.5, s.nd)
+    projs = atoms.projectors(s)
+    ctx = Context(s)
+    ctx.set_veff(to_dev(torch, v))
+    for dtype, bar in (("float64", 1e-12), ("float32", 2e-6)):
+        X = np.full((ncol, s.nd + 3), 5.0, dtype=dtype)
+        X[:, :s.nd] = W.initial_orbitals(s.nd, ncol, 2)
+        Xd = to_dev(torch, X)
+        Y = torch.full_like(Xd, float("nan"))
+        ctx.apply_H(Xd, Y)
+        got = to_np(Y)
+        err = rel_err(got[:, :s.nd].astype(np.float64),
+                      hamiltonian.apply_H(s, v, projs, X[:, :s.nd].astype(np.float64)))
+        log(f"{system} {ncol} {dtype}: {err:.2e}")
+        assert err <= bar and np.all(np.isnan(got[:, s.nd:]))
+        Xd[3, s.nd // 2] = float("nan")
+        Y1 = torch.zeros_like(Xd[:5])
+        ctx.apply_H(Xd, Y)
+        ctx.apply_H(Xd[:5], Y1)
+        assert torch.equal(torch.isnan(Y[:5, :s.nd]), torch.isnan(Y1[:, :s.nd]))
+        assert int(torch.isnan(Y[:, :s.nd]).any(dim=1).sum()) == 1
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_bloch_h_written_by_the_pass(dtype):
+    """The same for Bloch columns (FP64 at 32 columns; FP32 takes this way only in
+    blocks of more than 128 MB: 62 x 62 x 62 x 96)."""
+    torch = require_gpu()
+    from paper_2005_10431_amd import Context
+    if dtype == "float64":
+        s, nc = _system("deep"), 32
+    else:
+        s, nc = W.tiny_system(n=(62, 62, 62), L=(18.6, 18.6, 18.6), n_atoms=60, seed=3, n_states=72), 96
+    k = (0.31, -0.17, 0.23)
+    v = np.random.default_rng(3).uniform(-1.0, 0.5, s.nd)
+    ctx = Context(s)
+    ctx.set_veff(to_dev(torch, v))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Xd = (torch.rand((nc, 2 * s.nd), generator=g, device="cuda") - 0.5).to(getattr(torch, dtype))
+    Y = torch.full_like(Xd, float("nan"))
+    ctx.apply_H_k(k, Xd, Y)
+    X = to_np(Xd[:2]).astype(np.float64)
+    ref = kpoints.apply_H_k(s, v, kpoints.projectors_k(s, k), X[:, :s.nd] + 1j * X[:, s.nd:], k)
+    got = to_np(Y[:2]).astype(np.float64)
+    err = rel_err(got[:, :s.nd] + 1j * got[:, s.nd:], ref)
+    log(f"Bloch {dtype} {nc}: {err:.2e}")
+    assert err <= (1e-12 if dtype == "float64" else 2e-6)
+    assert bool(torch.isfinite(Y).all())

@@ -696,6 +696,10 @@ sparc_status sparc_gpu_create(const sparc_gpu_system* s, void* hip_stream, sparc
     if (const char* e = std::getenv("SPARC_GPU_CHOL_MULTI_MIN")) c->chol_multi_min = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_STEIN_LDS_MIN_TPW")) c->stein_lds_min_tpw = std::atoi(e);
     if (const char* e = std::getenv("SPARC_GPU_SWEEP_GROUP")) c->sweep_group = std::atoi(e);
+    if (const char* e = std::getenv("SPARC_GPU_GEMM_TILE")) {
+        const int tile = std::atoi(e);
+        if (tile == 128 || tile == 160) c->gemm_tile = tile;
+    }
     if (const char* e = std::getenv("SPARC_GPU_CNN_TZ")) {
         const int tz = std::atoi(e);
         if (tz == 0 || tz == 4 || tz == 8) c->cnn_tz = tz;

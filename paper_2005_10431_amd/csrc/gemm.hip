@@ -268,7 +268,9 @@ __global__ __launch_bounds__(256) void k_gemm_tn_lds(int M, int N, long K, long 
         if (s + 1 < nst) store(buf ^ 1);
         __syncthreads();
     }
-    double* P = part + (long)split * M * N;
+    // the tile's partial: TT x TT, of active tiles only
+    constexpr int TT = 32 * MT;
+    double* P = part + ((long)split * active + tidx) * TT * TT;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -277,15 +279,18 @@ __global__ __launch_bounds__(256) void k_gemm_tn_lds(int M, int N, long K, long 
             for (int r = 0; r < 4; ++r) {
                 const int m = 16 * (sm + i) + Mfma<double>::row(lane, r);
                 const int n = 16 * (sn + j) + li;
-                if (m < M && n < N && !(symmetric && sm + i > sn + j)) P[m + (long)n * M] = acc[i][j][r];
+                if (m < M && n < N && !(symmetric && sm + i > sn + j))
+                    P[m - TT * tm + (n - TT * tn) * TT] = acc[i][j][r];
             }
 }
 
 // C = alpha * sum over splits, eighths of them by a thread each and in order;
 // with `symmetric` only strip pairs sn >= sm were computed and the lower ones are
-// mirrored.
+// mirrored.  tile: edge of the active tiles that a split's partial holds one after
+// another, 0 where it holds an M x N matrix.
 __global__ __launch_bounds__(256) void k_gemm_reduce(int M, int N, int nsplit, const double* __restrict__ part,
-                                                     double alpha, double* __restrict__ C, int ldc, bool symmetric) {
+                                                     double alpha, double* __restrict__ C, int ldc, bool symmetric,
+                                                     int tile, int tiles_m, int active) {
     __shared__ double eighth[8][33];
     const int el = threadIdx.x & 31, q = threadIdx.x >> 5;
     const long ms = (long)M * N, e = (long)blockIdx.x * 32 + el;
@@ -296,12 +301,18 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(int M, int N, int nsplit, c
         sn = m;
     }
     const double* p = part + sm + (long)sn * M;
+    long step = ms;
+    if (tile) {
+        const int tm = sm / tile, tn = sn / tile, tidx = symmetric ? tn * (tn + 1) / 2 + tm : tn * tiles_m + tm;
+        p = part + (long)tidx * tile * tile + (sm - tm * tile) + (long)(sn - tn * tile) * tile;
+        step = (long)active * tile * tile;
+    }
     const int len = (nsplit + 7) / 8, end = min(nsplit, (q + 1) * len);
     double s = 0.0;
     for (int k = q * len; k < end; k += 4) {
         double v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = p[min(k + u, end - 1) * ms];
+        for (int u = 0; u < 4; ++u) v[u] = p[min(k + u, end - 1) * step];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (k + u < end) s += v[u];
@@ -316,9 +327,11 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(int M, int N, int nsplit, c
 
 // Splits of K in FP64: the fewest that fill whole rounds of the workgroups that
 // the chip holds to within 3%, in multiples of 8 (see the kernels), at least 128
-// rows each.
-static int tn_splits(int active, long K, int waves) {
-    const long most = std::max<long>(1, K / 128);
+// rows each, and no more than 512 MB of partial sums (`bytes` each) unless 8 take
+// more.  1.73M x 1200 x 1200: 64, 461 MB (737 as full matrices), 48.8 ms; 9, the fewest
+// of any count that fill a round, 104 MB and 50.7 ms.
+static int tn_splits(int active, long K, int waves, size_t bytes) {
+    const long most = std::min(std::max<long>(1, K / 128), std::max<long>(8, ((long)512 << 20) / (long)bytes));
     if (most < 8) return (int)most;
     int best = 8;
     double full = 0;
@@ -348,8 +361,9 @@ static int tn_splits_f32(int M, int N, long K, bool symmetric) {
 struct TnGrid {
     int tiles_m = 0, active = 0, nsplit = 0;
     long kchunk = 0;
+    size_t part = 0;   // values of a split's partial
 };
-static TnGrid tn_grid(int M, int N, long K, bool symmetric, int MT, int NT, int f32_splits, int slots) {
+static TnGrid tn_grid(int M, int N, long K, bool symmetric, int MT, int NT, int f32_splits, int slots, bool tiles) {
     TnGrid G;
     G.tiles_m = div_up(M, 16 * MT);
     const int tiles_n = div_up(N, 16 * NT);
@@ -358,16 +372,20 @@ static TnGrid tn_grid(int M, int N, long K, bool symmetric, int MT, int NT, int 
         G.active = 0;
         for (int tn = 0; tn < tiles_n; ++tn) G.active += std::min(G.tiles_m, (tn * NT + NT - 1) / MT + 1);
     }
-    G.nsplit = f32_splits ? f32_splits : tn_splits(G.active, K, slots);
+    G.part = tiles ? (size_t)G.active * 256 * MT * NT : (size_t)M * N;
+    G.nsplit = f32_splits ? f32_splits : tn_splits(G.active, K, slots, G.part * sizeof(double));
     G.kchunk = ((K + G.nsplit - 1) / G.nsplit + 15) / 16 * 16;
     return G;
 }
 
-// Up to 32 columns a step holds few products and its loads dominate: small
-// tiles straight from L2, two steps of loads in flight (24^3 rows x 24: 8 us,
-// through LDS 35), a wave per workgroup.
+// Up to 32 columns (in FP32 64 of at most half a million rows) a step holds few
+// products and its loads dominate: small tiles straight from L2, two steps of loads
+// in flight, a wave per workgroup (24^3 rows x 24: 8 us, through LDS 35; FP32 24^3 x 33
+// 26, in 4 x 3 strips 55; 72^3 x 48 51 and 56, 100^3 x 48 103 and 97).
 // FP32 above that 4 x 3 strips (its splits are few: 8 of 1200 columns in 4 x 4
-// strips fill three quarters of the chip's wave slots).  FP64 through LDS, 128
+// strips fill three quarters of the chip's wave slots).  FP64 through LDS: up to 64
+// columns in one tile of that width (24^3 rows x 33 columns 14 us, in a 128-wide tile 21;
+// 72^3 x 64 62 and 100, 100^3 x 33 98 and 199; from L2 11, 87, 133), above it 128
 // columns per tile (two workgroups per compute unit), or 160 (one) where up to
 // 320 columns need fewer tiles that way: 72^3 rows x 128 columns 190 and 281 us,
 // x 160 436 and 337, x 200 590 and 979, x 320 1282 and 1137.
@@ -377,10 +395,16 @@ sparc_status gemm_tn(sparc_gpu_ctx c, int M, int N, long K, const T* A, long lda
     if (symmetric && M != N) return set_err(c, SPARC_ERR_ARG, "gemm_tn: symmetric needs M == N");
     const int mx = std::max(M, N), cus = c->prop.multiProcessorCount;
     const int f32 = sizeof(T) == 4 ? tn_splits_f32(M, N, K, symmetric) : 0;
-    const int strips = mx <= 32 ? 2 : (sizeof(T) == 4 ? 4 : (mx <= 320 && div_up(mx, 160) < div_up(mx, 128) ? 10 : 8));
-    const TnGrid G = tn_grid(M, N, K, symmetric, strips, strips == 4 ? 3 : strips, f32,
-                             strips == 10 ? cus : (strips == 8 ? 2 * cus : 8 * cus));
-    sparc_status st = ensure_gemm_part(c, (size_t)G.nsplit * M * N);
+    // strips of a tile's edge
+    int strips = sizeof(T) == 4 ? (mx <= 32 || (mx <= 64 && K < 1L << 19) ? 2 : 4)
+                 : mx <= 32     ? 2
+                 : mx <= 64     ? 4
+                                : (mx <= 320 && div_up(mx, 160) < div_up(mx, 128) ? 10 : 8);
+    if (sizeof(T) == 8 && mx > 64 && c->gemm_tile) strips = c->gemm_tile / 16;
+    const bool lds = sizeof(T) == 8 && strips > 2;
+    const TnGrid G = tn_grid(M, N, K, symmetric, strips, strips == 4 && !lds ? 3 : strips, f32,
+                             strips == 10 ? cus : (lds ? (strips == 8 ? 2 : 4) * cus : 8 * cus), lds);
+    sparc_status st = ensure_gemm_part(c, G.nsplit * G.part);
     if (st != SPARC_OK) return st;
     const long nblocks = (long)G.active * G.nsplit;
     if (nblocks > 0x7fffffffL) return set_err(c, SPARC_ERR_ARG, "gemm_tn: too many blocks");
@@ -393,6 +417,9 @@ sparc_status gemm_tn(sparc_gpu_ctx c, int M, int N, long K, const T* A, long lda
     } else if constexpr (sizeof(T) == 4) {
         k_gemm_tn_split<T, 4, 3, 2><<<g, 64, 0, c->stream>>>(M, N, K, G.kchunk, A, lda, B, ldb, part, G.tiles_m,
                                                              symmetric, G.active, G.nsplit);
+    } else if (strips == 4) {
+        k_gemm_tn_lds<2><<<g, 256, 0, c->stream>>>(M, N, K, G.kchunk, A, lda, B, ldb, part, G.tiles_m, symmetric,
+                                                   G.active, G.nsplit);
     } else if (strips == 10) {
         k_gemm_tn_lds<5><<<g, 256, 0, c->stream>>>(M, N, K, G.kchunk, A, lda, B, ldb, part, G.tiles_m, symmetric,
                                                    G.active, G.nsplit);
@@ -402,7 +429,8 @@ sparc_status gemm_tn(sparc_gpu_ctx c, int M, int N, long K, const T* A, long lda
     }
     SG_CHECK_LAUNCH(c);
     prof_end(c, slot);
-    k_gemm_reduce<<<div_up((long)M * N, 32), 256, 0, c->stream>>>(M, N, G.nsplit, part, alpha, C, ldc, symmetric);
+    k_gemm_reduce<<<div_up((long)M * N, 32), 256, 0, c->stream>>>(M, N, G.nsplit, part, alpha, C, ldc, symmetric,
+                                                                 lds ? 16 * strips : 0, G.tiles_m, G.active);
     SG_CHECK_LAUNCH(c);
     return SPARC_OK;
 }

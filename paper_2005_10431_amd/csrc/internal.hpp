@@ -176,6 +176,7 @@ struct sparc_gpu_ctx_s {
     // captured Jacobi sweep (see dense.hip)
     hipStream_t cap_stream = nullptr;
     int sweep_group = 4;        // SPARC_GPU_SWEEP_GROUP: orbitals whose copies of a slab the sweep dispatches side by side
+    int gemm_tile = 0;          // SPARC_GPU_GEMM_TILE: edge of the FP64 Gram tiles above 64 columns (128, 160; 0: by size)
     int cnn_tz = 8;             // SPARC_GPU_CNN_TZ: depth of the matrix-core 16 -> 16 convolution tile (4, 8; 0: vector kernel)
     int cnn_per_cu[2][2] = {};  // resident convolution workgroups per CU, by (tile depth 8, MODE)
     hipGraphExec_t jac_exec = nullptr;

@@ -134,7 +134,7 @@ sparc_status sparc_gpu_chebyshev_filter(sparc_gpu_ctx ctx, sparc_prec prec, void
  * hipMalloc): same arguments, results and errors as
  * sparc_gpu_chebyshev_filter, bitwise equal to it, and it calls no hipMalloc,
  * hipFree or other allocating routine (nor records timing events).  Its
- * projection partials live in a fixed 32 MiB device array of the library
+ * projection partials live in a fixed 64 MiB device array of the library
  * (one copy per GPU, held until the process ends, its address looked up at
  * sparc_gpu_create); columns are processed in as many groups as that needs.
  * Returns SPARC_ERR_ARG when the partials of one column alone exceed the

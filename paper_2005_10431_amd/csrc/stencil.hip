@@ -486,11 +486,13 @@ template sparc_status launch_hsweep<float>(sparc_gpu_ctx, const float*, float*, 
 
 // ---- allocation-free filter -----------------------------------------------
 // The projection partials of sparc_gpu_chebyshev_filter_noalloc live in this
-// fixed array (32 MiB; each GPU the library runs on holds its own copy until
+// fixed array (64 MiB; each GPU the library runs on holds its own copy until
 // the process ends) instead of memory the library allocates.  Host code never
 // names the array: it uses the device address looked up once per device by
-// scratch_init.  Calls that overlap on one GPU share it and race.
-constexpr size_t kScratchDoubles = (size_t)4 << 20;
+// scratch_init.  Calls that overlap on one GPU share it and race.  Its size sets
+// the columns of a group: 120^3 x 600 with 500 atoms, 6 degrees in FP64, 90 ms in
+// groups of 112 (32 MiB, 320 workgroups of the pass on 512 places), 75 in groups of 240.
+constexpr size_t kScratchDoubles = (size_t)8 << 20;
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
 sparc_status scratch_init(sparc_gpu_ctx c, int dev) {

@@ -200,14 +200,15 @@ __global__ __launch_bounds__(256 * sweep_simd_waves(VX * sizeof(T), BL)) void k_
     const int lrow = ((active ? ly : 0) + NO) * W + PAD + x0;
     auto ld = [](const T* p) -> rv { return *reinterpret_cast<const gv*>(p); };
     // the other half of a Bloch column, and a value of this half times
-    // exp(i s k L) (s = +1 past the upper face, -1 past the lower one), in double
+    // exp(i s k L) (s = +1 past the upper face, -1 past the lower one), in double; one
+    // order of rounding, or it would go with the ring phase that a plane falls on
     const T* __restrict__ xo = BL ? a.x + (long)(col >> 1) * a.ldx + (long)((col & 1) ^ 1) * a.half : nullptr;
     const double sgn = (col & 1) ? 1.0 : -1.0;
     auto rot = [&](rv own, rv oth, int axis, int s) -> rv {
         const double cs = a.ph[2 * axis], sn = (s > 0 ? sgn : -sgn) * a.ph[2 * axis + 1];
         rv r;
 #pragma unroll
-        for (int e = 0; e < VX; ++e) r[e] = (T)((double)own[e] * cs + (double)oth[e] * sn);
+        for (int e = 0; e < VX; ++e) r[e] = (T)fma((double)oth[e], sn, (double)own[e] * cs);
         return r;
     };
     const bool wedge = wleft || wright;

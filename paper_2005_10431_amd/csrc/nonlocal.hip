@@ -225,9 +225,12 @@ __device__ inline double add_sq(double r2, double d) {
 // workgroups of four waves fit a compute unit (71 KB of LDS each), so one's
 // table overlaps the other's products.  A wave has the loads of a whole plane
 // (12 KB in FP64) in flight: with half of that and six waves per workgroup
-// the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.
+// the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.  With 24 slots in FP64
+// the LDS holds one workgroup, which has the registers of both (within half of
+// them it spilled: 72^3 x 130 with supports of 4.1 Bohr, a filter step 1130 us, now 820).
 template <typename T, typename C, int S, int WB, int AP, bool PR, bool TAIL>
-__global__ __launch_bounds__(64 * kNlWaves, 2) void k_nl_pass(NlArgs<T, C> a) {
+__global__ __launch_bounds__(64 * kNlWaves, S == kMaxSlots && sizeof(C) == 8 ? 1 : 2) void k_nl_pass(
+    NlArgs<T, C> a) {
     using P = Pts<C>;
     using acc_t = typename Mfma<C>::acc_t;
     constexpr int NB = kNlBlocks, NG = S / 4, RS = 4 * S + 4, NP = 16 * NB;

@@ -145,21 +145,24 @@ __global__ __launch_bounds__(256) void k_force_overlap(ForceTab tab, int n_atoms
 constexpr int kForceTiles = 5;   // 16-column tiles of a workgroup at most
 
 // Projections of the columns on the atom's projectors and their gradients:
-// pd[((part n_atoms + a) ncol + col) 16 + q] with q = k (chi_k^T psi, k = s, px, py, pz) and
-// q = 4 + 3 k + d ((d/dx_d chi_k)^T psi), each times dV; parts are added later.
+// pd[((part n_atoms + a) ncol + col) 16 + q] with q = k (chi_k^T psi, k = s, px,
+// py, pz) and q = 4 + 3 k + d ((d/dx_d chi_k)^T psi), each times dV; parts are
+// added later.
 //
 // The 16 functions of an atom are the rows of one FP64 MFMA tile.  A workgroup
 // takes an atom, up to 80 columns (TL tiles of 16) and one of `parts` shares of the
-// x-lines of the atom's sphere, its waves every (4 parts)-th of them, 24 points at a time with the next ones' loads in flight, and for
-// each point every lane forms the one function of its row,
+// x-lines of the atom's sphere, its waves every (4 parts)-th of them, 24 points at
+// a time with the next ones' loads in flight, and for each point every lane forms
+// the one function of its row,
 //   f_q = exp(-r^2 / rc^2) (c0 + c1 u v),   u, v each 1, dx, dy or dz,
-// which all columns then share.  Reading is what bounds it: the lanes
-// of a wave hold 16 different columns, so that a load of 8 bytes per lane costs
-// the L1 57 accesses, and the overlapping spheres read the block 5 times (4 GB at
-// 72^3, 108 atoms, 260 columns).  There 1.95 ms as vector code with the 16 sums of
-// four columns per thread; 1.27 on the matrix cores with loads of single points,
-// 1.11 with pairs (the products alone would take 0.13).  Neighbouring atoms on one
-// XCD made no difference.
+// which all columns then share.  Reading is what bounds it: the lanes of a wave
+// hold 16 different columns, so that a load of 8 bytes per lane costs the L1 57
+// accesses, and the overlapping spheres read the block 5 times (4 GB at 72^3, 108
+// atoms, 260 columns).  There 1.95 ms as vector code with the 16 sums of four
+// columns per thread; 1.27 on the matrix cores with loads of single points, 1.06
+// with pairs, 0.86 in three parts whose lines outside the sphere are skipped (the
+// products alone would take 0.13).  Neighbouring atoms on one XCD made no
+// difference.
 template <typename T, int TL>
 __global__ __launch_bounds__(256, 2) void k_force_nl_proj(const T* __restrict__ X, long ldx, int ncol, ForceTab tab,
                                                           int nx, int ny, int nz, double hx, double hy, double hz,
@@ -335,8 +338,8 @@ namespace {
 // workgroups, and the last ones run on after the others for about 0.6 of their
 // time; a part costs 0.03 spheres more than its lines (set-up, the sum over the
 // waves).  In one part few atoms or columns leave the chip idle: 4 atoms x 12
-// columns 521 and now 209 us with the local part, 46 x 77 600 and 288, 108 x 16 723
-// and 340; 108 x 260 fills it unevenly (1302 us in one part, 1124 in 3, 1146 in 4).
+// columns 521 and now 209 us with the local part, 46 x 77 600 and 293, 108 x 16 724
+// and 328; 108 x 260 fills it unevenly (1302 us in one part, 1124 in 3, 1146 in 4).
 struct ForceGrid {
     int tiles, chunks, parts;
 };
@@ -406,7 +409,8 @@ sparc_status sparc_gpu_forces(sparc_gpu_ctx c, const double* d_phi, sparc_prec p
     sparc_status st;
     if ((st = ensure_force_tables(c)) != SPARC_OK) return st;
     const int na = c->n_atoms;
-    const size_t need = std::max((size_t)na * kLocalChunks * 3, nl ? (size_t)na * ncol * 16 * force_grid(na, ncol).parts : 0);
+    const size_t need = std::max((size_t)na * kLocalChunks * 3,
+                                 nl ? (size_t)na * ncol * 16 * force_grid(na, ncol).parts : 0);
     if ((st = ensure_red(c, need)) != SPARC_OK) return st;
     const ForceTab tab = force_tab(c);
     int slot = prof_begin(c, PK_FORCE_LOCAL);

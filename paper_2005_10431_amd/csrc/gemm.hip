@@ -380,12 +380,12 @@ static TnGrid tn_grid(int M, int N, long K, bool symmetric, int MT, int NT, int 
 
 // Up to 32 columns (in FP32 64 of at most half a million rows) a step holds few
 // products and its loads dominate: small tiles straight from L2, two steps of loads
-// in flight, a wave per workgroup (24^3 rows x 24: 8 us, through LDS 35; FP32 24^3 x 33
-// 26, in 4 x 3 strips 55; 72^3 x 48 51 and 56, 100^3 x 48 103 and 97).
+// in flight, a wave per workgroup (24^3 rows x 24: 8 us, through LDS 35; FP32 24^3 x
+// 33 26, in 4 x 3 strips 55; 72^3 x 48 51 and 56, 100^3 x 48 103 and 97).
 // FP32 above that 4 x 3 strips (its splits are few: 8 of 1200 columns in 4 x 4
 // strips fill three quarters of the chip's wave slots).  FP64 through LDS: up to 64
-// columns in one tile of that width (24^3 rows x 33 columns 14 us, in a 128-wide tile 21;
-// 72^3 x 64 62 and 100, 100^3 x 33 98 and 199; from L2 11, 87, 133), above it 128
+// columns in one tile of that width (24^3 rows x 33 columns 14 us, in a 128-wide
+// tile 21; 72^3 x 64 62 and 100, 100^3 x 33 98 and 199; from L2 11, 87, 133), above it 128
 // columns per tile (two workgroups per compute unit), or 160 (one) where up to
 // 320 columns need fewer tiles that way: 72^3 rows x 128 columns 190 and 281 us,
 // x 160 436 and 337, x 200 590 and 979, x 320 1282 and 1137.

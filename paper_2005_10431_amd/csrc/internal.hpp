@@ -175,8 +175,8 @@ struct sparc_gpu_ctx_s {
 
     // captured Jacobi sweep (see dense.hip)
     hipStream_t cap_stream = nullptr;
-    int sweep_group = 4;        // SPARC_GPU_SWEEP_GROUP: orbitals whose copies of a slab the sweep dispatches side by side
-    int gemm_tile = 0;          // SPARC_GPU_GEMM_TILE: edge of the FP64 Gram tiles above 64 columns (128, 160; 0: by size)
+    int sweep_group = 4;        // SPARC_GPU_SWEEP_GROUP: orbitals whose copies of a slab run side by side
+    int gemm_tile = 0;          // SPARC_GPU_GEMM_TILE: FP64 Gram tiles above 64 columns (128, 160; 0: by size)
     int cnn_tz = 8;             // SPARC_GPU_CNN_TZ: depth of the matrix-core 16 -> 16 convolution tile (4, 8; 0: vector kernel)
     int cnn_per_cu[2][2] = {};  // resident convolution workgroups per CU, by (tile depth 8, MODE)
     hipGraphExec_t jac_exec = nullptr;
@@ -251,9 +251,9 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
 // The nonlocal term of a block in one pass: apply (add: y += chi D; write: y = chi D,
 // only where nl_writes says so) and / or project (D = alpha gamma dV chi^T y of the
 // completed y, alpha that of the filter step (mode, step) that will apply it, 1
-// for mode 0).  The partial sums go to `part`
-// (part_elems doubles, as many columns at a time as fit) when given, else to
-// context memory sized for the whole block.  Does nothing without projectors.
+// for mode 0).  The partial sums go to `part` (part_elems doubles, as many columns
+// at a time as fit) when given, else to context memory sized for the whole block.
+// Does nothing without projectors.
 enum class NlApply { no, add, write };
 template <typename T>
 sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply apply, bool project, int mode, int step,

@@ -1,5 +1,7 @@
-// Nonlocal term of H at the Gamma point (Sec. 2.1: applied through its outer
-// products), V_nl x = sum_I sum_lm chi_Ilm D_Ilm with D = gamma dV chi^T x.
+// Nonlocal term of H (Sec. 2.1: applied through its outer products),
+// V_nl x = sum_I sum_lm chi_Ilm D_Ilm with D = gamma dV chi^T x, and its Bloch
+// form, whose passes are the same over the halves [Re; Im] of a column and whose
+// phases enter with the sum over an atom's entries (k_nl_reduce_k).
 //
 // The projections D of a block and their application are products with a
 // tall matrix that every orbital shares: chi on a tile of the grid, against
@@ -15,8 +17,9 @@
 //    16), so that a wave reads and writes whole lines of every orbital: on
 //    24-point pieces of rows instead, a plain read and write of the block
 //    ran at 2.9 instead of 4.3 TB/s at 120^3 x 1200;
-//  - a pencil is up to kNlBlocks blocks that lie close together in x and y; a unit is a
-//    pencil over a range of z;
+//  - a pencil is up to kNlBlocks blocks that lie close together in x and y; a
+//    unit is a pencil over a range of z, of which few columns take more and
+//    shorter ones (nl_shape);
 //  - along the unit's planes every (atom, image) pair that reaches it holds
 //    one of S slots for its z extent.  A slot's 4 projections stay in
 //    accumulators and its 4 coefficients in registers until it leaves, when
@@ -27,7 +30,7 @@
 //  - per plane the workgroup tabulates chi of the plane's points x slots in
 //    LDS, shared by its orbitals; slots go in groups of four (16 projectors,
 //    one MFMA row tile) and a block skips the groups that do not touch it (a
-//    block of a 4.5-Bohr lattice meets 5.3 pairs in 2.6 groups on average).
+//    block of a 4.5-Bohr lattice meets 5.3 pairs in 2.15 groups on average).
 // The accumulator layout of the apply product is the operand layout of the
 // projection product, so a value goes from its load through both without
 // leaving its lane.
@@ -53,7 +56,7 @@ namespace sg {
 namespace {
 
 constexpr int kIdle = 255;          // slot without a pair
-constexpr int kMaxLocal = 112;      // pairs of a unit (with 24 slots and 128 planes 160 KB of LDS are full)
+constexpr int kMaxLocal = 112;      // pairs of a unit (with 24 slots and 128 planes 106 KB of LDS in FP64)
 constexpr int kMaxPlanes = 128;     // planes of a unit
 constexpr int kMaxSlots = 24;
 constexpr int kNlWaves = 4;         // waves of a workgroup, 16 orbitals each
@@ -218,16 +221,16 @@ __device__ inline double add_sq(double r2, double d) {
     return r2 + d * d;
 }
 
-// AP: y += chi D (1) or y = chi D (2).  PR: partial projections of (the completed) y.  WB: blocks
-// of a wave: all of the pencil's, or a third of them, when the waves of a workgroup
-// share 16 columns and leave a partial entry each (see nl_shape).
+// AP: y += chi D (1) or y = chi D (2).  PR: partial projections of (the completed)
+// y.  WB: blocks of a wave: all of the pencil's, or a third of them, when the waves
+// of a workgroup share 16 columns and leave a partial entry each (see nl_shape).
 // Per plane: barrier; chi of the plane into LDS; barrier; the products.  Two
 // workgroups of four waves fit a compute unit (71 KB of LDS each), so one's
 // table overlaps the other's products.  A wave has the loads of a whole plane
 // (12 KB in FP64) in flight: with half of that and six waves per workgroup
-// the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.  With 24 slots in FP64
-// the LDS holds one workgroup, which has the registers of both (within half of
-// them it spilled: 72^3 x 130 with supports of 4.1 Bohr, a filter step 1130 us, now 820).
+// the pass took 9.5 instead of 8.3 ms at 120^3 x 1200 in FP64.  With 24 slots in
+// FP64 the LDS holds one workgroup, which has the registers of both (within half of
+// them it spilled: 72^3 x 130, supports of 4.1 Bohr, a filter step 1130 us, now 820).
 template <typename T, typename C, int S, int WB, int AP, bool PR, bool TAIL>
 __global__ __launch_bounds__(64 * kNlWaves, S == kMaxSlots && sizeof(C) == 8 ? 1 : 2) void k_nl_pass(
     NlArgs<T, C> a) {
@@ -247,8 +250,8 @@ __global__ __launch_bounds__(64 * kNlWaves, S == kMaxSlots && sizeof(C) == 8 ? 1
 
     // block b runs on XCD b % 8.  All units of 64 orbitals go before the next
     // orbitals, the last ones first, which the sweep before has left in the
-    // last-level cache; an XCD takes a contiguous
-    // eighth of the units, a different one each time, since some hold one more
+    // last-level cache; an XCD takes a contiguous eighth of the units, a different
+    // one each time, since some hold one more
     if (PR && blockIdx.x == 0 && threadIdx.x == 0) {
         double csh, beta;
         filter_coefs(a.params, a.mode, a.step, *a.alpha, csh, beta);
@@ -593,7 +596,8 @@ __global__ __launch_bounds__(64 * kNlWaves, S == kMaxSlots && sizeof(C) == 8 ? 1
     }
 }
 
-// What the sums over entries need to form a projection again from the block.
+// What the sums over entries need to form again, from the block, a projection
+// that is not finite.
 template <typename T>
 struct NlSupport {
     const T* y;
@@ -630,8 +634,9 @@ __device__ double sum_support(const NlSupport<T>& a, const NlCand& c, const T* y
     return s;
 }
 
-// D(4a+lm, col) = alpha gamma_lm dV sum of atom a's entries (nw partial ones each, 1 or kNlSplit), in
-// `parts` runs of them side by side, each in entry order, added in order.
+// D(4a+lm, col) = alpha gamma_lm dV sum of atom a's entries (nw partial ones each,
+// 1 or kNlSplit), in `parts` runs of them side by side, each in entry order, added
+// in order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_nl_reduce(const double* __restrict__ part, int ncol, int nw, int parts,
                                                    const int* __restrict__ off, const int* __restrict__ ent,
@@ -775,7 +780,8 @@ void free_nl_pass(NlPass& T) {
     for (void* p : {(void*)T.blk, (void*)T.cand, (void*)T.cand_off, (void*)T.odd, (void*)T.zero, T.dummy})
         if (p) hipFree(p);
     for (NlRanges& R : T.ranges)
-        for (void* p : {(void*)R.units, (void*)R.occ, (void*)R.gm, (void*)R.ent_cand, (void*)R.red_off, (void*)R.red_ent})
+        for (void* p : {(void*)R.units, (void*)R.occ, (void*)R.gm, (void*)R.ent_cand, (void*)R.red_off,
+                        (void*)R.red_ent})
             if (p) hipFree(p);
     T = NlPass{};
 }
@@ -1118,7 +1124,9 @@ static int reduce_runs(int ncol) {
 // Ranges and waves of a pass over ncol columns: the cheapest by nl_cost of the
 // ranges that were built; other than those of the full block only where their
 // partial sums fit the fixed scratch array, so that the allocation-free filter
-// takes the same.
+// takes the same.  H X in FP64 with the full block's ranges and whole waves for
+// every width, and now: 72^3 x 1 238 and 81 us, x 12 261 and 107, x 24 279 and 173;
+// 120^3 x 1 1072 and 275.
 struct NlShape {
     const NlRanges* R;
     int nw;   // partial entries of a unit and pair (waves that share the blocks)
@@ -1268,8 +1276,8 @@ static sparc_status run_layers(sparc_gpu_ctx c, NlArgs<T, C> a, NlShape sh, NlAp
 // workgroups have columns (three where planes share 128-byte lines), and Bloch
 // columns in FP32, whose products take twice their reading, are more than the
 // last-level cache holds along.  H X with the pass last and first, us: 72^3 x 64
-// FP64 278, 250; 120^3 x 32 728, 789; 120^3 x 130 2543, 2690; 51 x 68 x 93 x 77 357, 338;
-// Bloch FP32 71 x 61 x 45 x 30 154, 176 and 72^3 x 260 1831, 1707.
+// FP64 278, 250; 120^3 x 32 728, 789; 120^3 x 130 2543, 2690; 51 x 68 x 93 x 77
+// 357, 338; Bloch FP32 71 x 61 x 45 x 30 154, 176 and 72^3 x 260 1831, 1707.
 bool nl_writes(sparc_gpu_ctx c, int ncol, bool fp32, bool bloch) {
     const NlPass& N = c->nlp;
     if (N.ranges.empty() || N.ranges[0].n_entries == 0) return false;
@@ -1280,8 +1288,9 @@ bool nl_writes(sparc_gpu_ctx c, int ncol, bool fp32, bool bloch) {
     return waves == 4 || (waves == 3 && (long)c->nx * c->ny % 16 != 0);
 }
 
-// One pass over a block: apply (y += chi D, or y = chi D) and / or project (D = alpha gamma dV
-// chi^T y, alpha that of filter step `step` of mode `mode`, which will apply it).
+// One pass over a block: apply (y += chi D, or y = chi D) and / or project
+// (D = alpha gamma dV chi^T y, alpha that of filter step `step` of mode `mode`,
+// which will apply it).
 template <typename T>
 sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bool pr, int mode, int step, double* part,
                      size_t part_elems) {

@@ -451,7 +451,8 @@ sparc_status launch_hsweep(sparc_gpu_ctx c, const T* x, T* out, const T* xprev, 
         const long whole = n / a.round * a.round;
         slots = std::max(slots, whole + (n - whole) * a.split);
     }
-    const int slot = prof_begin(c, halves ? PK_BLOCH : mode == 2 && step > 0 ? PK_SWEEP : mode == 1 ? PK_SWEEP1 : PK_APPLY, stream);
+    const int slot = prof_begin(
+        c, halves ? PK_BLOCH : mode == 2 && step > 0 ? PK_SWEEP : mode == 1 ? PK_SWEEP1 : PK_APPLY, stream);
     const dim3 g((unsigned)(8 * slots)), b(sh.threads);
     auto go = [&](auto vx, auto mv, auto hv, auto bl) {
         k_hsweep<T, vx(), mv(), hv(), bl()><<<g, b, sh.lds, stream>>>(a);
@@ -518,9 +519,9 @@ sparc_status apply_impl(sparc_gpu_ctx c, const T* X, T* Y, int ncol, long ldx) {
     sparc_status st = nl_pass<T>(c, const_cast<T*>(X), ncol, ldx, NlApply::no, true, 0, 0);
     if (st != SPARC_OK) return st;
     // V_nl X first and the local part added to it, where that pays: the sweep reads
-    // faster than the pass, above all where planes are no multiple of
-    // 128 bytes (99 x 98 x 81 x 504 in FP64 4480 us, with the pass last 4720; 72^3 x 260
-    // 1060 and 1100)
+    // faster than the pass, above all where planes are no multiple of 128 bytes
+    // (99 x 98 x 81 x 504 in FP64 4480 us, with the pass last 4720; 72^3 x 260 1060
+    // and 1100)
     if (nl_writes(c, ncol, sizeof(T) == 4, false)) {
         if ((st = nl_pass<T>(c, Y, ncol, ldx, NlApply::write, false, 0, 0)) != SPARC_OK) return st;
         return launch_hsweep<T>(c, X, Y, Y, ncol, ldx, 2, 0);

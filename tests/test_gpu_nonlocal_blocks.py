@@ -7,6 +7,8 @@ needs a second layer of slots.
 
 Tolerances as for the other parity tests: 1e-12 for H X and 1e-11 for the filter
 in FP64, 2e-6 for H X in FP32."""
+import re
+
 import numpy as np
 import pytest
 
@@ -164,3 +166,20 @@ def test_bloch_h_written_by_the_pass(dtype):
     log(f"Bloch {dtype} {nc}: {err:.2e}")
     assert err <= (1e-12 if dtype == "float64" else 2e-6)
     assert bool(torch.isfinite(Y).all())
+
+
+@pytest.mark.parametrize("system, slots, layers", [("dense", 24, 1), ("layers", 24, 2)])
+def test_dense_systems_reach_the_slots_and_layers_they_stand_for(system, slots, layers, capfd, monkeypatch):
+    """The widest slot count, and a further layer, in the pass that the tests of
+    these systems run (the diagnostics line of context creation)."""
+    require_gpu()
+    from paper_2005_10431_amd import Context
+    monkeypatch.setenv("SPARC_GPU_DEBUG", "1")
+    for n_states in (8, 70, 200):
+        capfd.readouterr()
+        ctx = Context(SYSTEMS[system](n_states))
+        found = re.findall(r"nonlocal pass: .* (\d+) slots \(\d+ used\), (\d+) layers", capfd.readouterr().err)
+        del ctx
+        assert found
+        for s, n in found:
+            assert int(s) == slots and int(n) >= layers

@@ -360,6 +360,16 @@ ForceGrid force_grid(int n_atoms, int ncol) {
     return g;
 }
 
+// Doubles of projections that blocks of up to ncol columns take: fewer columns in
+// more parts can take more, and a call must not allocate after a wider one.
+size_t force_doubles(int n_atoms, int ncol) {
+    size_t most = 0;
+    for (int n = std::min(16, ncol);; n = std::min(n + 16, ncol)) {
+        most = std::max(most, (size_t)n_atoms * n * 16 * force_grid(n_atoms, n).parts);
+        if (n == ncol) return most;
+    }
+}
+
 template <typename T>
 sparc_status nl_force(sparc_gpu_ctx c, const T* X, int ncol, long ldx, const double* w, double* pd, double* out) {
     const ForceTab tab = force_tab(c);
@@ -409,8 +419,7 @@ sparc_status sparc_gpu_forces(sparc_gpu_ctx c, const double* d_phi, sparc_prec p
     sparc_status st;
     if ((st = ensure_force_tables(c)) != SPARC_OK) return st;
     const int na = c->n_atoms;
-    const size_t need = std::max((size_t)na * kLocalChunks * 3,
-                                 nl ? (size_t)na * ncol * 16 * force_grid(na, ncol).parts : 0);
+    const size_t need = std::max((size_t)na * kLocalChunks * 3, nl ? force_doubles(na, ncol) : 0);
     if ((st = ensure_red(c, need)) != SPARC_OK) return st;
     const ForceTab tab = force_tab(c);
     int slot = prof_begin(c, PK_FORCE_LOCAL);

@@ -69,6 +69,7 @@ struct NlPass {
     int* cand_off = nullptr;     // pairs of each atom
     int n_cand = 0, npen = 0, slots = 8;
     std::vector<NlRanges> ranges;   // the first is made for the context's full block
+    std::vector<size_t> part_upto;  // doubles of partial sums that blocks of up to n columns take
 };
 
 // Shape of a sweep over ncol columns (see sweep_plan)

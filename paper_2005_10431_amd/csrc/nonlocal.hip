@@ -936,6 +936,67 @@ static sparc_status build_ranges(sparc_gpu_ctx c, const std::vector<NlCand>& can
     return put(c, &R.red_ent, rent);
 }
 
+// Runs of entries that k_nl_reduce sums side by side: as many as the threads of a
+// workgroup allow for ncol columns.
+static int reduce_runs(int ncol) {
+    int parts = 1;
+    while (parts < 16 && 8 * parts * ncol <= 256) parts *= 2;
+    return parts;
+}
+
+// Ranges and waves of a pass over ncol columns: the cheapest by nl_cost of the
+// ranges that were built; other than those of the full block only where their
+// partial sums fit the fixed scratch array, so that the allocation-free filter
+// takes the same.  H X in FP64 with the full block's ranges and whole waves for
+// every width, and now: 72^3 x 1 238 and 81 us, x 12 261 and 107, x 24 279 and 173;
+// 120^3 x 1 1072 and 275.
+struct NlShape {
+    const NlRanges* R;
+    int nw;   // partial entries of a unit and pair (waves that share the blocks)
+};
+static NlShape nl_shape(sparc_gpu_ctx c, int ncol, bool fp32) {
+    const NlPass& N = c->nlp;
+    NlShape best{&N.ranges[0], 1};
+    double least = 0;
+    for (const NlRanges& R : N.ranges)
+        for (int nw : {1, kNlSplit}) {
+            const bool full = &R == &N.ranges[0] && nw == 1;
+            if (!full && (size_t)R.n_entries * nw * 4 * ncol > c->scratch_elems) continue;
+            // the sum over an atom's entries takes 0.023 planes per entry and run
+            const double cost = nl_cost(N.npen, c->nz, div_up(ncol, 16), div_up(c->nz, R.zlen), nw > 1, fp32) +
+                                0.023 * R.n_entries * nw / c->n_atoms / reduce_runs(ncol);
+            if (full || cost < least) {
+                least = cost;
+                best = NlShape{&R, nw};
+            }
+        }
+    return best;
+}
+
+static size_t part_doubles(const NlShape& sh, int ncol) { return (size_t)sh.R->n_entries * sh.nw * 4 * ncol; }
+
+// Partial sums of any block of up to n columns, n = 0 .. 2 n_states (halves of Bloch
+// columns): with each width's own shape a narrower block can take more than a wider
+// one, but a call must not allocate after one at least as wide (it may be captured,
+// or a graph may hold the memory).  Within a tile, runs and the shapes allowed they
+// grow with the width, so only where one of these changes is looked at.
+static void plan_partials(sparc_gpu_ctx c) {
+    NlPass& N = c->nlp;
+    const int most = 2 * c->n_states;
+    std::vector<int> at{1, 2, 4, 8};
+    for (int n = 16; n < most; n += 16) at.push_back(n);
+    for (const NlRanges& R : N.ranges)
+        for (int nw : {1, kNlSplit})
+            at.push_back((int)std::min<size_t>(most, c->scratch_elems / std::max(1L, 4 * nw * R.n_entries)));
+    at.push_back(most);
+    N.part_upto.assign(most + 1, 0);
+    for (int n : at)
+        if (n > 0 && n <= most)
+            for (bool fp32 : {false, true})
+                N.part_upto[n] = std::max(N.part_upto[n], part_doubles(nl_shape(c, n, fp32), n));
+    for (int n = 1; n <= most; ++n) N.part_upto[n] = std::max(N.part_upto[n], N.part_upto[n - 1]);
+}
+
 // The pencils of the pass and its tables.  segs: every (atom, image)
 // pair's support as line segments of the wrapped grid.
 sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, const std::vector<NlSeg>& segs) {
@@ -1110,44 +1171,8 @@ sparc_status build_nl_pass(sparc_gpu_ctx c, const std::vector<NlCand>& cands, co
                     "entries, at most %d pairs per unit\n",
                     npen, R.layer_off.back(), R.zlen, T.slots, most, R.layer_off.size() - 1, R.n_entries, R.ncl);
     }
+    plan_partials(c);
     return SPARC_OK;
-}
-
-// Runs of entries that k_nl_reduce sums side by side: as many as the threads of a
-// workgroup allow for ncol columns.
-static int reduce_runs(int ncol) {
-    int parts = 1;
-    while (parts < 16 && 8 * parts * ncol <= 256) parts *= 2;
-    return parts;
-}
-
-// Ranges and waves of a pass over ncol columns: the cheapest by nl_cost of the
-// ranges that were built; other than those of the full block only where their
-// partial sums fit the fixed scratch array, so that the allocation-free filter
-// takes the same.  H X in FP64 with the full block's ranges and whole waves for
-// every width, and now: 72^3 x 1 238 and 81 us, x 12 261 and 107, x 24 279 and 173;
-// 120^3 x 1 1072 and 275.
-struct NlShape {
-    const NlRanges* R;
-    int nw;   // partial entries of a unit and pair (waves that share the blocks)
-};
-static NlShape nl_shape(sparc_gpu_ctx c, int ncol, bool fp32) {
-    const NlPass& N = c->nlp;
-    NlShape best{&N.ranges[0], 1};
-    double least = 0;
-    for (const NlRanges& R : N.ranges)
-        for (int nw : {1, kNlSplit}) {
-            const bool full = &R == &N.ranges[0] && nw == 1;
-            if (!full && (size_t)R.n_entries * nw * 4 * ncol > c->scratch_elems) continue;
-            // the sum over an atom's entries takes 0.023 planes per entry and run
-            const double cost = nl_cost(N.npen, c->nz, div_up(ncol, 16), div_up(c->nz, R.zlen), nw > 1, fp32) +
-                                0.023 * R.n_entries * nw / c->n_atoms / reduce_runs(ncol);
-            if (full || cost < least) {
-                least = cost;
-                best = NlShape{&R, nw};
-            }
-        }
-    return best;
 }
 
 template <typename T, typename C, int S>
@@ -1178,8 +1203,11 @@ static sparc_status launch_pass(sparc_gpu_ctx c, const NlArgs<T, C>& a, int nw, 
     return SPARC_OK;
 }
 
-// Partial sums of ncol columns: the caller's memory or the context's
-static sparc_status partials(sparc_gpu_ctx c, size_t need, double** part) {
+// The context's memory for the partial sums of ncol real columns (halves), and of
+// fewer (see plan_partials)
+static sparc_status partials(sparc_gpu_ctx c, const NlShape& sh, int ncol, double** part) {
+    const std::vector<size_t>& upto = c->nlp.part_upto;
+    const size_t need = std::max(part_doubles(sh, ncol), upto[std::min<size_t>(ncol, upto.size() - 1)]);
     if (c->nl_part_elems < need) {
         if (c->nl_part) {
             SG_HIP(c, hipStreamSynchronize(c->stream));
@@ -1300,7 +1328,7 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bool
     const NlShape sh = nl_shape(c, ncol, sizeof(T) == 4);
     const NlRanges& R = *sh.R;
     const int runs = reduce_runs(ncol);
-    const size_t per_col = (size_t)R.n_entries * sh.nw * 4;
+    const size_t per_col = part_doubles(sh, 1);
     int group = ncol;
     if (pr && part) {
         // caller memory: as many columns at a time as it holds, whole
@@ -1310,7 +1338,7 @@ sparc_status nl_pass(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bool
         group = (int)std::min<size_t>((size_t)ncol, part_elems / per_col);
         if (group >= 16 && group < ncol) group -= group % 16;
     } else if (pr) {
-        if ((st = partials(c, per_col * ncol, &part)) != SPARC_OK) return st;
+        if ((st = partials(c, sh, ncol, &part)) != SPARC_OK) return st;
     }
     NlArgs<T, T> a = pass_args<T, T>(c, R, ldx, mode, step);
     a.ldD = 4L * c->n_atoms;
@@ -1349,7 +1377,7 @@ sparc_status nl_pass_k(sparc_gpu_ctx c, T* y, int ncol, long ldx, NlApply ap, bo
     const NlRanges& R = *sh.R;
     const int runs = reduce_runs(ncol);
     double* part = nullptr;
-    if (pr && (st = partials(c, (size_t)R.n_entries * sh.nw * 4 * 2 * ncol, &part)) != SPARC_OK) return st;
+    if (pr && (st = partials(c, sh, 2 * ncol, &part)) != SPARC_OK) return st;
     const long ldD = 4L * N.n_cand;
     if (c->kp_D_elems < (size_t)ldD * 2 * ncol) {
         if (c->kp_D) {
